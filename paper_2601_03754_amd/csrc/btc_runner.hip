@@ -1,10 +1,11 @@
 // Step runner: executes a list of level steps of many handles with one
 // kernel launch per (operation, kernel, padded block size) group.  Each step
-// contributes its work items (the nodes of one level, the block rows of a
-// residual, or one refinement test) and its descriptor; descriptors and items
-// of a call are packed into one upload from a pinned staging buffer
+// contributes a run of work items (the nodes of one level, the block rows of a
+// residual, or one refinement test) and its descriptor.  The descriptors of a
+// call are packed into one upload from a pinned staging buffer
 // (double-buffered, so the host can prepare the next call while the device
-// runs the current one).  Batched factorization and solve of many
+// runs the current one), with the items themselves when they are few, else
+// with the runs, which k_expand_items spreads out on the device.  Batched factorization and solve of many
 // independent instances, and the continuous-batching server, are built on it.
 #include <hip/hip_runtime.h>
 #include <string.h>
@@ -31,6 +32,26 @@ __global__ void k_reset_infos(unsigned long long* const* __restrict__ ptrs, int 
     if (t < count) *ptrs[t] = kInfoOk;
 }
 
+// A run of work items: count items from k = first on, written at byte offset
+// `out` of the call's device buffer.
+struct ItemRun {
+    int64_t out, first, count;
+    int32_t inst, level;
+};
+
+// Items of a call from its runs.  Writing the items of large batches on the
+// host (16 bytes each, more than half a million per level walk of 512 uneven
+// instances) bound their solves: 5.8 of 6.1 ms per batched solve were host
+// time.  Below kHostItems items the upload takes them as they are: a launch
+// costs more than 64 KB of host writes.
+constexpr int64_t kHostItems = 4096;
+__global__ __launch_bounds__(256) void k_expand_items(const ItemRun* __restrict__ runs, char* __restrict__ dev) {
+    const ItemRun r = runs[blockIdx.x];
+    btc::WorkItem* out = (btc::WorkItem*)(dev + r.out);
+    for (int64_t q = threadIdx.x + 256 * blockIdx.y; q < r.count; q += 256 * gridDim.y)
+        out[q] = {r.inst, r.level, r.first + q};
+}
+
 // One group = one launch.
 struct Group {
     int stage = 0;
@@ -47,7 +68,12 @@ struct Group {
     Work part[4];          // tile-parallel factor: work of each of its kernels (1..3)
     std::vector<char> descs;  // packed descriptors (all of one type)
     size_t desc_size = 0;
-    std::vector<btc::WorkItem> items;
+    std::vector<ItemRun> runs;  // work items (their output offset set by layout_call)
+    int64_t items = 0;          // their number
+    void add_run(int32_t inst, int32_t level, int64_t first, int64_t count) {
+        runs.push_back({0, first, count, inst, level});
+        items += count;
+    }
     size_t off_desc = 0, off_items = 0;
 };
 
@@ -59,6 +85,8 @@ struct Call {
     std::map<std::tuple<int, int, int, int>, Group> groups;  // (stage, op, kind, np)
     std::vector<unsigned long long*> resets;
     size_t off_resets = 0;
+    bool expand = false;  // the items are written by k_expand_items
+    size_t off_runs = 0, runs = 0;
 };
 
 }  // namespace
@@ -171,7 +199,9 @@ void add_untimed(btc_runner_s* r, const std::tuple<int, int, int, int>& key, con
 
 namespace {
 
-int slot_reserve(btc_runner r, btc_runner_s::Slot& s, size_t bytes) {
+// Room for `bytes` in the slot's staging buffer and `dev_bytes` in its device
+// buffer.
+int slot_reserve(btc_runner r, btc_runner_s::Slot& s, size_t bytes, size_t dev_bytes) {
     if (s.pending) {
         const auto t0 = std::chrono::steady_clock::now();
         const hipError_t e = hipEventSynchronize(s.ev);
@@ -189,12 +219,12 @@ int slot_reserve(btc_runner r, btc_runner_s::Slot& s, size_t bytes) {
         }
         s.hcap = cap;
     }
-    if (bytes > s.dcap) {
+    if (dev_bytes > s.dcap) {
         // the device buffer may still be read by launches of an earlier call
         if (hipStreamSynchronize(r->st) != hipSuccess) return BTC_ERR_HIP;
         dev_free(r->alloc, s.dev, r->st);
         s.dev = nullptr;
-        const size_t cap = std::max(bytes, (size_t)1 << 16) * 2;
+        const size_t cap = std::max(dev_bytes, (size_t)1 << 16) * 2;
         if (dev_alloc(r->alloc, (void**)&s.dev, cap, r->st) != hipSuccess) {
             s.dcap = 0;
             return BTC_ERR_OOM;
@@ -386,8 +416,7 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             const int32_t inst = (int32_t)(g.descs.size() / sizeof(btc::FactorDesc));
             push_desc(g, fd);
             add_work(r, g, s, mixed);
-            const int64_t nodes = level_nodes(h->N, s.level);
-            for (int64_t q = 0; q < nodes; ++q) g.items.push_back({inst, s.level, q});
+            g.add_run(inst, s.level, 0, level_nodes(h->N, s.level));
             continue;
         }
         const Workspace w = carve(h, h->ws_m);
@@ -411,11 +440,9 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             }
             add_work(r, g, s, mixed);
             if (range) {
-                const int64_t cnt = chunk_count(h->N, s.level, s.level_end);
-                for (int64_t q = 0; q < cnt; ++q) g.items.push_back({inst, s.level | (s.level_end << 8), q});
+                g.add_run(inst, s.level | (s.level_end << 8), 0, chunk_count(h->N, s.level, s.level_end));
             } else {
-                const int64_t nodes = level_nodes(h->N, s.level);
-                for (int64_t q = 0; q < nodes; ++q) g.items.push_back({inst, s.level, q});
+                g.add_run(inst, s.level, 0, level_nodes(h->N, s.level));
             }
         } else if (s.op == BTC_OP_RESIDUAL) {
             Group& g = groups[std::make_tuple(s.stage, s.op, 0, np)];
@@ -427,7 +454,7 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             const int32_t inst = (int32_t)(g.descs.size() / sizeof(btc::ResidualDesc));
             push_desc(g, residual_desc(h, w, s.B, s.X, s.nrhs, mixed));
             add_work(r, g, s, mixed);
-            for (int64_t q = 0; q < h->N; ++q) g.items.push_back({inst, 0, q});
+            g.add_run(inst, 0, 0, h->N);
         } else {
             Group& g = groups[std::make_tuple(s.stage, s.op, 0, 0)];
             g.stage = s.stage;
@@ -439,43 +466,81 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             const int steps_budget = mixed ? 1 + h->max_refine : 1;
             push_desc(g, ir_desc(h, w, s.nrhs, tol, steps_budget));
             add_work(r, g, s, mixed);
-            g.items.push_back({inst, 0, 0});
+            g.add_run(inst, 0, 0, 1);
         }
     }
 
 }
 
-// Offsets of the call's reset list, descriptors and items from `base`;
-// returns the end.
-size_t layout_call(Call& c, size_t base) {
+// Offsets of the call's reset list, descriptors and items (or runs and, past
+// *upload, the items to be expanded on the device) from `base`; returns the
+// end, *upload the end of what the host writes.
+size_t layout_call(Call& c, size_t base, bool may_expand, size_t* upload) {
     c.off_resets = base;
     size_t bytes = align256(base + c.resets.size() * sizeof(unsigned long long*));
+    int64_t items = 0;
+    c.runs = 0;
     for (auto& kv : c.groups) {
         Group& g = kv.second;
         g.off_desc = bytes;
         bytes = align256(bytes + g.descs.size());
-        g.off_items = bytes;
-        bytes = align256(bytes + g.items.size() * sizeof(btc::WorkItem));
+        items += g.items;
+        c.runs += g.runs.size();
     }
+    c.expand = may_expand && items > kHostItems;
+    if (c.expand) {
+        c.off_runs = bytes;
+        bytes = align256(bytes + c.runs * sizeof(ItemRun));
+        *upload = bytes;
+    }
+    for (auto& kv : c.groups) {
+        Group& g = kv.second;
+        g.off_items = bytes;
+        for (ItemRun& r : g.runs) {
+            r.out = (int64_t)bytes;
+            bytes += (size_t)r.count * sizeof(btc::WorkItem);
+        }
+        bytes = align256(bytes);
+    }
+    if (!c.expand) *upload = bytes;
     return bytes;
 }
 
 void write_call(const Call& c, char* host) {
     if (!c.resets.empty()) memcpy(host + c.off_resets, c.resets.data(), c.resets.size() * sizeof(unsigned long long*));
+    size_t off_runs = c.off_runs;
     for (auto& kv : c.groups) {
         const Group& g = kv.second;
         memcpy(host + g.off_desc, g.descs.data(), g.descs.size());
-        memcpy(host + g.off_items, g.items.data(), g.items.size() * sizeof(btc::WorkItem));
+        if (c.expand) {
+            memcpy(host + off_runs, g.runs.data(), g.runs.size() * sizeof(ItemRun));
+            off_runs += g.runs.size() * sizeof(ItemRun);
+            continue;
+        }
+        for (const ItemRun& r : g.runs) {
+            btc::WorkItem* out = (btc::WorkItem*)(host + r.out);
+            for (int64_t q = 0; q < r.count; ++q) out[q] = {r.inst, r.level, r.first + q};
+        }
     }
 }
 
-// Enqueue the call (its descriptors already in `dev`): status resets, then
-// the groups stage by stage, the independent groups of a stage spread over
+// Enqueue the call (its descriptors already in `dev`): the work items where
+// they are expanded on the device, status resets, then the groups stage by stage, the independent groups of a stage spread over
 // the runner's streams.
 int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
     hipError_t e = hipSuccess;
     auto& groups = c.groups;
     const auto& resets = c.resets;
+    if (c.expand) {
+        int64_t longest = 1;
+        for (auto& kv : groups)
+            for (const ItemRun& r : kv.second.runs) longest = std::max(longest, r.count);
+        const unsigned y = (unsigned)std::min<int64_t>((longest + 1023) / 1024, 64);
+        hipLaunchKernelGGL(k_expand_items, dim3((unsigned)c.runs, y), dim3(256), 0, st,
+                           (const ItemRun*)(dev + c.off_runs), dev);
+        e = hipGetLastError();
+        if (e != hipSuccess) return to_code(e);
+    }
     if (!resets.empty()) {
         const int n = (int)resets.size();
         hipLaunchKernelGGL(k_reset_infos, dim3((n + 255) / 256), dim3(256), 0, st,
@@ -485,7 +550,7 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
     }
     if (timing && !r->pending.empty()) drain_prof(r, false);
     auto launch_group = [&](const Group& g) -> int {
-        const int64_t items = (int64_t)g.items.size();
+        const int64_t items = g.items;
         hipStream_t gs = g.lane == 0 ? st : r->side[g.lane - 1];
         hipEvent_t ea = nullptr, eb = nullptr;
         const bool split = g.prof && timing && g.op == BTC_OP_FACTOR && tiled_kind(g.kind);
@@ -568,7 +633,7 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
                 continue;
             }
             const double np = (double)std::max(gr.np, 8);
-            const double w = (gr.op == BTC_OP_FACTOR ? np : 1.0) * np * np * (double)gr.items.size();
+            const double w = (gr.op == BTC_OP_FACTOR ? np : 1.0) * np * np * (double)gr.items;
             order.push_back({w, &gr});
         }
         std::sort(order.begin(), order.end(), [](const std::pair<double, Group*>& a, const std::pair<double, Group*>& b) {
@@ -658,9 +723,10 @@ int runner_run(btc_runner r, int32_t count, const btc_step* steps) {
         r->rec.push_back(std::move(c));
         return BTC_OK;
     }
-    const size_t bytes = layout_call(c, 0);
+    size_t bytes = 0;
+    const size_t dev_bytes = layout_call(c, 0, true, &bytes);
     btc_runner_s::Slot& sl = r->slot[r->cur];
-    rc = slot_reserve(r, sl, bytes);
+    rc = slot_reserve(r, sl, bytes, dev_bytes);
     if (rc != BTC_OK) return rc;
     write_call(c, sl.host);
     hipError_t e = hipMemcpyAsync(sl.dev, sl.host, bytes, hipMemcpyHostToDevice, st);
@@ -704,7 +770,10 @@ BTC_API int btc_graph_end(btc_runner r, btc_graph* out) {
     btc_graph g = new (std::nothrow) btc_graph_s();
     if (!g) return BTC_ERR_OOM;
     size_t bytes = 0;
-    for (auto& c : calls) bytes = layout_call(c, bytes);
+    for (auto& c : calls) {
+        size_t upload;
+        bytes = layout_call(c, bytes, false, &upload);
+    }
     std::vector<char> host(std::max<size_t>(bytes, 256));
     for (auto& c : calls) write_call(c, host.data());
     // the recorded work of the runner's stream must be done before the

@@ -190,3 +190,28 @@ def test_level_ranges_equal_single_levels(btc, precision, N, n, m):
         assert np.array_equal(X2.cpu().numpy(), Xr.cpu().numpy())
     r.close()
     f.close()
+
+
+@pytest.mark.parametrize("N", [8191, 8193, 40000])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_batched_items_expanded_on_device(btc, N, precision):
+    """Calls of up to 4096 work items upload them (level 0 of N = 8191), larger
+    ones spread them out on the device (N = 8193: 4097; N = 40000: runs of
+    more than one workgroup stride): every item once, next to a one-block and
+    a ragged instance, bit for bit the single instances' results."""
+    prs = [inputs.block_tridiag(a, b, seed=7 + a, nrhs=2) for a, b in ((N, 4), (1, 3), (37, 4))]
+    r = btc.Runner()
+    hs = [btc.btc_create(p.N, p.n, precision) for p in prs]
+    Bs = [dev(p.B) for p in prs]
+    Xs = [torch.empty_like(b) for b in Bs]
+    Ds, Es = [dev(p.D) for p in prs], [dev(p.E) for p in prs]
+    r.factor_batched(hs, Ds, Es)
+    r.solve_batched(hs, Bs, Xs, 2)
+    r.sync()
+    for k, p in enumerate(prs):
+        Xsng, blocks_s, _ = single(btc, p, precision)
+        assert np.array_equal(Xs[k].cpu().numpy(), Xsng), (k, p.N)
+        blocks_b = btc.btc_export_factor(hs[k], p.N, p.n)
+        assert all(np.array_equal(a, b) for a, b in zip(blocks_b, blocks_s))
+        btc.btc_destroy(hs[k])
+    r.close()
