@@ -259,8 +259,9 @@ BTC_API void btc_destroy(btc_handle h);
 
 /*
  * btc_footprint_bytes -- device bytes a handle of this shape holds after one
- * solve with nrhs right-hand sides (for admission control).  0 on invalid
- * arguments.
+ * solve with nrhs right-hand sides (for admission control), not counting the
+ * 8 (N + 1) bytes of synchronisation words that btc_solve takes on its first
+ * call.  0 on invalid arguments.
  */
 BTC_API size_t btc_footprint_bytes(int64_t N, int64_t n, int32_t precision, int64_t nrhs);
 
@@ -341,8 +342,7 @@ typedef struct {
     int32_t first;          /* BTC_FP32_IR sweeps: 1 for the first solve (reads B, sets X) */
     int32_t level_end;      /* FORWARD / BACKWARD: 0 for the single level `level`; else the
                                levels level .. level_end-1 in one step (level < level_end <=
-                               floor(log2 N)+1): the elimination subtrees of those levels, one
-                               workgroup each (btc_sweep_ranges gives the library's ranges) */
+                               floor(log2 N)+1; btc_sweep_ranges gives ranges) */
     int32_t stage;          /* 0..7: order of dependent steps within one call */
     int32_t pad;
 } btc_step;
@@ -369,15 +369,16 @@ BTC_API int btc_runner_create(void *stream, btc_runner *out);
 BTC_API int btc_runner_run(btc_runner r, int32_t count, const btc_step *steps);
 
 /*
- * btc_sweep_ranges -- the level ranges in which the library runs a sweep of
- * an instance with N blocks (host computation): bounds[0] = 0 < bounds[1] <
- * ... < bounds[r] = floor(log2 N)+1, r returned (bounds needs r+1 <= max
- * entries; -2 if it is too short).  A range of one level runs one wavefront
- * per node; a longer range runs each elimination subtree of its levels in
- * one workgroup (section "Cholesky Solve": the forward step of a node reads
- * only results of its descendants, the backward step only those of its
- * ancestors), so it costs one launch and one dependency step instead of one
- * per level.
+ * btc_sweep_ranges -- level ranges for the sweep steps of an instance with N
+ * blocks (host computation): bounds[0] = 0 < bounds[1] < ... < bounds[r] =
+ * floor(log2 N)+1, r returned (bounds needs r+1 <= max entries; -2 if it is
+ * too short).  A level with 4096 nodes or more is a range of its own; a
+ * longer range holds levels of which every elimination subtree has at most
+ * four nodes per level.  Any range may be stepped (level_end): a step over
+ * several levels is one launch in which every node waits for the nodes it
+ * depends on (section "Cholesky Solve": the forward step of a node reads only
+ * results of its descendants, the backward step only those of its
+ * ancestors).
  */
 BTC_API int btc_sweep_ranges(int64_t N, int32_t *bounds, int32_t max);
 
@@ -432,14 +433,14 @@ BTC_API void btc_graph_destroy(btc_graph g);
  *     precisions, n 17..32, and any precision, n 33..64: 0 one workgroup per
  *     node, 1 the tile-parallel level step (different rounding orders:
  *     results change at round-off level when the choice changes)
- *   BTC_OP_FORWARD / BACKWARD / RESIDUAL (nrhs > 1; level ignored): 0 four
- *     right-hand-side columns per dependency-chain group, 1 one (identical
- *     results)
+ *   BTC_OP_FORWARD / BACKWARD (level ignored): 0 with more than four
+ *     right-hand sides, 8 or 16 columns per pass over the factor (FP64), 1
+ *     four; BTC_OP_RESIDUAL (nrhs > 1; level ignored): 0 four columns per
+ *     dependency-chain group, 1 one (identical results)
  *   BTC_TUNE_SWEEP_SHAPE, any precision, any n (level ignored): the launch
- *     shape of both sweeps: 0 level ranges (btc_sweep_ranges) with
- *     workgroups of 4 wavefronts, 1 one launch per level, 2 level ranges
- *     with workgroups of 8 wavefronts (ranges one level deeper); identical
- *     results
+ *     shape of both sweeps: 0 one launch per level for levels of many nodes,
+ *     the levels above them in one launch, 1 one launch per level, 2 all
+ *     levels in one launch; identical results
  * With the environment variable BTC_TUNE_CACHE naming a file, the table
  * (kernel variants and the strategy choices of btc_autotune_strategy) is
  * read from that file when the library first consults it, and written back

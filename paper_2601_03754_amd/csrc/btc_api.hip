@@ -18,6 +18,14 @@
 
 namespace btc_host {
 __global__ void k_set_u64(unsigned long long* p, unsigned long long v) { *p = v; }
+__global__ void k_zero_words(int* p, int64_t count) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < count) p[k] = 0;
+}
+hipError_t launch_zero_words(int* p, int64_t count, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, p, count);
+    return hipGetLastError();
+}
 
 namespace {
 std::mutex g_alloc_mu;
@@ -535,6 +543,8 @@ BTC_API int btc_solve(btc_handle h, const double* B, double* X, int64_t nrhs, vo
         if (rc != BTC_OK) return rc;
     }
     if (own) {
+        rc = ensure_flow(h, st);
+        if (rc != BTC_OK) return rc;
         const Workspace w = carve(h, h->ws_m);  // one layout per allocation
         h->stream = st;
         rc = solve_with(h, w, B, X, nrhs, st, info);
@@ -545,9 +555,16 @@ BTC_API int btc_solve(btc_handle h, const double* B, double* X, int64_t nrhs, vo
     }
     void* mem = nullptr;
     const Allocator a = current_allocator();
-    hipError_t e = dev_alloc_async(a, &mem, workspace_bytes(h->N, h->n, h->precision, nrhs), st);
+    const size_t ws = (workspace_bytes(h->N, h->n, h->precision, nrhs) + 255) & ~(size_t)255;
+    hipError_t e = dev_alloc_async(a, &mem, ws + flow_bytes(h->N), st);
     if (e != hipSuccess) return to_code(e);
-    const Workspace w = carve_at(mem, h->N, h->n, h->precision, nrhs);
+    Workspace w = carve_at(mem, h->N, h->n, h->precision, nrhs);
+    w.flow = (int*)((char*)mem + ws);
+    e = launch_zero_words(w.flow, 2 * h->N + 2, st);
+    if (e != hipSuccess) {
+        dev_free_async(a, mem, st);
+        return to_code(e);
+    }
     h->stream = st;
     rc = solve_with(h, w, B, X, nrhs, st, info);
     dev_free_async(a, mem, st);
@@ -667,6 +684,11 @@ BTC_API int btc_export_factor(btc_handle h, double* Ld, double* Rb, double* Tb) 
                 memcpy(dst, tmp.data() + (size_t)btc::perm_pos(N, l, i) * nn, nn * sizeof(double));
             else
                 memset(dst, 0, nn * sizeof(double));
+            // above the diagonal the stored L_ii holds its inverted diagonal
+            // tiles (or nothing)
+            if (a == 0)
+                for (int64_t r = 0; r + 1 < h->n; ++r)
+                    memset(dst + r * h->n + r + 1, 0, (size_t)(h->n - 1 - r) * sizeof(double));
         }
     }
     return BTC_OK;

@@ -199,13 +199,13 @@ __global__ __launch_bounds__(kWave) void k_chain_solve(ChainDesc P) {
             double a = 0.0;
             if (lane < n) {
                 a = P.B[((size_t)(c - 1) * n + lane) * m + q];
-                // contributions of c's descendants in the first k levels
-                for (int l2 = 0; l2 < k; ++l2) {
-                    const int64_t s2 = (int64_t)1 << l2;
-                    const size_t off = (size_t)lane * m + q;
-                    a -= P.U[(size_t)perm_pos(N, l2, c - s2) * nm + off];
-                    if (c + s2 <= N) a -= P.V[(size_t)perm_pos(N, l2, c + s2) * nm + off];
-                }
+                // the sums c's descendants in the first k levels left for it:
+                // U of the nearest on the left, V of the nearest on the right
+                const size_t off = (size_t)lane * m + q;
+                if (k > 0) a -= P.U[(size_t)perm_pos(N, k - 1, c - ((int64_t)1 << (k - 1))) * nm + off];
+                int l2 = k - 1;
+                while (l2 >= 0 && c + ((int64_t)1 << l2) > N) --l2;
+                if (l2 >= 0) a -= P.V[(size_t)perm_pos(N, l2, c + ((int64_t)1 << l2)) * nm + off];
             }
             if (j > 1) {
                 // - R'_{j-1} y_{j-1}

@@ -12,6 +12,10 @@
 //     overwritten by L_ii when block i is eliminated; Rb[p] / Tb[p] first hold
 //     the right / left coupling of block i at its level and are overwritten by
 //     R_i = C_{i+s,i} L_ii^{-T} and T_i = L_ii^{-1} C_{i,i-s}.
+//   * the level kernels also leave the inverse of every 16 x 16 diagonal tile
+//     of L_ii in Ld: its strict lower part, transposed, in the strict upper
+//     part of that tile (its diagonal is 1 / L_jj), for the sweeps' triangular
+//     solves; the rest of the strict upper triangle is not written.
 //   * inside a kernel, blocks are staged in LDS padded to NP x NP (NP >= n,
 //     a multiple of 8) with row stride NP+1 doubles, so that a wavefront
 //     reading one column hits 32 distinct banks.  Padding is the identity on
@@ -47,17 +51,23 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(const void* p, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
 }
-__device__ __forceinline__ void buf_ld(double& x, __amdgpu_buffer_rsrc_t r, int off) {
-    x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+// (soff: a wave-uniform part of the offset, included in the range check;
+// AUX: cache policy bits)
+template <int AUX = 0>
+__device__ __forceinline__ void buf_ld(double& x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+    x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, AUX));
 }
-__device__ __forceinline__ void buf_ld(float& x, __amdgpu_buffer_rsrc_t r, int off) {
-    x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+template <int AUX = 0>
+__device__ __forceinline__ void buf_ld(float& x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+    x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, AUX));
 }
+template <int AUX = 0>
 __device__ __forceinline__ void buf_st(double x, __amdgpu_buffer_rsrc_t r, int off) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x), r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x), r, off, 0, AUX);
 }
+template <int AUX = 0>
 __device__ __forceinline__ void buf_st(float x, __amdgpu_buffer_rsrc_t r, int off) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, off, 0, AUX);
 }
 // Element (r, c) of an n x n row-major block of S: byte offset, or kOob
 // when not `ok`.

@@ -152,6 +152,26 @@ __global__ __launch_bounds__(NT) void k_factor_level_f64(Launch<FactorDesc> L) {
             for (int c = 0; c < NP; ++c) base[c * stride] = x[c];
         }
     }
+    // inverse of every diagonal tile of L_ii (16 x 16, or the whole block when
+    // smaller), stored above the diagonal of L_ii: thread c of a group solves
+    // for column c of its tile
+    for (int col = (NT >= 3 * NP ? tid - 2 * NP : tid); col >= 0 && col < NP; col += NT) {
+        constexpr int TS = NP < 16 ? NP : 16;
+        const int t0 = col / TS * TS, c = col % TS;
+        double x[TS];
+#pragma unroll
+        for (int j = 0; j < TS; ++j) x[j] = (j == c) ? 1.0 : 0.0;
+#pragma unroll
+        for (int j = 0; j < TS; ++j) {
+            x[j] *= invd[t0 + j];
+#pragma unroll
+            for (int k = j + 1; k < TS; ++k) x[k] = fma(-sA[(t0 + k) * LD + t0 + j], x[j], x[k]);
+        }
+        double* dst = P.Ld + (size_t)pi * nn + (size_t)col * n + t0;
+#pragma unroll
+        for (int j = 1; j < TS; ++j)
+            if (j > c && t0 + j < n) dst[j] = x[j];
+    }
     __syncthreads();
 
     // 4./5. separator update and fill-in, straight from registers to HBM
@@ -174,7 +194,10 @@ __global__ __launch_bounds__(NT) void k_factor_level_f64(Launch<FactorDesc> L) {
                                                       : P.Tb + (size_t)perm_pos(N, lvl + 1, rgt) * nn;
         tile_store_global<NP, NT>(t, dst, n, -1.0);
     }
-    lds_store<NP>(P.Ld + (size_t)pi * nn, sA, n, true, tid, NT);
+    for (int idx = tid; idx < NP * NP; idx += NT) {
+        const int r = idx / NP, c = idx % NP;
+        if (r < n && c <= r) P.Ld[(size_t)pi * nn + (size_t)r * n + c] = sA[r * LD + c];
+    }
     if (has_r) lds_store<NP>(P.Rb + (size_t)pi * nn, sB, n, false, tid, NT);
     if (has_l) lds_store<NP>(P.Tb + (size_t)pi * nn, sD, n, false, tid, NT);
 }

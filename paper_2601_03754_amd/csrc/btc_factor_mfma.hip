@@ -187,7 +187,7 @@ __global__ __launch_bounds__(MfmaCfg<NP>::NT) void k_factor_level_mfma(Launch<Fa
             acc_store_global(acc, dst, n, w * kT, t * kT);
         }
     }
-    lds_store<NP>(P.Ld + (size_t)pi * nn, sS, n, true, tid, NT);
+    store_factor_lds<NP>(P.Ld + (size_t)pi * nn, sS, sInv, n, tid, NT);
     if (has_r) lds_store<NP>(P.Rb + (size_t)pi * nn, sB, n, false, tid, NT);
     if (has_l) lds_store<NP>(P.Tb + (size_t)pi * nn, sD, n, false, tid, NT);
 }

@@ -108,6 +108,7 @@ struct btc_handle_s {
     // stream before that point takes a workspace of its own)
     void* ws = nullptr;
     int64_t ws_m = 0;
+    int* flow = nullptr;  // flags of the sweeps that use ws
     hipStream_t ws_stream = nullptr;
     hipEvent_t ws_ev = nullptr;
     bool ws_ev_valid = false;
@@ -185,6 +186,7 @@ inline void free_all(btc_handle h) {
     dfree(h, h->T32);
     dfree(h, h->info);
     dfree(h, h->ws);
+    dfree(h, h->flow);
 }
 
 inline hipEvent_t take_event(btc_handle h) {
@@ -247,7 +249,13 @@ struct Workspace {
     double* part = nullptr;
     double *rp = nullptr, *rq = nullptr;  // residual scratch
     btc::IrState* ir = nullptr;
+    int* flow = nullptr;  // flags and counters of the sweeps (flow_bytes; null: one launch per level)
 };
+
+// Flags (one per node and direction) and two work counters of the sweeps that
+// take several levels per launch; all 0 between launches.
+inline size_t flow_bytes(int64_t N) { return (2 * (size_t)N + 2) * sizeof(int); }
+hipError_t launch_zero_words(int* p, int64_t count, hipStream_t st);
 
 // Workspace layout of an (N, n, precision) system with m right-hand sides in
 // the memory at `base` (workspace_bytes long, 256-byte aligned).
@@ -288,7 +296,19 @@ inline Workspace carve_at(void* base, int64_t N, int64_t n, int32_t prec, int64_
     return w;
 }
 
-inline Workspace carve(btc_handle h, int64_t m) { return carve_at(h->ws, h->N, h->n, h->precision, m); }
+inline Workspace carve(btc_handle h, int64_t m) {
+    Workspace w = carve_at(h->ws, h->N, h->n, h->precision, m);
+    w.flow = h->flow;
+    return w;
+}
+
+// The handle's sweep flags (taken on the first sweep over several levels).
+inline int ensure_flow(btc_handle h, hipStream_t st) {
+    if (h->flow) return BTC_OK;
+    hipError_t e = dev_alloc(h->alloc, (void**)&h->flow, flow_bytes(h->N), st);
+    if (e == hipSuccess) e = launch_zero_words(h->flow, 2 * h->N + 2, st);
+    return to_code(e);
+}
 
 inline int ensure_workspace(btc_handle h, int64_t m) {
     if (m <= h->ws_m && h->ws) return BTC_OK;
@@ -415,10 +435,15 @@ inline int32_t factor_flags(btc_handle h, int level) {
     return (eager(level) ? btc::kFactorEagerT : 0) | (eager(level - 1) ? btc::kFactorDeferredDone : 0);
 }
 
-// Right-hand-side columns per dependency-chain group of a sweep or residual
-// launch (results do not depend on it).
+// Right-hand-side columns per dependency-chain group of a residual launch
+// (results do not depend on it).
 inline int sweep_mc(int op, int kind, int np, int64_t m) {
     return (m <= 1 || tune_variant(op, kind, np, 0) == 1) ? 1 : 4;
+}
+// Right-hand-side columns per pass of a sweep launch (results do not depend
+// on it; FP32 sweeps always take 16).
+inline int sweep_cols(int op, int kind, int np, int64_t m) {
+    return (m <= 4 || tune_variant(op, kind, np, 0) == 1) ? 4 : 16;
 }
 
 // deferred: some item of the launch has deferred updates to apply (tile-
@@ -495,57 +520,45 @@ inline int launch_factor(btc_handle h, const double* A_diag, const double* A_off
     return BTC_OK;
 }
 
-// Level ranges of a sweep, one launch each: a range of one level runs one
-// wavefront per node (levels with many nodes: the most parallel form), a
-// range of several levels one workgroup per subtree (launch_sweep's chunk
-// form), which saves a launch and a dependency step per level.  A node step
-// is latency bound (one wavefront streams its blocks slab by slab: about
-// 15 us FP32, 45 us FP64 at n = 96), so a range takes only levels whose
-// subtree nodes the workgroup's wavefronts cover in one round each: its time
-// is then one node step per level, as with one launch per level.  Greedy
-// from level 0: a level with at least kSweepNodesPerLevel nodes is a range
-// of its own; otherwise the range grows while every level of a subtree has
-// at most kChunkWaves nodes.
-constexpr int64_t kSweepNodesPerLevel = 4096;
-
-inline int64_t chunk_rounds(int64_t N, int l0, int l1, int kw) {
-    int64_t r = 0;
-    for (int l = l0; l < l1; ++l) {
-        const int64_t per = (int64_t)1 << (l1 - l - 1);
-        const int64_t nodes = level_nodes(N, l);
-        const int64_t c = per < nodes ? per : nodes;
-        r += (c + kw - 1) / kw;
-    }
-    return r;
-}
-
-// Sweep launch shapes (tune key BTC_TUNE_SWEEP_SHAPE): 0 level ranges with
-// 4-wavefront workgroups, 1 one launch per level, 2 level ranges with
-// 8-wavefront workgroups.
+// Level ranges of a sweep, one launch each: a single level (one workgroup
+// per node, nothing to wait for), or the levels from l0 up in one launch
+// (k_sweep_flow: the workgroups wait for each other's flags, which saves a
+// launch, the start of its workgroups and the first loads of its blocks per
+// level).  A level of the first kind costs nothing more while it has work for
+// the whole GPU; measured on one instance (FP64, n = 96, m = 1), levels with
+// at most kFlowNodes nodes are faster in one launch.
+constexpr int64_t kFlowNodes = 1024;
+// Sweep launch shapes (tune key BTC_TUNE_SWEEP_SHAPE): 0 as above, 1 one
+// launch per level, 2 all levels in one launch.
 inline int sweep_shape(int32_t prec, int64_t n) {
     return tune_variant(BTC_TUNE_SWEEP_SHAPE, is_mixed(prec) ? 1 : 0, btc::padded_block((int)n), 0);
 }
-inline int shape_waves(int shape) { return shape == 2 ? 8 : 4; }
 
-// Subtrees of the range [l0, l1): those j with a level-l0 node in (j 2^l1, (j+1) 2^l1).
-inline int64_t chunk_count(int64_t N, int l0, int l1) {
-    return ((N - ((int64_t)1 << l0)) >> l1) + 1;
+// First level of the range in one launch (levels: none): nodes[l] nodes at
+// level l.
+inline int flow_start(const int64_t* nodes, int levels, int shape) {
+    if (shape == 1) return levels;
+    int l = 0;
+    while (shape != 2 && l < levels && nodes[l] > kFlowNodes) ++l;
+    return l + 1 < levels ? l : levels;  // one level alone is no range
 }
 
 // bounds[0] = 0 < bounds[1] < ... < bounds[r] = levels; returns r.
-inline int sweep_ranges(int64_t N, int levels, int* bounds, int shape = 0) {
-    int r = 0, l0 = 0;
+inline int range_bounds(int flow, int levels, int* bounds) {
+    int r = 0;
     bounds[0] = 0;
-    const int kw = shape_waves(shape);
-    while (l0 < levels) {
-        int l1 = l0 + 1;
-        if (shape != 1 && level_nodes(N, l0) < kSweepNodesPerLevel)
-            while (l1 < levels && chunk_rounds(N, l0, l1 + 1, kw) <= l1 + 1 - l0) ++l1;
-        bounds[++r] = l1;
-        l0 = l1;
-    }
+    for (int l = 1; l <= flow && l <= levels; ++l) bounds[++r] = l;
+    if (flow < levels) bounds[++r] = levels;
     return r;
 }
+inline int sweep_ranges(int64_t N, int levels, int* bounds, int shape) {
+    int64_t nodes[66];
+    for (int l = 0; l < levels; ++l) nodes[l] = level_nodes(N, l);
+    return range_bounds(flow_start(nodes, levels, shape), levels, bounds);
+}
+
+// Nodes of the levels l0 .. l1-1.
+inline int64_t range_nodes(int64_t N, int l0, int l1) { return (N >> l0) - (N >> l1); }
 
 // One range of a sweep (forward or backward) of one instance.
 template <class T>
@@ -553,13 +566,20 @@ inline hipError_t sweep_range(btc_handle h, btc::Launch<btc::SweepDesc<T>>& L, i
                               hipStream_t st) {
     const int np = btc::padded_block((int)h->n);
     const int op = bwd ? BTC_OP_BACKWARD : BTC_OP_FORWARD;
-    const int mc = sweep_mc(op, sizeof(T) == 4, np, L.single.m);
-    const bool chunk = l1 > l0 + 1;
-    L.level = chunk ? (l0 | (l1 << 8)) : l0;
-    const int64_t items = chunk ? chunk_count(h->N, l0, l1) : level_nodes(h->N, l0);
-    const int kw = shape_waves(sweep_shape(h->precision, h->n));
+    const int mc = sweep_cols(op, sizeof(T) == 4, np, L.single.m);
+    const bool flow = l1 > l0 + 1;
+    L.level = flow ? (l0 | (l1 << 8)) : l0;
+    int* const words = L.single.flow;  // forward flags, backward flags, two counters
+    if (flow) {
+        L.ticket = words + 2 * h->N + (bwd ? 1 : 0);
+        if (bwd) L.single.flow = words + h->N;
+    }
+    const int64_t items = flow ? range_nodes(h->N, l0, l1) : level_nodes(h->N, l0);
     // profiled per range, attributed to its first level
-    return timed(h, bwd ? 2 : 1, l0, st, [&] { return btc::launch_sweep(L, np, items, bwd, mc, st, chunk, kw); });
+    const hipError_t e =
+        timed(h, bwd ? 2 : 1, l0, st, [&] { return btc::launch_sweep(L, np, items, bwd, mc, st, flow); });
+    L.single.flow = words;
+    return e;
 }
 
 template <class T>
@@ -585,7 +605,7 @@ inline hipError_t sweeps(btc_handle h, const btc::SweepDesc<T>& d, hipStream_t s
     int b[66];
     // the levels of the multi-stage order (all of them, or the first k), in
     // ranges; a k-stage order solves along its chain in between
-    const int r = sweep_ranges(h->N, h->nd_levels, b, sweep_shape(h->precision, h->n));
+    const int r = sweep_ranges(h->N, h->nd_levels, b, d.flow ? sweep_shape(h->precision, h->n) : 1);
     for (int k = 0; k < r; ++k) {
         hipError_t e = sweep_range(h, L, b[k], b[k + 1], false, st);
         if (e != hipSuccess) return e;
@@ -611,6 +631,7 @@ inline btc::SweepDesc<double> sweep_desc64(btc_handle h, const Workspace& w, con
     p.Y = w.Y;
     p.U = w.U;
     p.V = w.V;
+    p.flow = w.flow;
     p.info = h->info;
     p.N = h->N;
     p.n = (int32_t)h->n;
@@ -630,6 +651,7 @@ inline btc::SweepDesc<float> sweep_desc32(btc_handle h, const Workspace& w, cons
     p.Y = w.y;
     p.U = w.u;
     p.V = w.v;
+    p.flow = w.flow;
     p.X64 = X;
     p.info = h->info;
     p.skip = &w.ir->done;

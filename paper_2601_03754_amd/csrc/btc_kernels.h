@@ -28,6 +28,7 @@ struct Launch {
     const D* descs;         // explicit mode: descriptor array (device)
     const WorkItem* items;  // explicit mode: item array (device); nullptr = implicit
     int32_t level;          // implicit mode: level of every item
+    int* ticket;            // sweeps over a range of levels: work counter (0 between launches)
 };
 
 template <class D>
@@ -88,8 +89,8 @@ struct SweepDesc {
     const double* B64;         // optional: read the right-hand side from this FP64 array instead
     T* X;                      // [N][n][m] solution (original order)
     T* Y;                      // [N][n][m] permuted: forward-sweep result y
-    T* U;                      // [N][n][m] permuted: R_i y_i left for i+s
-    T* V;                      // [N][n][m] permuted: T_i^T y_i left for i-s
+    T* U;                      // [N][n][m] permuted: what i's subtree leaves for i+s
+    T* V;                      // [N][n][m] permuted: what i's subtree leaves for i-s
     double* X64;               // optional: X64 = X (first) or X64 += X after the backward sweep
     const unsigned long long* info;
     const int* skip;           // optional: the item does nothing while *skip != 0
@@ -98,6 +99,8 @@ struct SweepDesc {
     int32_t m;
     int32_t first;
     int32_t pad;
+    int* flow;                 // sweeps over a range of levels: one flag per node of the range
+                               // (indexed by permuted position), 0 between launches
 };
 
 // Device-side state of iterative refinement of one solve.
@@ -200,17 +203,20 @@ hipError_t launch_factor_mixed(const Launch<FactorDesc>& p, int np, bool bf16, i
 // whole level step, 1..3 one of its three kernels (in that order).
 hipError_t launch_factor_tiled(const Launch<FactorDesc>& p, int np, int mode, int part, bool deferred,
                                int64_t items, hipStream_t st);
-// mc: right-hand-side columns per dependency-chain group (1 or 4; with 4,
-// instances with fewer columns mask the rest).  chunk: the items are
-// subtrees of several levels (level field l0 | l1 << 8, k the subtree index
-// j: the nodes of levels l0 .. l1-1 strictly between blocks j 2^l1 and
-// (j+1) 2^l1), one workgroup of kw (4 or 8) wavefronts each; else single
-// nodes, one wavefront each.
+// A node step is done by a team of np/16 wavefronts (one workgroup).  mc:
+// right-hand-side columns per pass over a node (FP64: 4, or when more than 4,
+// 16 up to n = 64 and 8 above; FP32 always 16; results do not depend on it).
+// flow: the items are the nodes of a range of levels l0 .. l1-1 in level order
+// (level field l0 | l1 << 8, explicit items also the node's level << 16),
+// which wait for each other through SweepDesc.flow; Launch.ticket is set.
+// Else independent nodes of single levels.
 hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool chunk = false, int kw = 4);
+                        hipStream_t st, bool flow = false);
 hipError_t launch_sweep(const Launch<SweepDesc<float>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool chunk = false, int kw = 4);
-// Two launches over the same items (every block row of each instance).
+                        hipStream_t st, bool flow = false);
+// Two launches over the same items (every block row of each instance); mc:
+// right-hand-side columns per dependency-chain group (1 or 4; with 4,
+// instances with fewer columns mask the rest).
 hipError_t launch_residual(const Launch<ResidualDesc>& p, int np, int64_t items, int mc, hipStream_t st);
 hipError_t launch_ir_init(const Launch<IrDesc>& p, int64_t items, hipStream_t st);
 hipError_t launch_ir_check(const Launch<IrDesc>& p, int64_t items, hipStream_t st);

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(MixCfg<NP>::NT) void k_factor_level_mixed(Launch<Fa
             acc32_store_global(acc, dst, n, w * kT, t * kT);
         }
     }
-    lds_store_as<NP, float, float>(P.L32 + (size_t)pi * nn, fL, n, true, tid, NT);
+    store_factor_lds<NP, float, float>(P.L32 + (size_t)pi * nn, fL, fInv, n, tid, NT);
     if (has_r) lds_store_as<NP, float, float>(P.R32 + (size_t)pi * nn, fB, n, false, tid, NT);
     if (has_l) lds_store_as<NP, float, float>(P.T32 + (size_t)pi * nn, fD, n, false, tid, NT);
 }

@@ -8,6 +8,7 @@
 // with the runs, which k_expand_items spreads out on the device.  Batched factorization and solve of many
 // independent instances, and the continuous-batching server, are built on it.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <string.h>
 
 #include <algorithm>
@@ -74,7 +75,23 @@ struct Group {
         runs.push_back({0, first, count, inst, level});
         items += count;
     }
-    size_t off_desc = 0, off_items = 0;
+    // sweeps over several levels: items in level order, one flag per node (of
+    // every instance in turn) and a work counter in the call's buffer, uploaded
+    // as 0
+    struct Flags {
+        int64_t first, pos;  // the instance's first flag, and the permuted position it stands for
+    };
+    std::vector<Flags> flags;
+    int64_t words = 0;
+    size_t off_desc = 0, off_items = 0, off_words = 0;
+    // Items of all instances in level order: the launch's workgroups wait only
+    // for earlier ones.
+    void level_order() {
+        const bool down = op == BTC_OP_BACKWARD;
+        std::stable_sort(runs.begin(), runs.end(), [down](const ItemRun& a, const ItemRun& b) {
+            return down ? (a.level >> 16) > (b.level >> 16) : (a.level >> 16) < (b.level >> 16);
+        });
+    }
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -247,6 +264,7 @@ btc::Launch<D> make_launch(const Group& g, char* dev) {
     btc::Launch<D> L{};
     L.descs = (const D*)(dev + g.off_desc);
     L.items = (const btc::WorkItem*)(dev + g.off_items);
+    if (g.words) L.ticket = (int*)(dev + g.off_words) + g.words;
     return L;
 }
 
@@ -440,7 +458,10 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             }
             add_work(r, g, s, mixed);
             if (range) {
-                g.add_run(inst, s.level | (s.level_end << 8), 0, chunk_count(h->N, s.level, s.level_end));
+                g.flags.push_back({g.words, h->N - (h->N >> s.level)});
+                g.words += range_nodes(h->N, s.level, s.level_end);
+                for (int l = s.level; l < s.level_end; ++l)
+                    g.add_run(inst, s.level | (s.level_end << 8) | (l << 16), 0, level_nodes(h->N, l));
             } else {
                 g.add_run(inst, s.level, 0, level_nodes(h->N, s.level));
             }
@@ -469,7 +490,8 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             g.add_run(inst, 0, 0, 1);
         }
     }
-
+    for (auto& kv : groups)
+        if (kv.second.words) kv.second.level_order();
 }
 
 // Offsets of the call's reset list, descriptors and items (or runs and, past
@@ -484,6 +506,8 @@ size_t layout_call(Call& c, size_t base, bool may_expand, size_t* upload) {
         Group& g = kv.second;
         g.off_desc = bytes;
         bytes = align256(bytes + g.descs.size());
+        g.off_words = bytes;
+        if (g.words) bytes = align256(bytes + (size_t)(g.words + 1) * sizeof(int));
         items += g.items;
         c.runs += g.runs.size();
     }
@@ -506,12 +530,21 @@ size_t layout_call(Call& c, size_t base, bool may_expand, size_t* upload) {
     return bytes;
 }
 
-void write_call(const Call& c, char* host) {
+// (dev: the device buffer the call will be launched from)
+void write_call(const Call& c, char* host, char* dev) {
     if (!c.resets.empty()) memcpy(host + c.off_resets, c.resets.data(), c.resets.size() * sizeof(unsigned long long*));
     size_t off_runs = c.off_runs;
     for (auto& kv : c.groups) {
         const Group& g = kv.second;
         memcpy(host + g.off_desc, g.descs.data(), g.descs.size());
+        if (g.words) {
+            memset(host + g.off_words, 0, (size_t)(g.words + 1) * sizeof(int));
+            const size_t at = (g.kind & 1) ? offsetof(btc::SweepDesc<float>, flow) : offsetof(btc::SweepDesc<double>, flow);
+            for (size_t k = 0; k < g.flags.size(); ++k) {
+                int* const p = (int*)(dev + g.off_words) + g.flags[k].first - g.flags[k].pos;
+                memcpy(host + g.off_desc + k * g.desc_size + at, &p, sizeof(p));
+            }
+        }
         if (c.expand) {
             memcpy(host + off_runs, g.runs.data(), g.runs.size() * sizeof(ItemRun));
             off_runs += g.runs.size() * sizeof(ItemRun);
@@ -590,11 +623,10 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
                 const bool bwd = g.op == BTC_OP_BACKWARD;
                 const bool range = g.kind >= 2;
                 const int fk = g.kind & 1;
-                const int kw = shape_waves(tune_variant(BTC_TUNE_SWEEP_SHAPE, fk, g.np, 0));
                 if (fk == 1)
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<float>>(g, dev), g.np, items, bwd, sweep_mc(g.op, 1, g.np, g.m_max), gs, range, kw);
+                    e = btc::launch_sweep(make_launch<btc::SweepDesc<float>>(g, dev), g.np, items, bwd, sweep_cols(g.op, 1, g.np, g.m_max), gs, range);
                 else
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), g.np, items, bwd, sweep_mc(g.op, 0, g.np, g.m_max), gs, range, kw);
+                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), g.np, items, bwd, sweep_cols(g.op, 0, g.np, g.m_max), gs, range);
                 break;
             }
             case BTC_OP_RESIDUAL:
@@ -728,7 +760,7 @@ int runner_run(btc_runner r, int32_t count, const btc_step* steps) {
     btc_runner_s::Slot& sl = r->slot[r->cur];
     rc = slot_reserve(r, sl, bytes, dev_bytes);
     if (rc != BTC_OK) return rc;
-    write_call(c, sl.host);
+    write_call(c, sl.host, sl.dev);
     hipError_t e = hipMemcpyAsync(sl.dev, sl.host, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return to_code(e);
     (void)hipEventRecord(sl.ev, st);
@@ -775,12 +807,13 @@ BTC_API int btc_graph_end(btc_runner r, btc_graph* out) {
         bytes = layout_call(c, bytes, false, &upload);
     }
     std::vector<char> host(std::max<size_t>(bytes, 256));
-    for (auto& c : calls) write_call(c, host.data());
     // the recorded work of the runner's stream must be done before the
     // descriptors are uploaded and the capture starts
     hipError_t e = hipStreamSynchronize(r->st);
     g->alloc = current_allocator();
     if (e == hipSuccess) e = dev_alloc(g->alloc, (void**)&g->dev, host.size(), r->st);
+    if (e == hipSuccess)
+        for (auto& c : calls) write_call(c, host.data(), g->dev);
     if (e == hipSuccess) e = hipMemcpy(g->dev, host.data(), host.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&g->cap, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(g->cap, hipStreamCaptureModeThreadLocal);
@@ -859,8 +892,19 @@ BTC_API int btc_level_work(int32_t op, int32_t precision, int64_t N, int64_t n, 
 BTC_API int btc_sweep_ranges(int64_t N, int32_t* bounds, int32_t max) {
     if (N < 1) return -1;
     if (!bounds) return -2;
-    int b[66];
-    const int r = sweep_ranges(N, num_levels(N), b);
+    // greedy from level 0: a level of 4096 nodes or more is a range of its own;
+    // otherwise a range grows while every level of one of its subtrees (the
+    // nodes between two blocks of the level after it) has at most four nodes
+    const int levels = num_levels(N);
+    int b[66], r = 0;
+    b[0] = 0;
+    for (int l0 = 0; l0 < levels;) {
+        int l1 = l0 + 1;
+        if (level_nodes(N, l0) < 4096)
+            while (l1 < levels && std::min<int64_t>((int64_t)1 << (l1 - l0), level_nodes(N, l0)) <= 4) ++l1;
+        b[++r] = l1;
+        l0 = l1;
+    }
     if (r + 1 > max) return -2;
     for (int k = 0; k <= r; ++k) bounds[k] = b[k];
     return r;
@@ -940,14 +984,19 @@ BTC_API int btc_solve_batched(btc_runner r, int32_t count, const btc_handle* h, 
             rounds = std::max(rounds, 1 + h[k]->max_refine);
         }
     }
-    // each instance's sweeps in its level ranges; call q runs range q of
-    // every instance that has one (backward: counted from the top)
+    // each instance's sweeps in its level ranges, the levels in one launch
+    // starting where the batch's nodes no longer fill launches of their own;
+    // call q runs range q of every instance that has one (backward: from the
+    // top)
     std::vector<std::vector<int>> bounds((size_t)count);
     int max_ranges = 0;
+    int64_t nodes[66] = {};
+    for (int32_t k = 0; k < count; ++k)
+        for (int l = 0; l < h[k]->levels; ++l) nodes[l] += level_nodes(h[k]->N, l);
     for (int32_t k = 0; k < count; ++k) {
         bounds[(size_t)k].resize(66);
-        const int nr = sweep_ranges(h[k]->N, h[k]->levels, bounds[(size_t)k].data(),
-                                    sweep_shape(h[k]->precision, h[k]->n));
+        const int flow = flow_start(nodes, h[k]->levels, sweep_shape(h[k]->precision, h[k]->n));
+        const int nr = range_bounds(flow, h[k]->levels, bounds[(size_t)k].data());
         bounds[(size_t)k].resize((size_t)nr + 1);
         max_ranges = std::max(max_ranges, nr);
     }

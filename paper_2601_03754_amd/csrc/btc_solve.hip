@@ -4,6 +4,7 @@
 // decision is deterministic).
 #include "btc_device.h"
 #include "btc_kernels.h"
+#include "btc_residual.h"
 
 namespace btc {
 namespace {

@@ -1,34 +1,44 @@
-// Level sweeps of the solve (section "Cholesky Solve", Algorithm 6) and the
-// FP64 residual b - Psi x, streaming form: one wavefront per node (per block
-// row for the residual), every n x n block read from HBM once and coalesced.
-//
-// Lane r owns rows r and r + 64 of the node's vectors (columns of the
-// right-hand side are processed MC at a time, MC independent chains).  Every
-// block goes through LDS in slabs of 16 columns (each row contributes one
-// contiguous 16-element segment, written transposed) or 16 rows (contiguous),
-// laid out so that lane r reads slab[k][r] conflict-free whichever of
-// M[r][c] or M[c][r] the product needs.  The global loads of slab p+1 (NP/4
-// per lane, held in registers) are in flight while slab p is consumed from
-// LDS, so the triangular solves' dependency chains overlap the block
-// traffic; with one wavefront per workgroup and one slab buffer (at most
-// 16.5 KB), many nodes share each compute unit.
+// Level sweeps of the solve (section "Cholesky Solve", Algorithm 6) on the
+// matrix cores: one team of NP/16 wavefronts per node, every n x n block read
+// from HBM once, straight into the matrix cores' operand registers.
 //
 //   forward, node i of level l (stride s), levels ascending:
-//     y_i = L_ii^{-1} (b_i - sum of the u / v its descendants left for it)
-//         [column slabs of L_ii, column sweep, pivots broadcast by readlane]
-//     u_i = R_i y_i   [column slabs of R_i]   (pulled by node i+s)
-//     v_i = T_i^T y_i [row slabs of T_i]      (pulled by node i-s)
+//     y_i = L_ii^{-1} (b_i - U_{i-s/2} - V_{i+s/2})
+//     U_i = R_i y_i + U_{i+s/2}     (everything i's subtree leaves for i+s)
+//     V_i = T_i^T y_i + V_{i-s/2}   (everything it leaves for i-s)
 //   backward, levels descending:
 //     x_i = L_ii^{-T} (y_i - R_i^T x_{i+s} - T_i x_{i-s})
-//         [R_i row slabs; T_i column slabs; L_ii row slabs consumed from the
-//          last row up]
-//   residual, block row i: r_i = b_i - D_i x_i - E_{i-1} x_{i-1} - E_i^T x_{i+1}
-//     [row slabs of the lower triangle of D_i and of E_i, each element used
-//      for its own row and, through a wavefront sum, for its transpose's;
-//      E_i x_i is left for row i+1]; then per-column partial squared norms
-//     of r_i and b_i.
 // Instead of two nodes subtracting into the same y concurrently, each node
-// pulls its contributions in a fixed order: results are deterministic.
+// takes its two children's sums and passes on theirs with its own (the
+// subtree left of a node leaves one vector for it, however many levels it
+// has; leaving one per level made a top node gather up to twice its level's
+// number of vectors).  Results are deterministic.
+//
+// A node step of the upper levels is bound by latency, not by traffic: one
+// wavefront per node that streams the blocks through LDS slab by slab takes
+// 30 to 45 us in FP64 at n = 96 (about 380 cycles for each of its 288 column
+// steps: LDS read, lane broadcast, division, update).  Here
+//   * all loads of a node (its L, R and T blocks) are in flight at once, in
+//     the registers of the team's wavefronts: wavefront w holds tile row w of
+//     L and R and tile column w of T (forward; transposed roles backward);
+//   * the triangular solve is a chain over 16 x 16 tiles, not over columns:
+//     the factor kernels leave the inverse of every diagonal tile in the
+//     strict upper part of that tile of L_ii (transposed; its diagonal is
+//     1 / L_jj), so a chain step is one product with the inverse and one
+//     with the next tile of L, about 300 cycles for 16 columns;
+//   * every product runs on the matrix cores (FP64 4x4x4 with four blocks:
+//     16 rows by 4 columns in 16 cycles; FP32 16x16x4), which also do the
+//     sums over lanes; up to 16 right-hand sides share one pass over the
+//     blocks.
+//   * the upper levels run in one launch (k_sweep_flow), whose workgroups have
+//     their blocks in registers when the vectors they wait for arrive.
+// Measured, before and after: N = 4096, n = 96, one right-hand side, FP64:
+// forward 560 -> 223 us, backward 480 -> 217 us (level 0, 377 MB: 94 us, 4.0
+// TB/s; the twelve upper levels in one launch 129 us; a level of its own
+// launch 11 us instead of 40); N = 1023, n = 128, five right-hand sides: whole
+// solve 2 855 -> 291 us.
+#include <type_traits>
+
 #include "btc_device.h"
 #include "btc_kernels.h"
 
@@ -36,853 +46,710 @@ namespace btc {
 namespace {
 
 constexpr unsigned long long kInfoOk = ~0ull;
-constexpr int kS = 16;  // slab width
+constexpr int kTl = 16;  // tile side
 
-__device__ __forceinline__ double bcast(double v, int lane) { return readlane_d(v, lane); }
-__device__ __forceinline__ float bcast(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+// Matrix-core engine of a storage type: a 16 x 16 tile of A times CW columns
+// in four instructions.  Lane l holds A[l % 16][k(s)] of step s and B[k(s)][col],
+// k(s) = kidx(s, l / 16): the order of k is chosen so that a lane's four
+// elements of a row-major tile row are contiguous in pairs (FP64) or all
+// four (FP32).  Accumulator register v of lane l: element (row(v), col).
+template <class T>
+struct Eng;
+
+// v_mfma_f64_4x4x4 with four blocks: block b (lanes 4b .. 4b+3 of every row of
+// 16 lanes) multiplies rows 4b .. 4b+3 of the tile with four columns.
+template <>
+struct Eng<double> {
+    static constexpr int CW = 4, NV = 1;
+    struct Acc {
+        double v[1];
+    };
+    __device__ static int kidx(int s, int q) { return 8 * (s >> 1) + 2 * q + (s & 1); }
+    __device__ static int row(int, int lane) { return (lane & 12) + (lane >> 4); }
+    __device__ static int col(int lane) { return lane & 3; }
+    __device__ static void mma(Acc& c, double a, double b) {
+        c.v[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c.v[0], 0, 0, 0);
+    }
+    // Product of the diagonal tile's inverse with a vector tile in the
+    // accumulator layout: the four blocks of an instruction may take
+    // different k ranges, so step s takes in block b the rows 4((b - s) % 4)
+    // .. +3, which a rotation of the 16-lane rows by 4s brings there (no LDS
+    // round trip).  didx: the k of step s.
+    __device__ static int didx(int s, int lane) { return 4 * ((((lane & 15) >> 2) - s) & 3) + (lane >> 4); }
+    template <int CTRL>
+    __device__ static double rot(double x) {
+        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, false);
+        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, false);
+        return __hiloint2double(hi, lo);
+    }
+    __device__ static Acc dmul(const double (&d)[4], const Acc& x) {
+        Acc o;
+        o.v[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(d[0], x.v[0], 0.0, 0, 0, 0);
+        mma(o, d[1], rot<0x124>(x.v[0]));  // row_ror:4
+        mma(o, d[2], rot<0x128>(x.v[0]));  // row_ror:8
+        mma(o, d[3], rot<0x12C>(x.v[0]));  // row_ror:12
+        return o;
+    }
+};
+
+template <>
+struct Eng<float> {
+    static constexpr int CW = 16, NV = 4;
+    union Acc {
+        f4_t f;
+        float v[4];
+    };
+    __device__ static int kidx(int s, int q) { return 4 * q + s; }
+    __device__ static int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+    __device__ static int col(int lane) { return lane & 15; }
+    __device__ static void mma(Acc& c, float a, float b) {
+        c.f = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c.f, 0, 0, 0);
+    }
+    // the accumulator layout is the B operand layout of k = 4q + s
+    __device__ static int didx(int s, int lane) { return 4 * (lane >> 4) + s; }
+    __device__ static Acc dmul(const float (&d)[4], const Acc& x) {
+        Acc o;
+        o.f = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) mma(o, d[s], x.f[s]);
+        return o;
+    }
+};
+
+template <class T>
+__device__ __forceinline__ typename Eng<T>::Acc acc_zero() {
+    typename Eng<T>::Acc a;
+#pragma unroll
+    for (int v = 0; v < Eng<T>::NV; ++v) a.v[v] = T(0);
+    return a;
 }
 
-constexpr int gcd_i(int a, int b) { return b == 0 ? a : gcd_i(b, a % b); }
+// All loads of a node go out in straight-line code: a load that does not
+// apply (a block the node does not have, a tile past n) gets a scalar offset
+// past the resource's end and reads 0 without touching memory.  No branch
+// then separates a load from its use, so the compiler's waits count exactly
+// the loads that are needed; with branches it waits for every load in flight
+// before the first use.
 
-template <int NP>
-struct Geo {
-    static_assert(NP % kS == 0, "padded size is a multiple of the slab width");
-    static constexpr int RPL = (NP + kWave - 1) / kWave;  // rows per lane
-    static constexpr int LDB = NP + 1;                    // slab stride (elements)
-    // lanes past the last row (r >= NP) read past the end of the last slab
-    // row: the buffer is long enough for them (their values are never used)
-    static constexpr int BUF = kS * LDB + kWave * RPL - NP;
-    static constexpr int PER = NP * kS / kWave;           // slab elements per lane
-    // row slab element u of a lane: pattern u % RP (row, column) of the first
-    // RP elements, moved down by (u / RP) * RK rows
-    static constexpr int RP = NP / gcd_i(NP, kWave);
-    static constexpr int RK = kWave / gcd_i(NP, kWave);
-};
+// Loads return in the order they went out: the instruction scheduler is held
+// to the order of use.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0); }
 
-// Slab loads go through buffer resources (block_rsrc): rows and columns
-// beyond n and the skipped parts are masked by offset.
-
-// Where the next slab comes from: column slab (elements M[r][c0+k], rows
-// r >= rmin) or row slab (elements M[r0+k][r], only r <= r0+k when tri).
-template <class S>
-struct SlabSrc {
-    const S* M;
-    int off;
-    int rmin;
-    bool rows;
-    bool tri;
-};
-
-template <int NP, class T>
-struct SlabRegs {
-    T v[Geo<NP>::PER];
-
-    // Column slab: lane (q, k) = (lane / 16, lane % 16) reads rows q + 4u
-    // of column off + k, every offset a lane constant plus 4un.  Row slab:
-    // lanes read along the rows (pattern offsets of Geo).  Both skip what the
-    // triangular blocks do not use (column slab: the rows above rmin, a
-    // whole element index at a time; row slab: columns past the slab's last
-    // row).
-    template <class S>
-    __device__ __forceinline__ void fetch(const SlabSrc<S>& s, int n, int lane) {
-        using G = Geo<NP>;
-        const __amdgpu_buffer_rsrc_t rs = block_rsrc(s.M, n * n * (int)sizeof(S));
-        if (!s.rows) {
-            const int k = lane & (kS - 1), q = lane >> 4;
-            const int c = s.off + k;
-            const int base = c < n ? (q * n + c) * (int)sizeof(S) : kOob;
-            const int step = 4 * n * (int)sizeof(S);
+// Lane offsets (bytes) of the tile operands of an n x n block.
+template <class T>
+struct Lane {
+    int rw;     // row-wise: row i of a tile row, first element of the lane's share
+    int cw[4];  // column-wise: the lane's elements of column c0 + i, masked past n
+    // c0: first column of the column-wise tiles
+    __device__ __forceinline__ Lane(int lane, int n, int c0) {
+        using E = Eng<T>;
+        const int i = lane & 15, q = lane >> 4;
+        rw = (i * n + E::kidx(0, q)) * (int)sizeof(T);
 #pragma unroll
-            for (int u = 0; u < G::PER; ++u) {
-                if (4 * u < s.rmin)
-                    v[u] = T(0);
-                else
-                    buf_ld(v[u], rs, base + u * step);
-            }
-        } else {
-            int base[G::RP];
-#pragma unroll
-            for (int j = 0; j < G::RP; ++j) {
-                const int e = lane + kWave * j, r = e % NP, k = e / NP;
-                const bool ok = r < n && (!s.tri || r < s.off + kS);
-                base[j] = ok ? ((s.off + k) * n + r) * (int)sizeof(S) : kOob;
-            }
-            const int step = G::RK * n * (int)sizeof(S);
-#pragma unroll
-            for (int u = 0; u < G::PER; ++u) buf_ld(v[u], rs, base[u % G::RP] + (u / G::RP) * step);
-        }
-    }
-
-    __device__ __forceinline__ void put(T* __restrict__ buf, bool rows, int lane) const {
-        if (!rows) {
-#pragma unroll
-            for (int u = 0; u < Geo<NP>::PER; ++u) {
-                const int e = lane + kWave * u;
-                buf[(e % kS) * Geo<NP>::LDB + e / kS] = v[u];
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < Geo<NP>::PER; ++u) {
-                const int e = lane + kWave * u;
-                buf[(e / NP) * Geo<NP>::LDB + e % NP] = v[u];
-            }
-        }
+        for (int s = 0; s < 4; ++s) cw[s] = c0 + i < n ? (E::kidx(s, q) * n + c0 + i) * (int)sizeof(T) : kOob;
     }
 };
 
-// Value of vector row j (wave-uniform) of column c, held by lane j % 64.
-template <int RPL, int MC, class T>
-__device__ __forceinline__ T row_value(const T (&a)[RPL][MC], int j, int c) {
-    T x = a[0][c];
+// Tile operand A[i][k] = M[r0 + i][c0 + k], soff the byte offset of (r0, c0):
+// 16-byte loads at element alignment (the blocks are unpadded; range checks
+// are per dword).  In the last, partial tile of a row the columns past n are
+// elements of the next row: mask_tail.
+template <class T>
+__device__ __forceinline__ void load_rowwise(T (&a)[4], __amdgpu_buffer_rsrc_t rs, const Lane<T>& ln, int soff) {
+    if constexpr (sizeof(T) == 8) {
 #pragma unroll
-    for (int rr = 1; rr < RPL; ++rr)
-        if (j >= kWave * rr) x = a[rr][c];
-    return bcast(x, j & (kWave - 1));
+        for (int h = 0; h < 2; ++h) {
+            const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(rs, ln.rw + 64 * h, soff, 0);
+            a[2 * h] = __hiloint2double((int)x[1], (int)x[0]);
+            a[2 * h + 1] = __hiloint2double((int)x[3], (int)x[2]);
+        }
+    } else {
+        const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(rs, ln.rw, soff, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[s] = __int_as_float((int)x[s]);
+    }
+}
+template <class T>
+__device__ __forceinline__ void mask_tail(T (&a)[4], int n, int c0, int lane) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (c0 + Eng<T>::kidx(s, lane >> 4) >= n) a[s] = T(0);
+}
+
+// Tile operand A[i][k] = M[r0 + k][c0 + i], soff the byte offset of row r0
+// (c0 is in ln): lanes read along the rows.
+template <class T>
+__device__ __forceinline__ void load_colwise(T (&a)[4], __amdgpu_buffer_rsrc_t rs, const Lane<T>& ln, int soff) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) buf_ld(a[s], rs, ln.cw[s], soff);
+}
+
+// Operand of the inverse of diagonal tile t (TR: its transpose), k order
+// didx.  The tile of the stored L_ii holds L in its lower part with the
+// diagonal, and the inverse's strict lower part transposed in its strict
+// upper part.  The diagonal itself is loaded as L_jj: invert_diag.
+template <class T, bool TR>
+__device__ __forceinline__ void load_dinv(T (&d)[4], __amdgpu_buffer_rsrc_t rs, int n, int t, int lane) {
+    const int i = lane & 15, t0 = kTl * t;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int k = Eng<T>::didx(s, lane);
+        // Dinv[i][k], k <= i, at row k, column i; Dinv^T[i][k] = Dinv[k][i],
+        // i <= k, at row i, column k
+        const int r = t0 + (TR ? i : k), c = t0 + (TR ? k : i);
+        buf_ld(d[s], rs, elem_off<T>(r, c, n, r <= c && c < n));
+    }
+}
+template <class T>
+__device__ __forceinline__ void invert_diag(T (&d)[4], int n, int t, int lane) {
+    const int i = lane & 15;
+    T piv = T(1);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (Eng<T>::didx(s, lane) == i && kTl * t + i < n) piv = d[s];
+    const T inv = T(1) / piv;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        if (Eng<T>::didx(s, lane) == i && kTl * t + i < n) d[s] = inv;
+}
+
+// Rows 16w .. 16w+15 of an n x m vector of one node, addressed by byte
+// offsets from row 16w; absent: reads 0, writes dropped.
+template <class T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t vec_rsrc(const T* v, int n, int m, int64_t node, bool present,
+                                                           int w) {
+    const int rows = n - kTl * w < kTl ? n - kTl * w : kTl;
+    const bool ok = present && rows > 0;
+    return block_rsrc(v + (ok ? ((size_t)node * n + kTl * w) * m : 0), ok ? rows * m * (int)sizeof(T) : 0);
 }
 
 template <class T>
 __device__ __forceinline__ bool skip_item(const SweepDesc<T>& P) {
-    if (*P.info != kInfoOk) return true;
-    if (P.skip && *P.skip) return true;
-    return false;
+    // both flags in one round trip
+    typedef const unsigned long long __attribute__((address_space(1)))* gu64;
+    typedef const int __attribute__((address_space(1)))* gi32;
+    const unsigned long long info = *(gu64)P.info;
+    const int skip = *(gi32)(P.skip ? P.skip : (const int*)P.info);
+    return info != kInfoOk || (P.skip && skip != 0);
 }
 
-// A kernel's block traffic as a list of up to four segments of slabs, each
-// segment the slabs of one block in one orientation.  Kept as separate
-// scalars (selected by wave-uniform indices) so the plan lives in registers.
-template <class S>
-struct Seg {
-    const S* M;
-    int count;   // slabs (0: segment absent)
-    bool rows;   // row slabs (else column slabs)
-    bool desc;   // slabs from the last one to the first
-    bool tri;    // column slab p: rows >= 16p only; row slab: r <= row only
-};
-
-template <class S>
-struct Plan {
-    const S *m0, *m1, *m2, *m3;
-    int c0, c1, c2, c3;
-    unsigned rows, desc, tri;  // bit g: property of segment g
-    int total;
-    int slabs;                 // slabs per block (the same for every present segment)
-
-    __device__ __forceinline__ void set(int g, const Seg<S>& sg) {
-        if (g == 0) { m0 = sg.M; c0 = sg.count; }
-        if (g == 1) { m1 = sg.M; c1 = sg.count; }
-        if (g == 2) { m2 = sg.M; c2 = sg.count; }
-        if (g == 3) { m3 = sg.M; c3 = sg.count; }
-        const unsigned bit = 1u << g;
-        rows = sg.rows ? (rows | bit) : (rows & ~bit);
-        desc = sg.desc ? (desc | bit) : (desc & ~bit);
-        tri = sg.tri ? (tri | bit) : (tri & ~bit);
-        total = c0 + c1 + c2 + c3;
-        if (sg.count) slabs = sg.count;
-    }
-
-    __device__ __forceinline__ void clear() {
-        m0 = m1 = m2 = m3 = nullptr;
-        c0 = c1 = c2 = c3 = 0;
-        rows = desc = tri = 0u;
-        total = 0;
-        slabs = 0;
-    }
-
-    __device__ __forceinline__ bool is_rows(int g) const { return (rows >> g) & 1u; }
-
-    // segment index and slab index within it of global slab p
-    __device__ __forceinline__ int locate(int p, int& q) const {
-        q = p;
-        if (q < c0) return 0;
-        q -= c0;
-        if (q < c1) return 1;
-        q -= c1;
-        if (q < c2) return 2;
-        q -= c2;
-        return 3;
-    }
-
-    __device__ __forceinline__ SlabSrc<S> src(int p) const {
-        int q;
-        const int g = locate(p, q);
-        const S* M = g == 0 ? m0 : g == 1 ? m1 : g == 2 ? m2 : m3;
-        const bool r = (rows >> g) & 1u, d = (desc >> g) & 1u, t = (tri >> g) & 1u;
-        const int sl = d ? slabs - 1 - q : q;  // every present segment has `slabs` slabs
-        return {M, kS * sl, (!r && t) ? kS * sl : 0, r, r && t};
-    }
-};
-
-// target[r] += sgn * slab[k][r] * vec[off + k] over the 16 slab columns
-// (column slab: vec indexed by the block's column; row slab: by its row).
-// mask: 0 none, 1 only off+k <= r, 2 only r < off+k.
-template <int NP, int MC, class T>
-__device__ __forceinline__ void slab_axpy(T (&target)[Geo<NP>::RPL][MC], const T* __restrict__ b,
-                                          const T (&vec)[Geo<NP>::RPL][MC], int off, int n, T sgn, int mask,
-                                          int lane) {
-    constexpr int RPL = Geo<NP>::RPL, LDB = Geo<NP>::LDB;
-    for (int k = 0; k < kS; ++k) {
-        const int cc = off + k;
-        if (cc >= n) break;
-        T xc[MC];
-#pragma unroll
-        for (int c = 0; c < MC; ++c) xc[c] = sgn * row_value<RPL, MC, T>(vec, cc, c);
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-            T a = b[k * LDB + r];
-            if (mask == 1 && cc > r) a = T(0);
-            if (mask == 2 && r >= cc) a = T(0);
-#pragma unroll
-            for (int c = 0; c < MC; ++c) target[rr][c] = fma(a, xc[c], target[rr][c]);
-        }
-    }
-}
-
-// Slabs in flight beyond the one being consumed.  Measured on MI355X: a
-// second one buys little per-node latency and costs occupancy (registers),
-// so one.
-template <int NP, class T>
-constexpr int slab_depth() { return 1; }
-
-// Walk the slabs of a plan through the LDS buffer: slab p is consumed by
-// body(p, segment, slab index in segment, buffer) while the loads of the next
-// DEPTH slabs are in flight (register buffers indexed by unrolled constants).
-template <int NP, class T, int DEPTH, class S, class Body>
-__device__ __forceinline__ void run_slabs(const Plan<S>& pl, int n, int lane, T* __restrict__ buf, Body&& body) {
-    SlabRegs<NP, T> r[DEPTH];
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u)
-        if (u < pl.total) r[u].fetch(pl.src(u), n, lane);
-    for (int p = 0; p < pl.total; p += DEPTH) {
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u) {
-            const int q = p + u;
-            if (q < pl.total) {
-                int qs;
-                const int g = pl.locate(q, qs);
-                r[u].put(buf, pl.is_rows(g), lane);
-                wave_lds_sync();
-                if (q + DEPTH < pl.total) r[u].fetch(pl.src(q + DEPTH), n, lane);
-                body(g, qs, buf);
-                wave_lds_sync();
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// a minus the contributions left for node i of level lvl by its descendants:
-// u from node i - 2^l2 and v from node i + 2^l2 for every l2 < lvl,
-// subtracted in level order.  The loads go out in groups of eight before any
-// subtraction, so their latencies overlap (a top-level node pulls from up to
-// twice its level count of places); a contribution that does not exist reads
-// slot 0 and subtracts +0, which leaves every value unchanged bit for bit.
+// A node's position in the elimination tree.
 template <class T>
-__device__ __forceinline__ T pull(const SweepDesc<T>& P, T a, int64_t i, int lvl, size_t off, size_t nm) {
-    const int64_t N = P.N;
-    for (int g = 0; g < lvl; g += 8) {
-        T cu[8], cv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int l2 = g + u;
-            const bool okl = l2 < lvl;
-            const int64_t s2 = (int64_t)1 << (okl ? l2 : 0);
-            const bool okr = okl && i + s2 <= N;
-            const size_t iu = okl ? (size_t)perm_pos(N, l2, i - s2) * nm + off : 0;
-            const size_t iv = okr ? (size_t)perm_pos(N, l2, i + s2) * nm + off : 0;
-            const T x = P.U[iu], y = P.V[iv];
-            cu[u] = okl ? x : T(0);
-            cv[u] = okr ? y : T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            a -= cu[u];
-            a -= cv[u];
-        }
+struct Pos {
+    int64_t i, s, pi;
+    bool has_r, has_l;
+    __device__ __forceinline__ Pos(const SweepDesc<T>& P, int lvl, int64_t kk) {
+        s = (int64_t)1 << lvl;
+        i = (kk * 2 + 1) << lvl;
+        has_r = i + s <= P.N;
+        has_l = i > s;
+        pi = perm_pos(P.N, lvl, i);
     }
-    return a;
+};
+
+// The tree of the sums: node i of level l > 0 takes its left child's (i - s/2)
+// and those of the nearest node below on its right, i + 2^l2: the right child,
+// or where the chain ends before it the largest 2^l2 still inside.  That
+// makes every node the source of exactly one other, its parent.
+template <class T>
+struct Kin {
+    bool left, right;   // children present
+    int l2;             // level of the right one
+    int64_t pl, pr;     // their positions
+    __device__ __forceinline__ Kin(const SweepDesc<T>& P, const Pos<T>& d, int lvl) {
+        const int64_t h = d.s >> 1, room = P.N - d.i;
+        left = lvl > 0;
+        right = lvl > 0 && room > 0;
+        l2 = room >= h ? lvl - 1 : room > 0 ? 63 - __builtin_clzll((unsigned long long)room) : 0;
+        pl = left ? perm_pos(P.N, lvl - 1, d.i - h) : 0;
+        pr = right ? perm_pos(P.N, l2, d.i + ((int64_t)1 << l2)) : 0;
+    }
+};
+// Level of node i's parent (64: none, the root).
+template <class T>
+__device__ __forceinline__ int parent_level(const Pos<T>& d, int lvl) {
+    const int64_t k = d.i >> (lvl + 1);
+    if ((k & 1) || d.has_r) return lvl + 1;
+    return k == 0 ? 64 : lvl + 1 + __builtin_ctzll((unsigned long long)k);
 }
 
+// Several levels in one launch (k_sweep_flow): the nodes of levels l0 .. l1-1,
+// one workgroup each, in level order.  A workgroup puts its node's blocks in
+// flight, waits for the flags of the nodes it depends on inside the range,
+// and sets its own once its vectors are out.  Flags: one word per node and
+// direction, set by the producer and cleared by its single reader, so they
+// are zero again when a launch ends.
+struct Flow {
+    int* flag;     // words of this direction, indexed by permuted position
+    int l0, l1;
+};
+constexpr int kCoherent = 16;  // cache policy of vectors exchanged inside a launch: agent scope (sc1)
+
+__device__ __forceinline__ int flag_load(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void flag_store(int* p, int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The first wavefront waits until flags a and b (null: nothing to wait for)
+// are set and clears them; the others wait for it.  The nodes waited for have
+// smaller tickets, so they are running or done.
+__device__ __forceinline__ void flow_wait(int* a, int* b, int wave) {
+    if (wave == 0 && (a || b)) {
+        int* f = (threadIdx.x & 1) ? b : a;
+        while (!__all(f == nullptr || flag_load(f) != 0)) __builtin_amdgcn_s_sleep(1);
+        if (threadIdx.x < 2 && f) flag_store(f, 0);
+    }
+    __syncthreads();
+}
+// Every thread's vector stores (agent scope) have reached memory, then the
+// flags are set.
+__device__ __forceinline__ void flow_signal(int* a, int* b) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (a) flag_store(a, 1);
+        if (b) flag_store(b, 1);
+    }
+}
+
+// Geometry of a team (NP/16 wavefronts, one node) with NG column groups per
+// pass.
+template <int NP, class T, int NG>
+struct Team {
+    using E = Eng<T>;
+    static constexpr int W = NP / kTl;            // wavefronts = tiles per side
+    static constexpr int TH = W * kWave;          // threads
+    static constexpr int CP = E::CW * NG;         // columns per pass
+    static constexpr int VEC = NP * CP;           // elements of a vector buffer
+    static constexpr int LDS(bool bwd) { return bwd ? 3 * VEC : VEC; }  // y, or x and two more vectors
+};
+
 // ---------------------------------------------------------------------------
-// Forward step of node kk of level lvl by one wavefront (buf: its slab buffer).
-template <int NP, int MC, class T>
-__device__ __forceinline__ void fwd_node(const SweepDesc<T>& P, int lvl, int64_t kk, T* __restrict__ buf) {
-    using G = Geo<NP>;
-    constexpr int RPL = G::RPL, LDB = G::LDB;
+// Forward step of node kk of level lvl by one team (wavefront w of it).
+template <int NP, class T, int NG, bool FLOW>
+__device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t kk, int w, T* __restrict__ lds,
+                                         const Flow& fl) {
+    using G = Team<NP, T, NG>;
+    using E = Eng<T>;
+    constexpr int W = G::W, CP = G::CP, SZ = (int)sizeof(T);
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t N = P.N;
-    const int n = P.n, m = P.m;
-    const size_t nn = (size_t)n * n, nm = (size_t)n * m;
-    const int64_t s = (int64_t)1 << lvl;
-    const int64_t i = (kk * 2 + 1) << lvl;
-    const bool has_r = i + s <= N, has_l = i > s;
-    const int64_t pi = perm_pos(N, lvl, i);
-    const int ns = (n + kS - 1) / kS;
-    // L_ii column slabs (lower part), R_i column slabs, T_i row slabs
-    Plan<T> pl;
-    pl.clear();
-    pl.set(0, {P.Ld + pi * nn, ns, false, false, true});
-    pl.set(1, {P.Rb + pi * nn, has_r ? ns : 0, false, false, false});
-    pl.set(2, {P.Tb + pi * nn, has_l ? ns : 0, true, false, false});
-
-    for (int q0 = 0; q0 < m; q0 += MC) {
-        T acc[RPL][MC], u[RPL][MC], v[RPL][MC];
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                T a = T(0);
-                if (r < n && q < m) {
-                    const size_t bidx = ((size_t)(i - 1) * n + r) * m + q;
-                    a = P.B64 ? (T)P.B64[bidx] : P.B[bidx];
-                    a = pull(P, a, i, lvl, (size_t)r * m + q, nm);
-                }
-                acc[rr][c] = a;
-                u[rr][c] = T(0);
-                v[rr][c] = T(0);
-            }
-        }
-        run_slabs<NP, T, slab_depth<NP, T>()>(pl, n, lane, buf, [&](int g, int q, const T* b) {
-            if (g == 0) {
-                // y = L^{-1} acc over columns j of this slab
-                for (int k = 0; k < kS; ++k) {
-                    const int j = kS * q + k;
-                    if (j >= n) break;
-                    const T inv = T(1) / b[k * LDB + j];
-                    T yj[MC];
-#pragma unroll
-                    for (int c = 0; c < MC; ++c) yj[c] = row_value<RPL, MC, T>(acc, j, c) * inv;
-#pragma unroll
-                    for (int rr = 0; rr < RPL; ++rr) {
-                        const int r = lane + kWave * rr;
-                        const T l = b[k * LDB + r];
-#pragma unroll
-                        for (int c = 0; c < MC; ++c) {
-                            if (r == j) acc[rr][c] = yj[c];
-                            else if (r > j) acc[rr][c] = fma(-l, yj[c], acc[rr][c]);
-                        }
-                    }
-                }
-            } else if (g == 1) {
-                slab_axpy<NP, MC, T>(u, b, acc, kS * q, n, T(1), 0, lane);  // u += R y
-            } else {
-                slab_axpy<NP, MC, T>(v, b, acc, kS * q, n, T(1), 0, lane);  // v += T^T y
-            }
-        });
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-            if (r >= n) continue;
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                if (q >= m) continue;
-                const size_t o = (size_t)pi * nm + (size_t)r * m + q;
-                P.Y[o] = acc[rr][c];
-                if (has_r) P.U[o] = u[rr][c];
-                if (has_l) P.V[o] = v[rr][c];
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Backward step of node kk of level lvl by one wavefront.
-template <int NP, int MC, class T>
-__device__ __forceinline__ void bwd_node(const SweepDesc<T>& P, int lvl, int64_t kk, T* __restrict__ buf) {
-    using G = Geo<NP>;
-    constexpr int RPL = G::RPL, LDB = G::LDB;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t N = P.N;
-    const int n = P.n, m = P.m;
-    const size_t nn = (size_t)n * n, nm = (size_t)n * m;
-    const int64_t s = (int64_t)1 << lvl;
-    const int64_t i = (kk * 2 + 1) << lvl;
-    const bool has_r = i + s <= N, has_l = i > s;
-    const int64_t pi = perm_pos(N, lvl, i);
-    const int ns = (n + kS - 1) / kS;
-    // R_i row slabs, T_i column slabs, L_ii row slabs from the last one up
-    Plan<T> pl;
-    pl.clear();
-    pl.set(0, {P.Rb + pi * nn, has_r ? ns : 0, true, false, false});
-    pl.set(1, {P.Tb + pi * nn, has_l ? ns : 0, false, false, false});
-    pl.set(2, {P.Ld + pi * nn, ns, true, true, true});
-
-    for (int q0 = 0; q0 < m; q0 += MC) {
-        T acc[RPL][MC], xr[RPL][MC], xl[RPL][MC];
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                const bool ok = r < n && q < m;
-                acc[rr][c] = ok ? P.Y[(size_t)pi * nm + (size_t)r * m + q] : T(0);
-                xr[rr][c] = (ok && has_r) ? P.X[((size_t)(i + s - 1) * n + r) * m + q] : T(0);
-                xl[rr][c] = (ok && has_l) ? P.X[((size_t)(i - s - 1) * n + r) * m + q] : T(0);
-            }
-        }
-        run_slabs<NP, T, slab_depth<NP, T>()>(pl, n, lane, buf, [&](int g, int q, const T* b) {
-            if (g < 2) {
-                // acc -= R^T x_{i+s} (g = 0) or T x_{i-s} (g = 1); the vector is
-                // selected element by element so that both stay in registers
-                T xv[RPL][MC];
-#pragma unroll
-                for (int rr = 0; rr < RPL; ++rr)
-#pragma unroll
-                    for (int c = 0; c < MC; ++c) xv[rr][c] = g == 0 ? xr[rr][c] : xl[rr][c];
-                slab_axpy<NP, MC, T>(acc, b, xv, kS * q, n, T(-1), 0, lane);
-            } else {
-                // x = L^{-T} acc over rows j of this slab, last row first
-                const int sl = ns - 1 - q;
-                for (int k = kS - 1; k >= 0; --k) {
-                    const int j = kS * sl + k;
-                    if (j >= n) continue;
-                    const T inv = T(1) / b[k * LDB + j];
-                    T xj[MC];
-#pragma unroll
-                    for (int c = 0; c < MC; ++c) xj[c] = row_value<RPL, MC, T>(acc, j, c) * inv;
-#pragma unroll
-                    for (int rr = 0; rr < RPL; ++rr) {
-                        const int r = lane + kWave * rr;
-                        const T l = b[k * LDB + r];
-#pragma unroll
-                        for (int c = 0; c < MC; ++c) {
-                            if (r == j) acc[rr][c] = xj[c];
-                            else if (r < j) acc[rr][c] = fma(-l, xj[c], acc[rr][c]);
-                        }
-                    }
-                }
-            }
-        });
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-            if (r >= n) continue;
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                if (q >= m) continue;
-                const size_t idx = ((size_t)(i - 1) * n + r) * m + q;
-                P.X[idx] = acc[rr][c];
-                if (P.X64) P.X64[idx] = P.first ? (double)acc[rr][c] : P.X64[idx] + (double)acc[rr][c];
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// One level of one or many instances: one wavefront per node.
-template <int NP, int MC, class T>
-__global__ __launch_bounds__(kWave) void k_fwd(Launch<SweepDesc<T>> L) {
-    __shared__ T buf[Geo<NP>::BUF];
-    SweepDesc<T> P;
-    int lvl;
-    int64_t kk;
-    fetch_item(L, P, lvl, kk);
-    if (skip_item(P)) return;
-    fwd_node<NP, MC, T>(P, lvl, kk, buf);
-}
-
-template <int NP, int MC, class T>
-__global__ __launch_bounds__(kWave) void k_bwd(Launch<SweepDesc<T>> L) {
-    __shared__ T buf[Geo<NP>::BUF];
-    SweepDesc<T> P;
-    int lvl;
-    int64_t kk;
-    fetch_item(L, P, lvl, kk);
-    if (skip_item(P)) return;
-    bwd_node<NP, MC, T>(P, lvl, kk, buf);
-}
-
-// Several levels in one launch.  The nodes of levels l0 .. l1-1 that lie
-// strictly between the blocks j 2^l1 and (j+1) 2^l1 form a subtree of the
-// elimination tree whose forward steps read only each other's results and
-// those of levels below l0 (a level-l node pulls from the blocks within s of
-// it), and whose backward steps read only each other's results and those of
-// levels l1 and above (the two blocks at the subtree's ends).  Item (inst, l0
-// | l1 << 8, j) is that subtree; its KW wavefronts take the nodes of one level
-// at a time (forward: levels ascending, backward: descending), with a
-// workgroup barrier between levels: the wavefronts of a workgroup share one
-// compute unit and its vector L1, so the barrier's workgroup-scope release
-// and acquire make one level's global stores visible to the next level's
-// loads (an agent-scope fence would write back and invalidate the L2 at
-// every level).
-template <int NP, int MC, class T, int KW, bool BWD>
-__global__ __launch_bounds__(KW * kWave) void k_sweep_chunk(Launch<SweepDesc<T>> L) {
-    __shared__ T buf[KW][Geo<NP>::BUF];
-    SweepDesc<T> P;
-    int code;
-    int64_t j;
-    fetch_item(L, P, code, j);
-    if (skip_item(P)) return;  // uniform over the workgroup
-    const int l0 = code & 0xff, l1 = code >> 8;
-    const int w = wave_id();
-    const int64_t N = P.N;
-    for (int t = 0; t < l1 - l0; ++t) {
-        const int l = BWD ? l1 - 1 - t : l0 + t;
-        const int64_t per = (int64_t)1 << (l1 - l - 1);  // nodes of a full subtree at level l
-        const int64_t s = (int64_t)1 << l;
-        const int64_t k0 = j * per, nodes = (N + s) / (2 * s);
-        const int64_t k1 = k0 + per < nodes ? k0 + per : nodes;
-        for (int64_t k = k0 + w; k < k1; k += KW) {
-            if (BWD)
-                bwd_node<NP, MC, T>(P, l, k, buf[w]);
-            else
-                fwd_node<NP, MC, T>(P, l, k, buf[w]);
-        }
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Residual in two kernels, every block read from HBM once.  The wavefront of
-// block row i streams the lower triangle of D_i and the coupling E_i (block
-// (i+1, i)) as row slabs and uses each element M[c][r] twice: as M^T[r][c]
-// (lane r, the vector's row c broadcast) and as M[c][r] (lane r's product
-// with the lane's own vector row, summed over the wavefront into row c):
-//   P_i     = b_i - D_i x_i - E_i^T x_{i+1}
-//   Q_{i+1} = E_i x_i
-// The second kernel forms r_i = P_i - Q_i, its FP32 copy and the per-column
-// partial squared norms of r_i and b_i.  Work items of consecutive block rows
-// share an XCD (xcd_local_block).
-
-// Value of the exchange partner across lane bit H: DPP within rows of 16
-// lanes (the row mirror for bit 3, the half-row mirror for bit 2, quad
-// permutations for bits 1 and 0), LDS permute across rows.  Each pairing is
-// an involution whose pairs differ in bit H and otherwise only in lower bits.
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const long long w = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)w, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(w >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-template <int H>
-__device__ __forceinline__ double partner(double v) {
-    if constexpr (H == 8) return dpp_d<0x140>(v);       // row_mirror
-    else if constexpr (H == 4) return dpp_d<0x141>(v);  // row_half_mirror
-    else if constexpr (H == 2) return dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    else if constexpr (H == 1) return dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    else return __shfl_xor(v, H);
-}
-// Lane bit of exchange step T: bits 3, 2, 1, 0 first (a mirror also flips
-// the bits below its own, so those must not be bound to a value yet), then
-// 4 and 5.
-constexpr int step_bit(int t) { return t < 4 ? 8 >> t : 16 << (t - 4); }
-
-// Halving exchanges from step T on, W values per lane in play: the lane
-// keeps the half its step bit selects and adds its partner's copy of it.
-template <int W, int T>
-__device__ __forceinline__ void halve(double* v, int lane) {
-    if constexpr (W >= 1) {
-        constexpr int H = step_bit(T);
-        const bool up = (lane & H) != 0;
-#pragma unroll
-        for (int j = 0; j < W; ++j) {
-            const double send = up ? v[j] : v[j + W];
-            const double keep = up ? v[j + W] : v[j];
-            v[j] = keep + partner<H>(send);
-        }
-        halve<W / 2, T + 1>(v, lane);
-    }
-}
-template <int T>
-__device__ __forceinline__ double all_sum(double s) {
-    if constexpr (T < 6) return all_sum<T + 1>(s + partner<step_bit(T)>(s));
-    else return s;
-}
-constexpr int ilog2_c(int v) { return v <= 1 ? 0 : 1 + ilog2_c(v / 2); }
-
-// Sum over the wavefront of KB values per lane (KB a power of two <= 16).
-// Afterwards the lanes given by row_source hold the totals.  Every total is
-// formed by the same tree of additions whatever KB is, so chunking rows
-// differently does not change a bit of the result.
-template <int KB>
-__device__ __forceinline__ double wave_sum_rows(double (&v)[KB], int lane) {
-    static_assert(KB >= 1 && KB <= 16 && (KB & (KB - 1)) == 0, "power of two up to 16");
-    halve<KB / 2, 0>(v, lane);
-    return all_sum<ilog2_c(KB)>(v[0]);
-}
-// A lane that holds the total of value k after wave_sum_rows<KB>: step t of
-// the halving bound the value's bit KB / 2^(t+1) to lane bit step_bit(t).
-template <int KB>
-__device__ __forceinline__ int row_source(int k) {
-    int l = 0;
-#pragma unroll
-    for (int t = 0, w = KB / 2; w >= 1; ++t, w /= 2)
-        if (k & w) l |= step_bit(t);
-    return l;
-}
-
-template <int NP, int MC>
-__global__ __launch_bounds__(kWave) void k_res(Launch<ResidualDesc> L) {
-    using G = Geo<NP>;
-    constexpr int RPL = G::RPL, LDB = G::LDB;
-    constexpr int KB = 4 / MC;              // slab rows per wavefront sum (4 sums live)
-    static_assert(KB >= 1 && kS % KB == 0, "chunks divide the slab");
-    __shared__ double buf[G::BUF];
-    ResidualDesc P;
-    int64_t row0;
-    {
-        const unsigned b = xcd_local_block();
-        if (L.items) {
-            const WorkItem it = L.items[b];
-            P = L.descs[it.inst];
-            row0 = it.k;
-        } else {
-            P = L.single;
-            row0 = b;
-        }
-    }
-    if (P.state && P.state->done) return;
-    const int lane = threadIdx.x;
-    const int64_t N = P.N;
     const int n = P.n, m = P.m;
     const size_t nn = (size_t)n * n;
-    const int64_t i = row0 + 1;
-    const bool rgt = i < N;
-    const int ns = (n + kS - 1) / kS;
-    // D_i row slabs (the lower triangle: slab rows c, columns r <= last row
-    // of the slab), E_i row slabs
-    Plan<double> pl;
-    pl.clear();
-    pl.set(0, {P.A_diag + (size_t)(i - 1) * nn, ns, true, false, true});
-    pl.set(1, {rgt ? P.A_off + (size_t)(i - 1) * nn : nullptr, rgt ? ns : 0, true, false, false});
+    const Pos<T> d(P, lvl, kk);
+    const Kin<T> kin(P, d, lvl);
+    const int nt = (n + kTl - 1) / kTl;
+    const bool mine = w < nt;  // this wavefront has a tile row
+    T* ys = lds;               // y, [row][column of the pass]
+    // U of the right child and V of the left child are passed on with the
+    // node's own products
+    const bool pass_u = lvl > 0 && d.has_r, pass_v = lvl > 0 && d.has_l;
 
-    for (int q0 = 0; q0 < m; q0 += MC) {
-        // acc: b_i minus the broadcast products; dl: (D_i x_i) over the lower
-        // triangle; qa: E_i x_i.  dl and qa take one wavefront sum per row,
-        // so the result does not depend on how rows are chunked (MC).
-        double acc[RPL][MC], dl[RPL][MC], qa[RPL][MC], x1[RPL][MC], x2[RPL][MC];
+    T Lr[W][4], Rr[W][4], Tr[W][4], Dr[4];
+    // one pass over columns q0 .. q0+CP-1; the first one, compiled on its own,
+    // loads the blocks (in code shared with the others its waits would have
+    // to hold for passes in which no block load follows the vectors)
+    auto pass = [&](int q0, auto load) {
+        constexpr bool LOAD = decltype(load)::value;
+        const int cols = m - q0 < CP ? m - q0 : CP;
+        typename E::Acc acc[NG], u[NG], v[NG], sl[NG], sr[NG];
+        double b64[NG][E::NV];
+        int vo[NG][E::NV];  // offsets of the lane's elements in a node's vectors
+        const bool wide = sizeof(T) == 4 && P.B64;  // the right-hand side is FP64
+        auto load_rhs = [&]() {
 #pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
+            for (int g = 0; g < NG; ++g) {
+                const int c = E::CW * g + E::col(lane);
 #pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                const bool ok = r < n && q < m;
-                acc[rr][c] = ok ? P.B[((size_t)(i - 1) * n + r) * m + q] : 0.0;
-                dl[rr][c] = 0.0;
-                qa[rr][c] = 0.0;
-                x1[rr][c] = ok ? P.X[((size_t)(i - 1) * n + r) * m + q] : 0.0;
-                x2[rr][c] = (ok && rgt) ? P.X[((size_t)i * n + r) * m + q] : 0.0;
+                for (int x = 0; x < E::NV; ++x) {
+                    const int r = E::row(x, lane);
+                    const bool ok = kTl * w + r < n && c < cols;
+                    vo[g][x] = ok ? (r * m + q0 + c) * SZ : kOob;
+                    buf_ld(acc[g].v[x], vec_rsrc(P.B, n, m, d.i - 1, !wide, w), vo[g][x]);
+                    if constexpr (SZ == 4)
+                        buf_ld(b64[g][x], vec_rsrc(P.B64, n, m, d.i - 1, wide, w), ok ? 2 * vo[g][x] : kOob);
+                }
+            }
+        };
+        auto load_sums = [&]() {
+            constexpr int AUX = FLOW ? kCoherent : 0;
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int x = 0; x < E::NV; ++x) {
+                    buf_ld<AUX>(sl[g].v[x], vec_rsrc(P.U, n, m, kin.pl, kin.left, w), vo[g][x]);
+                    buf_ld<AUX>(sr[g].v[x], vec_rsrc(P.V, n, m, kin.pr, kin.right, w), vo[g][x]);
+                    buf_ld<AUX>(u[g].v[x], vec_rsrc(P.U, n, m, kin.pr, pass_u, w), vo[g][x]);
+                    buf_ld<AUX>(v[g].v[x], vec_rsrc(P.V, n, m, kin.pl, pass_v, w), vo[g][x]);
+                }
+        };
+        // the vectors go out ahead of the block loads; the children's sums
+        // after them where they have to be waited for
+        load_rhs();
+        if constexpr (!FLOW || !LOAD) load_sums();
+        keep_order();
+        if constexpr (LOAD) {
+            const Lane<T> ln(lane, n, kTl * w);
+            const __amdgpu_buffer_rsrc_t lr = block_rsrc(P.Ld + d.pi * nn, mine ? n * n * SZ : 0),
+                                         rr = block_rsrc(P.Rb + d.pi * nn, mine && d.has_r ? n * n * SZ : 0),
+                                         tr = block_rsrc(P.Tb + d.pi * nn, mine && d.has_l ? n * n * SZ : 0);
+            load_dinv<T, false>(Dr, lr, n, w, lane);
+            keep_order();
+#pragma unroll
+            for (int p = 0; p + 1 < W; ++p) load_rowwise(Lr[p], lr, ln, p < w ? (kTl * w * n + kTl * p) * SZ : kOob);
+            keep_order();
+#pragma unroll
+            for (int p = 0; p < W; ++p) {
+                load_rowwise(Rr[p], rr, ln, p < nt ? (kTl * w * n + kTl * p) * SZ : kOob);
+                load_colwise(Tr[p], tr, ln, p < nt ? kTl * p * n * SZ : kOob);
+                keep_order();
+            }
+            if constexpr (FLOW) {
+                flow_wait(kin.left && lvl - 1 >= fl.l0 ? fl.flag + kin.pl : nullptr,
+                          kin.right && kin.l2 >= fl.l0 ? fl.flag + kin.pr : nullptr, w);
+                load_sums();
             }
         }
-        run_slabs<NP, double, slab_depth<NP, double>()>(pl, n, lane, buf, [&](int g, int q, const double* b) {
-            // g = 0: slab row c of D_i (elements with r <= c valid); g = 1:
-            // row c of E_i.  Rows past n are zero.
-            const int off = kS * q, dslot = off / kWave;
-#pragma unroll 1
-            for (int k0 = 0; k0 < kS; k0 += KB) {
-                double ps[MC][KB];
 #pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int cc = off + k0 + k;
-                    double xb[MC];
+        for (int g = 0; g < NG; ++g)
 #pragma unroll
-                    for (int c = 0; c < MC; ++c) {
-                        double t = g == 0 ? x1[0][c] : x2[0][c];
-#pragma unroll
-                        for (int rr = 1; rr < RPL; ++rr)
-                            if (cc >= kWave * rr) t = g == 0 ? x1[rr][c] : x2[rr][c];
-                        xb[c] = -bcast(t, cc & (kWave - 1));
-                        ps[c][k] = 0.0;
-                    }
-#pragma unroll
-                    for (int rr = 0; rr < RPL; ++rr) {
-                        const int r = lane + kWave * rr;
-                        // columns r in [n, NP) of the slab are zero; lanes r >= NP
-                        // would read the next slab row (perhaps the unread
-                        // upper triangle of D_i) and feed the wavefront sums
-                        const double a = (NP % kWave == 0 || rr < RPL - 1 || r < NP) ? b[(k0 + k) * LDB + r] : 0.0;
-                        if (g == 0 && rr == dslot) {
-                            // the diagonal tile of D_i: as element (r, c) above
-                            // the diagonal (r < c), as element (c, r) on and
-                            // below it
-                            const double au = r >= cc ? 0.0 : a;
-                            const double al = r > cc ? 0.0 : a;
-#pragma unroll
-                            for (int c = 0; c < MC; ++c) {
-                                acc[rr][c] = fma(au, xb[c], acc[rr][c]);
-                                ps[c][k] = fma(al, x1[rr][c], ps[c][k]);
-                            }
-                        } else {
-                            // D_i left of the diagonal tile (the rest of the
-                            // slab row is zero), E_i: both uses
-#pragma unroll
-                            for (int c = 0; c < MC; ++c) {
-                                acc[rr][c] = fma(a, xb[c], acc[rr][c]);
-                                ps[c][k] = fma(a, x1[rr][c], ps[c][k]);
-                            }
-                        }
-                    }
-                }
-                // row c = off + k0 + k gets its sum from lane row_source(k);
-                // its owner is lane c % 64 in slot c / 64
-                const int base = off + k0, slot = base / kWave;
-                const int k = lane - (base & (kWave - 1));
-                const int src = row_source<KB>(k & (KB - 1));
-#pragma unroll
-                for (int c = 0; c < MC; ++c) {
-                    const double s = wave_sum_rows<KB>(ps[c], lane);
-                    const double t = __shfl(s, src);
-                    if (k >= 0 && k < KB) {
-#pragma unroll
-                        for (int rr = 0; rr < RPL; ++rr) {
-                            if (rr == slot) {
-                                if (g == 0)
-                                    dl[rr][c] += t;
-                                else
-                                    qa[rr][c] += t;
-                            }
-                        }
-                    }
-                }
+            for (int x = 0; x < E::NV; ++x) {
+                if (SZ == 4) acc[g].v[x] += (T)b64[g][x];  // the absent one of the two reads 0
+                acc[g].v[x] = (acc[g].v[x] - sl[g].v[x]) - sr[g].v[x];
             }
-        });
+        if constexpr (LOAD) invert_diag(Dr, n, w, lane);
+        // y tile w = Dinv_w acc to LDS for the team
+        auto publish = [&]() {
 #pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
+            for (int g = 0; g < NG; ++g) {
+                if (E::CW * g >= cols) break;
+                acc[g] = E::dmul(Dr, acc[g]);
+                const int c = E::CW * g + E::col(lane);
 #pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                if (r < n && q < m) {
-                    P.P[((size_t)(i - 1) * n + r) * m + q] = acc[rr][c] - dl[rr][c];
-                    if (rgt) P.Q[((size_t)i * n + r) * m + q] = qa[rr][c];
+                for (int x = 0; x < E::NV; ++x) ys[(kTl * w + E::row(x, lane)) * CP + c] = acc[g].v[x];
+            }
+        };
+        if (w == 0) publish();
+#pragma unroll
+        for (int p = 0; p < W; ++p) {
+            if (p >= nt) break;
+            __syncthreads();
+            if (!mine) continue;
+            T b[NG][4];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (E::CW * g >= cols) break;
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    b[g][s] = ys[(kTl * p + E::kidx(s, lane >> 4)) * CP + E::CW * g + E::col(lane)];
+            }
+            if (p + 1 < W && w > p) {
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    if (E::CW * g >= cols) break;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) E::mma(acc[g], Lr[p + 1 < W ? p : 0][s], -b[g][s]);
+                }
+                // the next tile of the chain before the products off it
+                if (w == p + 1) publish();
+            }
+            if (kTl * p + kTl > n) mask_tail(Rr[p], n, kTl * p, lane);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (E::CW * g >= cols) break;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    E::mma(u[g], Rr[p][s], b[g][s]);
+                    E::mma(v[g], Tr[p][s], b[g][s]);
                 }
             }
         }
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int x = 0; x < E::NV; ++x) {
+                constexpr int AUX = FLOW ? kCoherent : 0;
+                buf_st(acc[g].v[x], vec_rsrc(P.Y, n, m, d.pi, true, w), vo[g][x]);
+                buf_st<AUX>(u[g].v[x], vec_rsrc(P.U, n, m, d.pi, d.has_r, w), vo[g][x]);
+                buf_st<AUX>(v[g].v[x], vec_rsrc(P.V, n, m, d.pi, d.has_l, w), vo[g][x]);
+            }
+    };
+    pass(0, std::true_type{});
+    for (int q0 = CP; q0 < m; q0 += CP) {
+        __syncthreads();  // the vector buffer is free again
+        pass(q0, std::false_type{});
     }
+    if constexpr (FLOW) flow_signal(parent_level(d, lvl) < fl.l1 ? fl.flag + d.pi : nullptr, nullptr);
 }
 
-// r_i = P_i - Q_i (Q_1 = 0), its FP32 copy and the partial norms; one
-// wavefront per block row.
-__global__ __launch_bounds__(kWave) void k_res_fin(Launch<ResidualDesc> L) {
-    ResidualDesc P;
-    int level;
-    int64_t row0;
-    fetch_item(L, P, level, row0);
-    if (P.state && P.state->done) return;
-    const int lane = threadIdx.x;
+// ---------------------------------------------------------------------------
+// Backward step of node kk of level lvl by one team.
+template <int NP, class T, int NG, bool FLOW>
+__device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t kk, int w, T* __restrict__ lds,
+                                         const Flow& fl) {
+    using G = Team<NP, T, NG>;
+    using E = Eng<T>;
+    constexpr int W = G::W, CP = G::CP, SZ = (int)sizeof(T);
+    const int lane = threadIdx.x & (kWave - 1);
     const int n = P.n, m = P.m;
-    const int64_t i = row0 + 1;
-    for (int q = 0; q < m; ++q) {
-        double r2 = 0.0, b2 = 0.0;
-        for (int r = lane; r < n; r += kWave) {
-            const size_t e = ((size_t)(i - 1) * n + r) * m + q;
-            const double v = i > 1 ? P.P[e] - P.Q[e] : P.P[e];
-            if (P.R32) P.R32[e] = (float)v;
-            if (P.R64) P.R64[e] = P.neg ? -v : v;
-            const double bv = P.B[e];
-            r2 = fma(v, v, r2);
-            b2 = fma(bv, bv, b2);
+    const size_t nn = (size_t)n * n;
+    const Pos<T> d(P, lvl, kk);
+    const int nt = (n + kTl - 1) / kTl;
+    const bool mine = w < nt;
+    T* xs = lds;                 // x, [row][column of the pass]
+    T* rs = lds + G::VEC;        // x_{i+s}
+    T* ls = lds + 2 * G::VEC;    // x_{i-s}
+
+    T Lr[W][4], Rr[W][4], Tr[W][4], Dr[4];
+    auto pass = [&](int q0, auto load) {
+        constexpr bool LOAD = decltype(load)::value;
+        const int cols = m - q0 < CP ? m - q0 : CP;
+        constexpr int PER = kTl * CP / kWave;
+        T xr[PER], xl[PER];
+        double x0[NG][E::NV];
+        typename E::Acc acc[NG];
+        int vo[NG][E::NV];  // offsets of the lane's elements in a node's vectors
+        // the neighbours' solutions (rows past n: zero)
+        auto load_neighbours = [&]() {
+            constexpr int AUX = FLOW ? kCoherent : 0;
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int e = lane + kWave * k, r = e / CP, c = e % CP;
+                const int off = (kTl * w + r < n && c < cols) ? (r * m + q0 + c) * SZ : kOob;
+                buf_ld<AUX>(xr[k], vec_rsrc(P.X, n, m, d.i + d.s - 1, d.has_r, w), off);
+                buf_ld<AUX>(xl[k], vec_rsrc(P.X, n, m, d.i - d.s - 1, d.has_l, w), off);
+            }
+        };
+        // the vectors go out ahead of the block loads (the neighbours' where
+        // they need no wait): the node's y and the iterate it corrects
+        if constexpr (!FLOW || !LOAD) load_neighbours();
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int c = E::CW * g + E::col(lane);
+#pragma unroll
+            for (int x = 0; x < E::NV; ++x) {
+                const int r = E::row(x, lane);
+                const bool ok = kTl * w + r < n && c < cols;
+                vo[g][x] = ok ? (r * m + q0 + c) * SZ : kOob;
+                buf_ld(acc[g].v[x], vec_rsrc(P.Y, n, m, d.pi, true, w), vo[g][x]);
+                if constexpr (SZ == 4)
+                    buf_ld(x0[g][x], vec_rsrc(P.X64, n, m, d.i - 1, P.X64 && !P.first, w), ok ? 2 * vo[g][x] : kOob);
+            }
+        }
+        keep_order();
+        if constexpr (LOAD) {
+            const Lane<T> ln(lane, n, kTl * w);
+            const __amdgpu_buffer_rsrc_t lr = block_rsrc(P.Ld + d.pi * nn, mine ? n * n * SZ : 0),
+                                         rr = block_rsrc(P.Rb + d.pi * nn, mine && d.has_r ? n * n * SZ : 0),
+                                         tr = block_rsrc(P.Tb + d.pi * nn, mine && d.has_l ? n * n * SZ : 0);
+#pragma unroll
+            for (int p = 0; p < W; ++p) {
+                load_colwise(Rr[p], rr, ln, p < nt ? kTl * p * n * SZ : kOob);
+                load_rowwise(Tr[p], tr, ln, p < nt ? (kTl * w * n + kTl * p) * SZ : kOob);
+                keep_order();
+            }
+            load_dinv<T, true>(Dr, lr, n, w, lane);
+            keep_order();
+#pragma unroll
+            for (int p = W - 1; p > 0; --p) {
+                load_colwise(Lr[p], lr, ln, p > w && p < nt ? kTl * p * n * SZ : kOob);
+                keep_order();
+            }
+            if constexpr (FLOW) {
+                flow_wait(parent_level(d, lvl) < fl.l1 ? fl.flag + d.pi : nullptr, nullptr, w);
+                load_neighbours();
+            }
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            r2 += __shfl_xor(r2, off);
-            b2 += __shfl_xor(b2, off);
+        for (int k = 0; k < PER; ++k) {
+            rs[kTl * CP * w + lane + kWave * k] = xr[k];
+            ls[kTl * CP * w + lane + kWave * k] = xl[k];
         }
-        if (lane == 0) {
-            P.part[((size_t)(i - 1) * m + q) * 2 + 0] = r2;
-            P.part[((size_t)(i - 1) * m + q) * 2 + 1] = b2;
+        __syncthreads();
+        auto operand = [&](const T* vec, int p, int g, int s) {
+            return vec[(kTl * p + E::kidx(s, lane >> 4)) * CP + E::CW * g + E::col(lane)];
+        };
+        if (mine) {
+#pragma unroll
+            for (int p = 0; p < W; ++p) {
+                if (p >= nt) break;
+                if (kTl * p + kTl > n) mask_tail(Tr[p], n, kTl * p, lane);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    if (E::CW * g >= cols) break;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        E::mma(acc[g], Rr[p][s], -operand(rs, p, g, s));
+                        E::mma(acc[g], Tr[p][s], -operand(ls, p, g, s));
+                    }
+                }
+            }
         }
+        if constexpr (LOAD) invert_diag(Dr, n, w, lane);
+        // tile p of x = Dinv_p^T acc to LDS for the team, then its share of the
+        // tiles above it
+#pragma unroll
+        for (int p = W - 1; p >= 0; --p) {
+            if (p >= nt) continue;
+            if (mine && w == p) {
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    if (E::CW * g >= cols) break;
+                    acc[g] = E::dmul(Dr, acc[g]);
+                    const int c = E::CW * g + E::col(lane);
+#pragma unroll
+                    for (int x = 0; x < E::NV; ++x) xs[(kTl * w + E::row(x, lane)) * CP + c] = acc[g].v[x];
+                }
+            }
+            if (p == 0) break;
+            __syncthreads();
+            if (mine && w < p) {
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    if (E::CW * g >= cols) break;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) E::mma(acc[g], Lr[p][s], -operand(xs, p, g, s));
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int x = 0; x < E::NV; ++x) {
+                buf_st<FLOW ? kCoherent : 0>(acc[g].v[x], vec_rsrc(P.X, n, m, d.i - 1, true, w), vo[g][x]);
+                if constexpr (SZ == 4)
+                    buf_st(x0[g][x] + (double)acc[g].v[x],  // first: the absent iterate reads 0
+                           vec_rsrc(P.X64, n, m, d.i - 1, P.X64, w), vo[g][x] == kOob ? kOob : 2 * vo[g][x]);
+            }
+    };
+    pass(0, std::true_type{});
+    for (int q0 = CP; q0 < m; q0 += CP) {
+        __syncthreads();  // the vector buffers are free again
+        pass(q0, std::false_type{});
+    }
+    if constexpr (FLOW) {
+        const Kin<T> kin(P, d, lvl);
+        flow_signal(kin.left && lvl - 1 >= fl.l0 ? fl.flag + kin.pl : nullptr,
+                    kin.right && kin.l2 >= fl.l0 ? fl.flag + kin.pr : nullptr);
     }
 }
 
-template <int NP, class T>
-hipError_t launch_sweep_np(const Launch<SweepDesc<T>>& p, int64_t items, bool backward, int mc, hipStream_t st) {
-    const dim3 g((unsigned)items), b(kWave);
-    if (mc <= 1) {
+// ---------------------------------------------------------------------------
+// One level of one or many instances: one workgroup (one team) per node.
+template <int NP, class T, int NG, bool BWD>
+__global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_level(Launch<SweepDesc<T>> L) {
+    __shared__ T lds[Team<NP, T, NG>::LDS(BWD)];
+    SweepDesc<T> P;
+    int lvl;
+    int64_t kk;
+    fetch_item(L, P, lvl, kk);
+    if (skip_item(P)) return;
+    const Flow none{nullptr, 0, 0};
+    if constexpr (BWD)
+        bwd_team<NP, T, NG, false>(P, lvl, kk, wave_id(), lds, none);
+    else
+        fwd_team<NP, T, NG, false>(P, lvl, kk, wave_id(), lds, none);
+}
+
+// A range of levels in one launch.  The item level field holds l0 | l1 << 8
+// and, of explicit items, the node's level << 16; they are in level order
+// (forward ascending, backward descending), as are the implicit ones.  The
+// workgroups take them by ticket: a workgroup that waits only waits for ones
+// that started before it, so the launch always makes progress, whatever the
+// dispatch order and whatever else runs on the GPU.  The last ticket resets
+// the counter.
+template <int NP, class T, int NG, bool BWD>
+__global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<SweepDesc<T>> L) {
+    __shared__ T lds[Team<NP, T, NG>::LDS(BWD)];
+    __shared__ int slot;
+    if (threadIdx.x == 0) {
+        const int t = __hip_atomic_fetch_add(L.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == (int)gridDim.x - 1) flag_store(L.ticket, 0);
+        slot = t;
+    }
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(slot);
+    SweepDesc<T> P;
+    int code, lvl;
+    int64_t kk;
+    fetch_item_at(L, t, P, code, kk);
+    const int l0 = code & 0xff, l1 = (code >> 8) & 0xff;
+    if (L.items) {
+        lvl = code >> 16;
+    } else {
+        // position of node t of the range, its level and number
+        const int64_t N = P.N, p = BWD ? N - (N >> l1) - 1 - kk : N - (N >> l0) + kk, left = N - p;
+        lvl = __builtin_clzll((unsigned long long)left) - __builtin_clzll((unsigned long long)N);
+        if ((N >> lvl) < left) --lvl;
+        kk = p - (N - (N >> lvl));
+    }
+    if (skip_item(P)) return;
+    const Flow fl{P.flow, l0, l1};
+    if constexpr (BWD)
+        bwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
+    else
+        fwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
+}
+
+template <int NP, class T, int NG>
+hipError_t launch_ng(const Launch<SweepDesc<T>>& p, int64_t items, bool backward, hipStream_t st, bool flow) {
+    const dim3 g((unsigned)items), b(Team<NP, T, NG>::TH);
+    if (!flow) {
         if (backward)
-            hipLaunchKernelGGL((k_bwd<NP, 1, T>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, true>), g, b, 0, st, p);
         else
-            hipLaunchKernelGGL((k_fwd<NP, 1, T>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, false>), g, b, 0, st, p);
     } else {
         if (backward)
-            hipLaunchKernelGGL((k_bwd<NP, 4, T>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, true>), g, b, 0, st, p);
         else
-            hipLaunchKernelGGL((k_fwd<NP, 4, T>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, false>), g, b, 0, st, p);
     }
     return hipGetLastError();
 }
 
-template <int NP, class T, int KW>
-hipError_t launch_chunk_kw(const Launch<SweepDesc<T>>& p, int64_t items, bool backward, int mc, hipStream_t st) {
-    const dim3 g((unsigned)items), b(KW * kWave);
-    if (mc <= 1) {
-        if (backward)
-            hipLaunchKernelGGL((k_sweep_chunk<NP, 1, T, KW, true>), g, b, 0, st, p);
-        else
-            hipLaunchKernelGGL((k_sweep_chunk<NP, 1, T, KW, false>), g, b, 0, st, p);
-    } else {
-        if (backward)
-            hipLaunchKernelGGL((k_sweep_chunk<NP, 4, T, KW, true>), g, b, 0, st, p);
-        else
-            hipLaunchKernelGGL((k_sweep_chunk<NP, 4, T, KW, false>), g, b, 0, st, p);
-    }
-    return hipGetLastError();
+// Column groups per pass: FP64 one group of four columns, or with more than
+// four columns (mc > 4) four of them, two above n = 64 (a node's blocks leave
+// registers for no more there); FP32 always one group of 16.
+template <int NP>
+hipError_t launch_np(const Launch<SweepDesc<double>>& p, int64_t items, bool backward, int mc, hipStream_t st,
+                     bool flow) {
+    return mc <= 4 ? launch_ng<NP, double, 1>(p, items, backward, st, flow)
+                   : launch_ng<NP, double, (NP > 64 ? 2 : 4)>(p, items, backward, st, flow);
 }
-
-template <int NP, class T>
-hipError_t launch_chunk_np(const Launch<SweepDesc<T>>& p, int64_t items, bool backward, int mc, hipStream_t st,
-                           int kw) {
-    return kw == 8 ? launch_chunk_kw<NP, T, 8>(p, items, backward, mc, st)
-                   : launch_chunk_kw<NP, T, 4>(p, items, backward, mc, st);
+template <int NP>
+hipError_t launch_np(const Launch<SweepDesc<float>>& p, int64_t items, bool backward, int, hipStream_t st,
+                     bool flow) {
+    return launch_ng<NP, float, 1>(p, items, backward, st, flow);
 }
 
 template <class T>
 hipError_t launch_sweep_t(const Launch<SweepDesc<T>>& p, int np, int64_t items, bool backward, int mc,
-                          hipStream_t st, bool chunk, int kw) {
+                          hipStream_t st, bool flow) {
     switch (np) {
         case 8:
-        case 16: return chunk ? launch_chunk_np<16, T>(p, items, backward, mc, st, kw) : launch_sweep_np<16, T>(p, items, backward, mc, st);
-        case 32: return chunk ? launch_chunk_np<32, T>(p, items, backward, mc, st, kw) : launch_sweep_np<32, T>(p, items, backward, mc, st);
-        case 64: return chunk ? launch_chunk_np<64, T>(p, items, backward, mc, st, kw) : launch_sweep_np<64, T>(p, items, backward, mc, st);
-        case 96: return chunk ? launch_chunk_np<96, T>(p, items, backward, mc, st, kw) : launch_sweep_np<96, T>(p, items, backward, mc, st);
-        case 128: return chunk ? launch_chunk_np<128, T>(p, items, backward, mc, st, kw) : launch_sweep_np<128, T>(p, items, backward, mc, st);
+        case 16: return launch_np<16>(p, items, backward, mc, st, flow);
+        case 32: return launch_np<32>(p, items, backward, mc, st, flow);
+        case 64: return launch_np<64>(p, items, backward, mc, st, flow);
+        case 96: return launch_np<96>(p, items, backward, mc, st, flow);
+        case 128: return launch_np<128>(p, items, backward, mc, st, flow);
         default: return hipErrorInvalidValue;
     }
-}
-
-template <int NP>
-hipError_t launch_res_np(const Launch<ResidualDesc>& p, int64_t items, int mc, hipStream_t st) {
-    const dim3 g((unsigned)items), b(kWave);
-    if (mc <= 1)
-        hipLaunchKernelGGL((k_res<NP, 1>), g, b, 0, st, p);
-    else
-        hipLaunchKernelGGL((k_res<NP, 4>), g, b, 0, st, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_res_fin, g, b, 0, st, p);
-    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool chunk, int kw) {
-    return launch_sweep_t<double>(p, np, items, backward, mc, st, chunk, kw);
+                        hipStream_t st, bool flow) {
+    return launch_sweep_t<double>(p, np, items, backward, mc, st, flow);
 }
 
 hipError_t launch_sweep(const Launch<SweepDesc<float>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool chunk, int kw) {
-    return launch_sweep_t<float>(p, np, items, backward, mc, st, chunk, kw);
-}
-
-hipError_t launch_residual(const Launch<ResidualDesc>& p, int np, int64_t items, int mc, hipStream_t st) {
-    switch (np) {
-        case 8:
-        case 16: return launch_res_np<16>(p, items, mc, st);
-        case 32: return launch_res_np<32>(p, items, mc, st);
-        case 64: return launch_res_np<64>(p, items, mc, st);
-        case 96: return launch_res_np<96>(p, items, mc, st);
-        case 128: return launch_res_np<128>(p, items, mc, st);
-        default: return hipErrorInvalidValue;
-    }
+                        hipStream_t st, bool flow) {
+    return launch_sweep_t<float>(p, np, items, backward, mc, st, flow);
 }
 
 }  // namespace btc

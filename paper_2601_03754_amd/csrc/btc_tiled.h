@@ -166,16 +166,18 @@ __device__ __forceinline__ void stage_lower_packed(double* __restrict__ dst, con
 }
 
 // Leading n x n part of a packed lower-tile LDS block to global memory as
-// type D (strict upper triangle written as 0); buffer stores, the part
-// beyond n dropped by offset.
+// type D: the lower tiles, the diagonal ones whole (their strict upper part
+// holds the tile's inverse, transposed); buffer stores, the part beyond n
+// dropped by offset.
 template <int NP, class D>
 __device__ __forceinline__ void store_lower_packed(D* __restrict__ dst, const double* __restrict__ src, int n, int t,
                                                    int nt) {
     const __amdgpu_buffer_rsrc_t rs = nn_rsrc(dst, n);
     for (int idx = t; idx < NP * NP; idx += nt) {
         const int r = idx / NP, c = idx % NP;
-        const double x = c <= r ? PackedLds::tile(src, r / kT, c / kT)[(r % kT) * kLDI + c % kT] : 0.0;
-        buf_st((D)x, rs, elem_off<D>(r, c, n, r < n && c < n));
+        const bool low = c / kT <= r / kT;
+        const double x = low ? PackedLds::tile(src, r / kT, c / kT)[(r % kT) * kLDI + c % kT] : 0.0;
+        buf_st((D)x, rs, elem_off<D>(r, c, n, low && r < n && c < n));
     }
 }
 

@@ -403,6 +403,20 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
 
 
 
+// L_ii (lower triangle of the NP x NP LDS block src, row stride NP+1) and its
+// inverted diagonal tiles inv (row stride kLDI) to an n x n global block as
+// type D: L below and on the diagonal, each tile's inverse transposed in the
+// strict upper part of its tile.
+template <int NP, class D, class S>
+__device__ __forceinline__ void store_factor_lds(D* __restrict__ dst, const S* __restrict__ src,
+                                                 const S (*__restrict__ inv)[kT * kLDI], int n, int t, int nt) {
+    for (int idx = t; idx < NP * NP; idx += nt) {
+        const int r = idx / NP, c = idx % NP;
+        if (r < n && c < n && c / kT <= r / kT)
+            dst[(size_t)r * n + c] = (D)(c <= r ? src[r * (NP + 1) + c] : inv[r / kT][(c % kT) * kLDI + r % kT]);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // FP32 tiles
 
