@@ -134,209 +134,162 @@ __device__ __forceinline__ double rsqrt_refined(double p) {
     return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
-// Cholesky of a 16-column panel held one row per lane: lanes 0..NC-1 hold
-// the rows of the NC x NC diagonal tile (zeros above the diagonal), any other
-// lane a row below it (or zeros).  Column j: the pivot row's lane forms
-// L_jj, every lane below it its multiplier a_rj / L_jj (for the rows below
-// the tile this is the triangular solve x L_pp^T = a), and the multipliers of
-// the pivot rows reach the later columns by readlane broadcasts (no LDS round
-// trip on the chain).  On return a holds the rows of L, myinv 1/L_rr on lane
-// r < NC; false on a non-positive or NaN pivot.
-template <int NC>
-__device__ __forceinline__ bool chol_rows(double (&a)[NC], double& myinv) {
-    const int lane = threadIdx.x & (kWave - 1);
-    double piv = readlane_d(a[0], 0);
-    double r = rsqrt_refined(piv);
-    myinv = 1.0;
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < NC; ++j) {
-        ok = ok && (piv > 0.0);
-        double l = a[j] * r;
-        l = (lane == j) ? piv * r : l;
-        l = (lane < j) ? 0.0 : l;
-        myinv = (lane == j) ? r : myinv;
-        a[j] = l;
-        if (j + 1 < NC) {
-            // the next pivot first: its reciprocal square root overlaps the
-            // rest of this column's update
-            a[j + 1] = fma(-l, readlane_d(l, j + 1), a[j + 1]);
-            piv = readlane_d(a[j + 1], j + 1);
-            const double rn = rsqrt_refined(piv);
-            double lc[NC];
-#pragma unroll
-            for (int c = j + 2; c < NC; ++c) lc[c] = readlane_d(l, c);
-#pragma unroll
-            for (int c = j + 2; c < NC; ++c) a[c] = fma(-l, lc[c], a[c]);
-            r = rn;
-        }
-    }
-    return ok;
+// Quad JB of every row of 16 lanes to all four quads of that row.
+template <int CTRL, int BANK>
+__device__ __forceinline__ double dpp_bank(double old, double x) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(x), CTRL, 0xF, BANK, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(x), CTRL, 0xF, BANK, false);
+    return __hiloint2double(hi, lo);
+}
+template <int JB>
+__device__ __forceinline__ double quad_bcast(double x) {
+    // quad b takes quad JB: a rotation by 4 (b - JB) lanes (row_ror)
+    double y = dpp_bank<0x124, 1 << ((JB + 1) & 3)>(x, x);
+    y = dpp_bank<0x128, 1 << ((JB + 2) & 3)>(y, x);
+    return dpp_bank<0x12C, 1 << ((JB + 3) & 3)>(y, x);
 }
 
-// Cholesky of the lower triangle of an NP x NP LDS tile (NP <= 16, row
-// stride LD) by one wavefront with lane r holding row r: writes L back (zero
-// strict upper part) and 1/L_jj to invd; false on a non-positive or NaN
-// pivot.
-template <int NP, int LD = NP + 1>
-__device__ __forceinline__ bool potrf_small(double* __restrict__ A, double* __restrict__ invd) {
-    static_assert(NP <= 16, "small tiles only");
-    const int lane = threadIdx.x & (kWave - 1);
-    double a[NP];
-#pragma unroll
-    for (int c = 0; c < NP; ++c) a[c] = (lane < NP && c <= lane) ? A[lane * LD + c] : 0.0;
-    double myinv;
-    const bool ok = chol_rows<NP>(a, myinv);
-    if (lane < NP) {
-#pragma unroll
-        for (int c = 0; c < NP; ++c) A[lane * LD + c] = (c <= lane) ? a[c] : 0.0;
-        invd[lane] = myinv;
-    }
-    return ok;
+__device__ __forceinline__ double mma4(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
-// Inverse of the 16 x 16 lower-triangular diagonal tile of L starting at
-// (r0, r0) into Dinv (row stride kLDI): lane c (< 16) forward-substitutes the
-// unit vector e_c.
-template <int LD, class TOut>
-__device__ __forceinline__ void tile_inverse(const double* __restrict__ L, int r0, const double* __restrict__ invd,
-                                             TOut* __restrict__ Dinv) {
-    const int lane = threadIdx.x & 63;
-    const int c = lane & 15;
-    double x[kT];
-#pragma unroll
-    for (int j = 0; j < kT; ++j) x[j] = (j == c) ? 1.0 : 0.0;
-#pragma unroll
-    for (int j = 0; j < kT; ++j) {
-        x[j] *= invd[r0 + j];
-#pragma unroll
-        for (int k = j + 1; k < kT; ++k) x[k] = fma(-L[(r0 + k) * LD + r0 + j], x[j], x[k]);
+// A 16 x 16 tile in four registers: register jb of lane l holds element (row
+// l % 16, column 4 jb + l / 16).  That is both the B operand (4 x 16, its
+// transpose) and the accumulator layout of v_mfma_f64_4x4x4 with four blocks,
+// so the products below chain through registers with no data movement; their
+// A operand, a 4 x 4 block in all four blocks (lane i + 4b + 16k: element
+// (i, k)), is a quad broadcast.
+//
+// Panel step KB: the 4 x 4 diagonal block of the panel's diagonal tile, its
+// Cholesky factor and the inverse M of that on every lane alike (ten values
+// by readlane; the only serial chain: four reciprocal square roots), then for
+// every tile of the panel X = (column block KB) M^T and the rank-4 update of
+// the column blocks right of it.  The same products applied to the identity
+// (E, register a of lane l: element (4a + l / 16, l % 16)) leave the inverse
+// of the diagonal tile.  The chain it replaces held one row per lane and
+// broadcast every multiplier by readlane (16 steps of about 300 cycles a
+// panel), with the diagonal tiles inverted at the end.  Measured, one node of
+// n = 96 alone in its launch: k_tiled_potrf_trsm 35.5 -> 28.4 us in FP64, and
+// with no strips to solve 25.5 -> 17.7; factorization at N = 4096: 1 366 ->
+// 1 239 us (n = 96), 609 -> 551 (n = 64, mixed); N = 1000, n = 32: 216 -> 193.
+template <int TB, int KB>
+__device__ __forceinline__ void panel_step(double (&Q)[4], double (&E)[4], double (&S)[TB][4], double& myinv, bool& ok,
+                                           int lane) {
+    const int r = lane & 15, c = lane >> 4, i = lane & 3;
+    const double q = Q[KB];
+    const double d00 = readlane_d(q, 4 * KB), d10 = readlane_d(q, 4 * KB + 1), d20 = readlane_d(q, 4 * KB + 2),
+                 d30 = readlane_d(q, 4 * KB + 3), d11 = readlane_d(q, 4 * KB + 17), d21 = readlane_d(q, 4 * KB + 18),
+                 d31 = readlane_d(q, 4 * KB + 19), d22 = readlane_d(q, 4 * KB + 34), d32 = readlane_d(q, 4 * KB + 35),
+                 d33 = readlane_d(q, 4 * KB + 51);
+    const double r0 = rsqrt_refined(d00);
+    const double l10 = d10 * r0, l20 = d20 * r0, l30 = d30 * r0;
+    const double p1 = fma(-l10, l10, d11), r1 = rsqrt_refined(p1);
+    const double l21 = fma(-l20, l10, d21) * r1, l31 = fma(-l30, l10, d31) * r1;
+    const double p2 = fma(-l21, l21, fma(-l20, l20, d22)), r2 = rsqrt_refined(p2);
+    const double l32 = fma(-l31, l21, fma(-l30, l20, d32)) * r2;
+    const double p3 = fma(-l32, l32, fma(-l31, l31, fma(-l30, l30, d33))), r3 = rsqrt_refined(p3);
+    ok = ok && d00 > 0.0 && p1 > 0.0 && p2 > 0.0 && p3 > 0.0;
+    // column c of M by forward substitution, then row i of it
+    const double x0 = c == 0 ? r0 : 0.0;
+    const double x1 = fma(-l10, x0, c == 1 ? 1.0 : 0.0) * r1;
+    const double x2 = fma(-l21, x1, fma(-l20, x0, c == 2 ? 1.0 : 0.0)) * r2;
+    const double x3 = fma(-l32, x2, fma(-l31, x1, fma(-l30, x0, c == 3 ? 1.0 : 0.0))) * r3;
+    const double m = i == 0 ? x0 : i == 1 ? x1 : i == 2 ? x2 : x3;
+    if ((r >> 2) == KB) myinv = i == 0 ? r0 : i == 1 ? r1 : i == 2 ? r2 : r3;
+    const double xq = mma4(m, q, 0.0);
+    const double x = r >= 4 * KB + c ? xq : 0.0;
+    Q[KB] = x;
+    double y1 = 0.0, y2 = 0.0, y3 = 0.0;
+    if constexpr (KB < 3) {
+        // the next diagonal block first
+        y1 = -quad_bcast<(KB + 1) & 3>(x);
+        Q[KB + 1] = mma4(y1, x, Q[KB + 1]);
     }
-    if (lane < kT) {
-#pragma unroll
-        for (int j = 0; j < kT; ++j) Dinv[j * kLDI + c] = (TOut)x[j];
+    if constexpr (KB < 2) {
+        y2 = -quad_bcast<(KB + 2) & 3>(x);
+        Q[KB + 2] = mma4(y2, x, Q[KB + 2]);
     }
+    if constexpr (KB < 1) {
+        y3 = -quad_bcast<3>(x);
+        Q[3] = mma4(y3, x, Q[3]);
+    }
+    auto other = [&](double (&t)[4]) {
+        const double z = mma4(m, t[KB], 0.0);
+        t[KB] = z;
+        if constexpr (KB < 3) t[KB + 1] = mma4(y1, z, t[KB + 1]);
+        if constexpr (KB < 2) t[KB + 2] = mma4(y2, z, t[KB + 2]);
+        if constexpr (KB < 1) t[3] = mma4(y3, z, t[3]);
+    };
+    other(E);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) other(S[t]);
 }
 
-
-// Inverse of the 16 x 16 lower-triangular tile T (row stride LD) by one
-// wavefront, written transposed into the tile's strict upper triangle: the
-// strict lower part of the inverse at T[c][j] for c < j (its diagonal is
-// invd).  Lane c (< 16) forward-substitutes e_c; the reads (lower part) and
-// the writes (upper part) never touch the same element.
-template <int LD>
-__device__ __forceinline__ void tile_inverse_upper(double* T, const double* __restrict__ invd) {
-    static_assert(LD > kT, "the tile rows need a padding column");
-    const int lane = threadIdx.x & 63;
-    const int c = lane & 15;
-    double x[kT];
-#pragma unroll
-    for (int j = 0; j < kT; ++j) x[j] = (j == c) ? 1.0 : 0.0;
-#pragma unroll
-    for (int j = 0; j < kT; ++j) {
-        x[j] *= invd[j];
-#pragma unroll
-        for (int k = j + 1; k < kT; ++k) x[k] = fma(-T[k * LD + j], x[j], x[k]);
-    }
-    if (lane < kT) {
-        // entries on or below the diagonal go to the row's padding column
-        // (index kT; LD > kT), so every store is unconditional
-#pragma unroll
-        for (int j = 1; j < kT; ++j) T[c * LD + (j > c ? j : kT)] = x[j];
-    }
-}
-
-// Blocked Cholesky of the lower triangle of an NP x NP LDS tile (row stride
-// LD) by all NW wavefronts of the workgroup (every thread must call it), in
-// 16-column panels.  A panel is factored in registers, one row per lane, by
-// chol_rows: each panel wavefront holds the 16 rows of the diagonal tile in
-// lanes 0..15 (every panel wavefront repeats that part of the chain, so no
-// wavefront waits on another inside a panel) and up to 48 rows below it in
-// lanes 16..63, whose multipliers are the triangular solve L_tp = A_tp
-// L_pp^{-T}.  Look-ahead: the panel wavefronts of panel p+1 apply panel p's
-// update to their own tiles of column p+1 (A_ap -= L_ap L_(p+1)p^T; the
-// diagonal tile into the wavefront's scratch tile when two or more
-// wavefronts share the panel) and factor it at once, while the other
-// wavefronts update the trailing tiles right of column p+1 (matrix cores).
-// The 16 x 16 diagonal tiles are inverted at
-// the end, spread over the wavefronts.  On return: L in the lower triangle
-// (strict upper part of each diagonal tile zeroed, tiles above the diagonal
-// untouched), 1/L_jj in invd, the inverted diagonal tiles in inv[NP/16] (row
-// stride kLDI).  *fail (LDS, 0 on entry) becomes 1 on a non-positive or NaN
-// pivot; the result is then false for every thread.
-// INV: where the inverted diagonal tiles go: 1 the array inv (row stride
-// kLDI), 2 transposed into the strict upper part of each diagonal tile.
-// scr: one 16 x kLDI tile per panel wavefront, needed when a panel has more
-// than 48 rows below its diagonal tile (NP > 64).
+// Blocked Cholesky of the lower triangle of an NP x NP LDS block by all NW
+// wavefronts of the workgroup (every thread must call it), in 16-column
+// panels.  Each panel wavefront holds the diagonal tile (every one repeats
+// its steps, so no wavefront waits on another inside a panel) and up to TB
+// tiles below it.  Look-ahead: the panel wavefronts of panel p+1 apply panel
+// p's update to their own tiles of column p+1 (A_ap -= L_ap L_(p+1)p^T, read
+// from LDS straight into the panel's register layout) and factor it at once,
+// while the other wavefronts update the trailing tiles right of column p+1.
+// The factored diagonal tile and its inverse stay in wavefront 0's registers
+// until the barrier (the other panel wavefronts read the unfactored tile).
+// On return: L in the lower triangle (tiles above the diagonal untouched),
+// 1/L_jj in invd, the inverted diagonal tiles: INV 1 in the array inv (row
+// stride kLDI; the strict upper part of each diagonal tile zero), INV 2
+// transposed in the strict upper part of each diagonal tile.  *fail (LDS, 0 on
+// entry) becomes 1 on a non-positive or NaN pivot; the result is then false
+// for every thread.
 template <int NP, int LD, int NW, class Lay = SquareLds<LD>, int INV = 1>
 __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __restrict__ invd,
-                                              double (*__restrict__ inv)[kT * kLDI], int* fail,
-                                              double (*__restrict__ scr)[kT * kLDI] = nullptr) {
+                                              double (*__restrict__ inv)[kT * kLDI], int* fail) {
     constexpr int NTL = NP / kT;
     constexpr int LT = Lay::LDT;
-    constexpr int kBelow = kWave - kT;  // rows below the diagonal tile per panel wavefront
+    constexpr int TB = NTL <= 2 ? 1 : 2;  // tiles below the diagonal tile per panel wavefront
     // wavefronts that factor panel q
-    constexpr auto pwaves = [](int q) { return NP - (q + 1) * kT <= 0 ? 1 : (NP - (q + 1) * kT + kBelow - 1) / kBelow; };
+    constexpr auto pwaves = [](int q) { return NTL - 1 - q <= 0 ? 1 : (NTL - 1 - q + TB - 1) / TB; };
     static_assert(pwaves(0) <= NW, "too few wavefronts for the first panel");
     static_assert(NTL <= 2 || pwaves(1) < NW, "the trailing update needs a wavefront outside the panel");
-    static_assert(kBelow % kT == 0, "whole tiles per panel wavefront");
-    constexpr int kTilesBelow = kBelow / kT;
-    constexpr bool kShared = pwaves(0) > 1;  // some panel has two or more wavefronts
     const int tid = threadIdx.x;
     const int w = wave_id();
     const int lane = tid & 63;
-    double a[kT];
+    const int r = lane & 15, c = lane >> 4;
+    double Q[4], E[4], S[TB][4];
     double myinv = 1.0;
-    // this wavefront's rows of panel q into registers (lanes 0..15 from the
-    // diagonal tile at D with row stride ldd, the others from the tiles below)
-    auto load_rows = [&](int q, const double* D, int ldd) {
-        const int below = NP - (q + 1) * kT;
-        const int rb = kBelow * w + lane - kT;
-        const bool diag = lane < kT;
-        const bool has = diag || (lane - kT < kBelow && rb < below);
-        // every lane loads from a valid row (a lane without a row reads the
-        // diagonal tile's first row and keeps zeros)
-        const double* row = diag ? D + lane * ldd : has ? Lay::tile(A, q + 1 + rb / kT, q) + (rb % kT) * LT : D;
+    auto load_tile = [&](double (&t)[4], const double* T) {
 #pragma unroll
-        for (int c = 0; c < kT; ++c) {
-            const double x = row[c];
-            a[c] = (has && (!diag || c <= lane)) ? x : 0.0;
-        }
+        for (int j = 0; j < 4; ++j) t[j] = T[r * LT + 4 * j + c];
     };
-    // wavefront 0's rows of the factored diagonal tile q: into the tile
-    // itself when it factored the panel alone (no other wavefront reads that
-    // tile), else into its scratch tile, copied into place after the barrier
-    // (the other panel wavefronts read the unfactored tile before it)
-    auto store_diag = [&](int q) {
-        if (w == 0 && lane < kT) {
-            const bool alone = !kShared || pwaves(q) == 1;
-            double* row = alone ? Lay::tile(A, q, q) + lane * LT : scr[0] + lane * kLDI;
+    // factor panel q (tiles in Q and S): the rows below and 1/L_jj to LDS
+    auto factor = [&](int q) {
+        bool ok = true;
 #pragma unroll
-            for (int c = 0; c < kT; ++c) row[c] = (c <= lane) ? a[c] : 0.0;
-        }
-    };
-    auto place_diag = [&](int q) {
-        if (kShared && pwaves(q) > 1 && w == 0) {
-            wave_lds_sync();
-            for (int e = lane; e < kT * kT; e += kWave)
-                Lay::tile(A, q, q)[(e / kT) * LT + e % kT] = scr[0][(e / kT) * kLDI + e % kT];
-            wave_lds_sync();
-        }
-    };
-    // factor panel q (rows loaded), store the rows below the diagonal tile
-    // and 1/L_jj
-    auto factor_rows = [&](int q) {
-        const bool ok = chol_rows<kT>(a, myinv);
+        for (int j = 0; j < 4; ++j) E[j] = 4 * j + c == r ? 1.0 : 0.0;
+        panel_step<TB, 0>(Q, E, S, myinv, ok, lane);
+        panel_step<TB, 1>(Q, E, S, myinv, ok, lane);
+        panel_step<TB, 2>(Q, E, S, myinv, ok, lane);
+        panel_step<TB, 3>(Q, E, S, myinv, ok, lane);
         if (!ok && lane == 0) *fail = 1;
-        const int below = NP - (q + 1) * kT;
-        const int rb = kBelow * w + lane - kT;
-        if (lane >= kT && lane - kT < kBelow && rb < below) {
-            double* row = Lay::tile(A, q + 1 + rb / kT, q) + (rb % kT) * LT;
 #pragma unroll
-            for (int c = 0; c < kT; ++c) row[c] = a[c];
+        for (int t = 0; t < TB; ++t) {
+            const int ta = q + 1 + TB * w + t;
+            if (ta >= NTL) break;
+            double* T = Lay::tile(A, ta, q);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) T[r * LT + 4 * j + c] = S[t][j];
         }
         if (w == 0 && lane < kT) invd[q * kT + lane] = myinv;
-        store_diag(q);
+    };
+    // wavefront 0's factored diagonal tile q and its inverse into place
+    auto place_diag = [&](int q) {
+        if (w != 0) return;
+        double* T = Lay::tile(A, q, q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            T[r * LT + 4 * j + c] = INV == 2 && r < 4 * j + c ? E[j] : Q[j];
+            if constexpr (INV == 1) inv[q][(4 * j + c) * kLDI + r] = E[j];
+        }
     };
     // A_ab -= L_ap L_bp^T
     auto update = [&](int ta, int tb, int p) {
@@ -347,38 +300,40 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         acc_store_lds<LT>(acc, Tab, 0, 0);
     };
     if (w < pwaves(0)) {
-        load_rows(0, Lay::tile(A, 0, 0), LT);
-        factor_rows(0);
+        load_tile(Q, Lay::tile(A, 0, 0));
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+            if (1 + TB * w + t < NTL) load_tile(S[t], Lay::tile(A, 1 + TB * w + t, 0));
+        factor(0);
     }
     __syncthreads();
     if (*fail) return false;
 #pragma unroll 1
     for (int p = 0; p + 1 < NTL; ++p) {
         const int q = p + 1;
-        const int pw = kShared ? pwaves(q) : 1;
+        const int pw = pwaves(q);
         place_diag(p);
         if (w < pw) {
-            // this wavefront's tiles of column q below the diagonal tile
-#pragma unroll 1
-            for (int t = 0; t < kTilesBelow; ++t) {
-                const int ta = q + 1 + kTilesBelow * w + t;
-                if (ta < NTL) update(ta, q, p);
-            }
-            // the diagonal tile: in place when this wavefront factors the
-            // panel alone, else into its scratch tile
-            d4 acc;
-            acc_load_lds<LT>(acc, Lay::tile(A, q, q), 0, 0);
-            mma_tile<LT, LT, false, true, true>(acc, Lay::tile(A, q, p), 0, 0, Lay::tile(A, q, p), 0, 0, kT);
-            if (!kShared || pw == 1) {
-                acc_store_lds<LT>(acc, Lay::tile(A, q, q), 0, 0);
-                wave_lds_sync();
-                load_rows(q, Lay::tile(A, q, q), LT);
-            } else {
-                acc_store_lds<kLDI>(acc, scr[w], 0, 0);
-                wave_lds_sync();
-                load_rows(q, scr[w], kLDI);
-            }
-            factor_rows(q);
+            // this wavefront's tiles of column q, minus panel p's share
+            double a[4][4];  // -L_qp, column block j, k step s
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) a[j][s] = -Lay::tile(A, q, p)[(4 * j + (lane & 3)) * LT + 4 * s + c];
+            auto updated = [&](double (&t)[4], int ta) {
+                double b[4];
+                load_tile(b, Lay::tile(A, ta, p));
+                load_tile(t, Lay::tile(A, ta, q));
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t[j] = mma4(a[j][s], b[s], t[j]);
+            };
+            updated(Q, q);
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                if (q + 1 + TB * w + t < NTL) updated(S[t], q + 1 + TB * w + t);
+            factor(q);
         } else {
             // the trailing tiles right of column q
             const int m = NTL - 1 - q;
@@ -393,15 +348,8 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
     }
     place_diag(NTL - 1);
     __syncthreads();
-    if (INV == 1)
-        for (int t = w; t < NTL; t += NW) tile_inverse<LT, double>(Lay::tile(A, t, t), 0, invd + t * kT, inv[t]);
-    else
-        for (int t = w; t < NTL; t += NW) tile_inverse_upper<LT>(Lay::tile(A, t, t), invd + t * kT);
-    __syncthreads();
     return true;
 }
-
-
 
 // L_ii (lower triangle of the NP x NP LDS block src, row stride NP+1) and its
 // inverted diagonal tiles inv (row stride kLDI) to an n x n global block as
