@@ -246,7 +246,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
                                               double (*__restrict__ inv)[kT * kLDI], int* fail) {
     constexpr int NTL = NP / kT;
     constexpr int LT = Lay::LDT;
-    constexpr int TB = NTL <= 2 ? 1 : 2;  // tiles below the diagonal tile per panel wavefront
+    // tiles below the diagonal tile per panel wavefront (one where that leaves
+    // wavefronts for the trailing update, and at n = 64, whose register budget
+    // holds no second one)
+    constexpr int TB = NTL <= 4 || NW >= 2 * (NTL - 1) ? 1 : 2;
     // wavefronts that factor panel q
     constexpr auto pwaves = [](int q) { return NTL - 1 - q <= 0 ? 1 : (NTL - 1 - q + TB - 1) / TB; };
     static_assert(pwaves(0) <= NW, "too few wavefronts for the first panel");
