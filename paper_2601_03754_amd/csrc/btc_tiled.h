@@ -23,6 +23,8 @@
 // accumulation).
 #pragma once
 
+#include <type_traits>
+
 #include "btc_device.h"
 #include "btc_kernels.h"
 #include "btc_tiles.h"
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(256) void k_tiled_update(Launch<FactorDesc> L) {
             y.load(T2, n, 32 * b, true, tid, k0);
         }
     };
-    typename Pr::Acc acc = {}, acc1 = {};
+    typename Pr::Acc acc = {};
     const int i = lane & 15, q = lane >> 4;
     // a phase's panels into LDS
     auto stage = [&](int ph, const Pan& ca, const Pan& cb) {
@@ -526,28 +528,20 @@ __global__ __launch_bounds__(256) void k_tiled_update(Launch<FactorDesc> L) {
                 // R T (B[k][c] = T[k][c])
                 mma_tile_bf16<LDR, LDP, false, false, false>(acc, pa, 16 * sr, 0, pb, 16 * sc, 0, KH);
         } else {
-            // two independent accumulation chains (hide the matrix-core latency)
-#pragma unroll 4
-            for (int k = 0; k < KH; k += 8) {
-                F a0, a1, b0, b1;
+            // one accumulation chain per product, k ascending (a dependent
+            // matrix-core instruction issues as fast as an independent one);
+            // k_tiled_update_node accumulates in the same order
+#pragma unroll 8
+            for (int k = 0; k < KH; k += 4) {
+                F a0, b0;
                 if (second) {
                     a0 = pa[(k + q) * LDP + 16 * sr + i];
-                    a1 = pa[(k + 4 + q) * LDP + 16 * sr + i];
                     b0 = pb[(k + q) * LDP + 16 * sc + i];
-                    b1 = pb[(k + 4 + q) * LDP + 16 * sc + i];
                 } else {
                     a0 = pa[(16 * sr + i) * LDR + k + q];
-                    a1 = pa[(16 * sr + i) * LDR + k + 4 + q];
                     b0 = sep ? pb[(16 * sc + i) * LDR + k + q] : pb[(k + q) * LDP + 16 * sc + i];
-                    b1 = sep ? pb[(16 * sc + i) * LDR + k + 4 + q] : pb[(k + 4 + q) * LDP + 16 * sc + i];
                 }
                 acc = Pr::mma(a0, b0, acc);
-                acc1 = Pr::mma(a1, b1, acc1);
-            }
-            if (ph % KS == KS - 1) {
-                // end of a product: fold its second chain
-                acc += acc1;
-                acc1 = {};
             }
         }
     };
@@ -601,6 +595,184 @@ __global__ __launch_bounds__(256) void k_tiled_update(Launch<FactorDesc> L) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// K4 for launches of many nodes: one workgroup of eight wavefronts computes
+// every product of a node, so that R, T and the right neighbour's T' come from
+// the L2 once per node, in ranges of KC along k through LDS (the next range in
+// flight in registers).  With one workgroup per 32 x 32 tile every panel is
+// read by each tile that needs it, 1.03 MB per node at n = 96 in FP64 against
+// 221 KB, and the L2 bounds the kernel.  The 16 x 16 tiles are dealt to the
+// wavefronts, those of the separator update from the first wavefront on, those
+// of the fill from the last on, so that every matrix core has the same number
+// of products to a tile in both passes (quadrants per wavefront left them
+// unevenly loaded, and the second product to three of eight wavefronts: 222 us
+// where this takes 188).  Every tile reads its own operands: with two LDS
+// reads per matrix instruction the LDS is half busy.  The order of
+// accumulation is k_tiled_update's: R R^T over all k, then T'^T T'.  Measured,
+// one workgroup per tile -> this, for 2048 nodes: n = 96 266 -> 188 us (FP64,
+// 45 TFLOP/s) and 150 -> 104 (mixed), n = 128 540 -> 413 and 313 -> 216, n = 64
+// 101 -> 72 and 57 -> 44.
+template <int NP, bool MIXED>
+__global__ __launch_bounds__(512, NP <= 96 ? 4 : 2) void k_tiled_update_node(Launch<FactorDesc> L) {
+    using Pr = Prec<MIXED>;
+    using F = typename Pr::F;
+    using Acc = typename Pr::Acc;
+    constexpr int NT = 512;
+    constexpr int KC = MIXED ? 32 : 16, NC = NP / KC, HB = NP / 32;
+    constexpr int LDR = KC + 1, LDT = NP + 16;  // conflict-free operand reads
+    constexpr int TO = NP * LDR;                // T range after the R range
+    constexpr int PER = NP * KC / NT;
+    static_assert(PER * NT == NP * KC, "threads divide a range");
+    // the second product takes T' in two halves: with the fill's accumulators
+    // stored before it, registers for that are free, and a quarter of the
+    // ranges have to be waited for
+    constexpr int KC2 = NP / 2, XR2 = KC2 / 16, PER2 = XR2 * HB;
+    __shared__ F sm[TO + KC * LDT > KC2 * LDT ? TO + KC * LDT : KC2 * LDT];
+    FactorDesc P;
+    int lvl;
+    int64_t kk;
+    // T' is the next node's T: consecutive nodes share an XCD's L2
+    fetch_item_at(L, xcd_local_block(), P, lvl, kk);
+    if (*P.info != kInfoOk) return;
+    const Node d = node_of(P, lvl, kk);
+    if (!d.has_r) return;
+    const int tid = threadIdx.x, w = wave_id(), lane = tid & 63;
+    const int n = d.n, i = lane & 15, q = lane >> 4;
+    const bool eager = (P.flags & kFactorEagerT) && d.i + 2 * d.s <= d.N;
+    const int bytes = n * n * (int)sizeof(F);
+    const __amdgpu_buffer_rsrc_t rr = nn_rsrc(Pr::Rf(P) + (size_t)d.pi * d.nn, n);
+    const __amdgpu_buffer_rsrc_t rt = block_rsrc(Pr::Tf(P) + (size_t)d.pi * d.nn, d.has_l ? bytes : 0);
+    const __amdgpu_buffer_rsrc_t ru = block_rsrc(
+        Pr::Tf(P) + (size_t)(eager ? perm_pos(d.N, lvl, d.i + 2 * d.s) : d.pi) * d.nn, eager ? bytes : 0);
+    // R: rows tid / KC + (NT / KC) x, column tid % KC of the range; T, T': row
+    // (tid / 32) + 16 (x % XR) of the range, column tid % 32 + 32 (x / XR).
+    // Rows past n lie past the resources' ends.
+    F gr[PER], gt[PER > PER2 ? PER : PER2];
+    constexpr int SZ = (int)sizeof(F), XR = KC / 16;
+    static_assert(PER == XR * HB, "whole rows of 32 per pass");
+    const int rrow = tid / KC, rcol = tid % KC, trow = tid >> 5, tcol = tid & 31;
+    // T or T': rows k0 + trow + 16 (x % xr), columns tcol + 32 (x / xr)
+    auto fetch_t = [&](const __amdgpu_buffer_rsrc_t rs, int k0, auto xr) {
+        constexpr int X = decltype(xr)::value;
+#pragma unroll
+        for (int x = 0; x < X * HB; ++x) {
+            const int to = tcol + 32 * (x / X) < n ? (trow * n + tcol) * SZ + 32 * (x / X) * SZ : kOob;
+            buf_ld(gt[x], rs, to, (k0 + 16 * (x % X)) * n * SZ);
+        }
+    };
+    auto put_t = [&](F* dst, auto xr) {
+        constexpr int X = decltype(xr)::value;
+#pragma unroll
+        for (int x = 0; x < X * HB; ++x) dst[(trow + 16 * (x % X)) * LDT + tcol + 32 * (x / X)] = gt[x];
+    };
+    using X1 = std::integral_constant<int, XR>;
+    using X2 = std::integral_constant<int, XR2>;
+    auto fetch = [&](int ch) {
+        const int k0 = KC * ch, ro = k0 + rcol < n ? (rrow * n + k0 + rcol) * SZ : kOob;
+#pragma unroll
+        for (int x = 0; x < PER; ++x) buf_ld(gr[x], rr, ro, x * (NT / KC) * n * SZ);
+        fetch_t(rt, k0, X1{});
+    };
+    // tiles of this wavefront
+    constexpr int T16 = NP / 16, NSEP = T16 * (T16 + 1) / 2, NFIL = T16 * T16;
+    constexpr int MS = (NSEP + 7) / 8, MF = (NFIL + 7) / 8;
+    int sa[MS], sb[MS], fa[MF], fb[MF];
+    Acc as[MS], af[MF];
+#pragma unroll
+    for (int t = 0; t < MS; ++t) {
+        as[t] = Acc{};
+        tri_tile(w + 8 * t < NSEP ? w + 8 * t : 0, sa[t], sb[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < MF; ++t) {
+        af[t] = Acc{};
+        const int id = 7 - w + 8 * t;
+        fa[t] = id / T16;
+        fb[t] = id % T16;
+    }
+    auto has_s = [&](int t) { return 8 * t + 7 < NSEP || w + 8 * t < NSEP; };
+    auto has_f = [&](int t) { return 8 * t + 7 < NFIL || 7 - w + 8 * t < NFIL; };
+    // operands: row r of R or column c of T, T' in tile t, step k
+    const int rbase = i * LDR + q, cbase = q * LDT + i;
+    fetch(0);
+#pragma unroll 1
+    for (int ch = 0; ch < NC; ++ch) {
+        if (ch) __syncthreads();  // the previous range has been read
+#pragma unroll
+        for (int x = 0; x < PER; ++x) sm[(rrow + (NT / KC) * x) * LDR + rcol] = gr[x];
+        put_t(sm + TO, X1{});
+        if (ch + 1 < NC)
+            fetch(ch + 1);
+        else
+            fetch_t(ru, 0, X2{});
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < MS; ++t) {
+            if (!has_s(t)) continue;
+            const int oa = rbase + 16 * LDR * sa[t], ob = rbase + 16 * LDR * sb[t];
+#pragma unroll
+            for (int k = 0; k < KC; k += 4) as[t] = Pr::mma(sm[oa + k], sm[ob + k], as[t]);
+        }
+        if (!d.has_l) continue;
+#pragma unroll
+        for (int t = 0; t < MF; ++t) {
+            if (!has_f(t)) continue;
+            const int oa = rbase + 16 * LDR * fa[t], ob = TO + cbase + 16 * fb[t];
+#pragma unroll
+            for (int k = 0; k < KC; k += 4) af[t] = Pr::mma(sm[oa + k], sm[ob + k * LDT], af[t]);
+        }
+    }
+    // offsets of the lane's elements of a tile (kOob: absent)
+    auto offset = [&](int a, int b, int v, int size, bool have) {
+        const int r = 16 * a + Pr::row(v, lane), c = 16 * b + i;
+        return have && r < n && c < n ? (r * n + c) * size : kOob;
+    };
+    if (d.has_l) {
+        const int64_t lft = d.i - d.s, rgt = d.i + d.s;
+        F* dst = (((lft >> (lvl + 1)) & 1) != 0) ? Pr::Rf(P) + (size_t)perm_pos(d.N, lvl + 1, lft) * d.nn
+                                                 : Pr::Tf(P) + (size_t)perm_pos(d.N, lvl + 1, rgt) * d.nn;
+        const __amdgpu_buffer_rsrc_t rf = nn_rsrc(dst, n);
+#pragma unroll
+        for (int t = 0; t < MF; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) buf_st(-af[t][v], rf, offset(fa[t], fb[t], v, SZ, has_f(t)));
+    }
+    if (eager) {
+#pragma unroll 1
+        for (int c = 0; c < 2; ++c) {
+            __syncthreads();  // the previous range has been read
+            put_t(sm, X2{});
+            if (c == 0) fetch_t(ru, KC2, X2{});
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < MS; ++t) {
+                if (!has_s(t)) continue;
+                const int oa = cbase + 16 * sa[t], ob = cbase + 16 * sb[t];
+#pragma unroll
+                for (int k = 0; k < KC2; k += 4) as[t] = Pr::mma(sm[oa + k * LDT], sm[ob + k * LDT], as[t]);
+            }
+        }
+    }
+    const double* src = (lvl == 0) ? P.A_diag + (size_t)(d.i + d.s - 1) * d.nn : P.Ld + (size_t)d.pr * d.nn;
+    const __amdgpu_buffer_rsrc_t rs = nn_rsrc(src, n), rd = nn_rsrc(P.Ld + (size_t)d.pr * d.nn, n);
+    double x[MS][4];
+#pragma unroll
+    for (int t = 0; t < MS; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) buf_ld(x[t][v], rs, offset(sa[t], sb[t], v, 8, has_s(t)));
+#pragma unroll
+    for (int t = 0; t < MS; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            buf_st(x[t][v] - (double)as[t][v], rd, offset(sa[t], sb[t], v, 8, has_s(t)));
+}
+
+// K4 by node from this many nodes on; below, one workgroup per tile spreads a
+// node over more compute units.  Measured, by tile against by node: 256 nodes
+// 36.0 / 30.4 us (n = 96, FP64), 15.6 / 12.9 (n = 64), 77 / 58 (n = 128); 128
+// nodes 23.0 / 26.4, 10.0 / 11.2, 43 / 48.
+constexpr int64_t kUpdateNodeItems = 192;
+
 // part 0: the whole level step; 1, 2, 3: only K1, K2, K4 (for per-kernel
 // timing; launched in that order they make up the step)
 template <int NP, bool MIXED, bool BF16>
@@ -620,6 +792,12 @@ hipError_t launch_tiled_np(const Launch<FactorDesc>& p, int part, bool deferred,
         }
         if (!done)
             hipLaunchKernelGGL((k_tiled_potrf_trsm<NP, MIXED>), dim3(g), dim3(k2_waves<NP>() * kWave), 0, st, p);
+    }
+    if constexpr (NP >= 64 && !BF16) {
+        if ((part == 0 || part == 3) && items >= kUpdateNodeItems) {
+            hipLaunchKernelGGL((k_tiled_update_node<NP, MIXED>), dim3(g), dim3(512), 0, st, p);
+            return hipGetLastError();
+        }
     }
     if (part == 0 || part == 3)
         hipLaunchKernelGGL((k_tiled_update<NP, MIXED, BF16>), dim3(g * (Cfg::NTRI32 + Cfg::W32 * Cfg::W32)), dim3(256),
