@@ -428,11 +428,12 @@ BTC_API void btc_graph_destroy(btc_graph g);
  * the factor at n 33..64 and 0 everywhere else),
  * keyed by operation, precision, block size n (through its padded size) and
  * level (bucket: level 0, levels >= 1):
- *   BTC_OP_FACTOR, BTC_FP64, n 9..32: 0 matrix-core kernel, 1 vector-ALU
- *     kernel, and for n 17..32 also 2 the tile-parallel level step; mixed
- *     precisions, n 17..32, and any precision, n 33..64: 0 one workgroup per
- *     node, 1 the tile-parallel level step (different rounding orders:
- *     results change at round-off level when the choice changes)
+ *   BTC_OP_FACTOR (different rounding orders: results change at round-off
+ *     level when the choice changes): 0 one workgroup per node; BTC_FP64,
+ *     n 9..32: 1 vector-ALU kernel, and for n 17..32 also 2 the tile-parallel
+ *     level step; mixed precisions, n 17..32: 1 the tile-parallel level step;
+ *     any precision, n 33..64: 0 the tile-parallel level step, 1 one workgroup
+ *     per node
  *   BTC_OP_FORWARD / BACKWARD (level ignored): 0 with more than four
  *     right-hand sides, 8 or 16 columns per pass over the factor (FP64), 1
  *     four; BTC_OP_RESIDUAL (nrhs > 1; level ignored): 0 four columns per

@@ -62,12 +62,12 @@ __device__ __forceinline__ void buf_ld(float& x, __amdgpu_buffer_rsrc_t r, int o
     x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, AUX));
 }
 template <int AUX = 0>
-__device__ __forceinline__ void buf_st(double x, __amdgpu_buffer_rsrc_t r, int off) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x), r, off, 0, AUX);
+__device__ __forceinline__ void buf_st(double x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x), r, off, soff, AUX);
 }
 template <int AUX = 0>
-__device__ __forceinline__ void buf_st(float x, __amdgpu_buffer_rsrc_t r, int off) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, off, 0, AUX);
+__device__ __forceinline__ void buf_st(float x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, off, soff, AUX);
 }
 // Element (r, c) of an n x n row-major block of S: byte offset, or kOob
 // when not `ok`.
@@ -99,28 +99,11 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Stage an n x n row-major block from global memory into an NP x NP LDS tile
-// (row stride NP+1).  lower_only: read only c <= r (the upper part becomes 0).
-// Padding: pad_diag on the diagonal, 0 elsewhere.  Threads [t0, t0+nt) take
-// part; consecutive threads read consecutive columns of a row.
-template <int NP>
-__device__ __forceinline__ void lds_load(double* __restrict__ dst, const double* __restrict__ src,
-                                         int n, bool lower_only, double pad_diag, int t, int nt) {
-    for (int idx = t; idx < NP * NP; idx += nt) {
-        const int r = idx / NP, c = idx % NP;
-        double v;
-        if (r < n && c < n)
-            v = (!lower_only || c <= r) ? src[(size_t)r * n + c] : 0.0;
-        else
-            v = (r == c) ? pad_diag : 0.0;
-        dst[r * (NP + 1) + c] = v;
-    }
-}
-
 // Batched staging of one n x n row-major block by a fixed group of NTH
 // threads: fetch() issues all of the thread's global loads into registers (so
 // that every load of several blocks is in flight at once), put() writes them
-// to the padded LDS tile.  Same element mapping and padding as lds_load.
+// to the padded LDS tile (row stride NP+1).  lower_only: read only c <= r (the
+// upper part becomes 0).  Padding: pad_diag on the diagonal, 0 elsewhere.
 template <int NP, int NTH, class V = double>
 struct Stage {
     static constexpr int PER = (NP * NP + NTH - 1) / NTH;
@@ -146,16 +129,6 @@ struct Stage {
         }
     }
 };
-
-// Store the leading n x n part of an LDS tile of type S as type D.
-template <int NP, class D, class S>
-__device__ __forceinline__ void lds_store_as(D* __restrict__ dst, const S* __restrict__ src, int n, bool lower_only,
-                                             int t, int nt) {
-    for (int idx = t; idx < NP * NP; idx += nt) {
-        const int r = idx / NP, c = idx % NP;
-        if (r < n && c < n) dst[(size_t)r * n + c] = (D)((!lower_only || c <= r) ? src[r * (NP + 1) + c] : S(0));
-    }
-}
 
 // Write the leading n x n part of an LDS tile to global memory
 // (lower_only: the strict upper triangle is written as 0).

@@ -33,15 +33,15 @@ struct Launch {
 
 template <class D>
 __device__ __forceinline__ void fetch_item_at(const Launch<D>& P, int64_t idx, D& d, int& level, int64_t& k) {
+    // (the launch's own descriptor first: all argument loads go out together)
+    d = P.single;
+    level = P.level;
+    k = idx;
     if (P.items) {
         const WorkItem it = P.items[idx];
         d = P.descs[it.inst];
         level = it.level;
         k = it.k;
-    } else {
-        d = P.single;
-        level = P.level;
-        k = idx;
     }
 }
 

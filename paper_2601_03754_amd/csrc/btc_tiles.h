@@ -76,38 +76,9 @@ __device__ __forceinline__ void acc_store_lds(const d4& acc, double* __restrict_
     for (int v = 0; v < 4; ++v) S[(r0 + acc_r(v, lane)) * LD + c0 + acc_c(lane)] = acc[v];
 }
 
-// Load a tile of an n x n global block (lower triangle only, identity padding).
-__device__ __forceinline__ void acc_load_sym(d4& acc, const double* __restrict__ src, int n, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int r = r0 + acc_r(v, lane), c = c0 + acc_c(lane);
-        double x = (r == c) ? 1.0 : 0.0;
-        if (r < n && c < n && c <= r) x = src[(size_t)r * n + c];
-        acc[v] = x;
-    }
-}
-
-__device__ __forceinline__ void acc_store_global(const d4& acc, double* __restrict__ dst, int n, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int r = r0 + acc_r(v, lane), c = c0 + acc_c(lane);
-        if (r < n && c < n) dst[(size_t)r * n + c] = acc[v];
-    }
-}
-
-// LDS layouts of the lower triangle of an NP x NP block, addressed by
-// 16 x 16 tiles; tile (a, b) has row stride LDT.
-// Row-major square layout, row stride LD.
-template <int LD>
-struct SquareLds {
-    static constexpr int LDT = LD;
-    template <class T>
-    __device__ static T* tile(T* A, int a, int b) { return A + (kT * a) * LD + kT * b; }
-};
-// Lower tiles only (about half the LDS): tile (a, b), b <= a, at position
-// a(a+1)/2 + b, rows of kLDI elements (conflict-free 16 x 4 operand reads).
+// LDS layout of the lower triangle of an NP x NP block: its 16 x 16 tiles
+// (a, b), b <= a, at position a(a+1)/2 + b, rows of kLDI elements (conflict-free
+// 16 x 4 operand reads).
 struct PackedLds {
     static constexpr int LDT = kLDI;
     static constexpr int kTile = kT * kLDI;
@@ -172,9 +143,13 @@ __device__ __forceinline__ double mma4(double a, double b, double c) {
 // n = 96 alone in its launch: k_tiled_potrf_trsm 35.5 -> 28.4 us in FP64, and
 // with no strips to solve 25.5 -> 17.7; factorization at N = 4096: 1 366 ->
 // 1 239 us (n = 96), 609 -> 551 (n = 64, mixed); N = 1000, n = 32: 216 -> 193.
-template <int TB, int KB>
-__device__ __forceinline__ void panel_step(double (&Q)[4], double (&E)[4], double (&S)[TB][4], double& myinv, bool& ok,
-                                           int lane) {
+// (panel_diag is the chain, panel_rest what hangs on it.)
+struct PanelStep {
+    double m;   // lane i + 4b + 16k: M[i][k]
+    double y1, y2, y3;  // minus the factored column's blocks below the diagonal, as A operands
+};
+template <int KB, class V>
+__device__ __forceinline__ PanelStep panel_diag(V& Q, double& myinv, bool& ok, int lane) {
     const int r = lane & 15, c = lane >> 4, i = lane & 3;
     const double q = Q[KB];
     const double d00 = readlane_d(q, 4 * KB), d10 = readlane_d(q, 4 * KB + 1), d20 = readlane_d(q, 4 * KB + 2),
@@ -194,37 +169,41 @@ __device__ __forceinline__ void panel_step(double (&Q)[4], double (&E)[4], doubl
     const double x1 = fma(-l10, x0, c == 1 ? 1.0 : 0.0) * r1;
     const double x2 = fma(-l21, x1, fma(-l20, x0, c == 2 ? 1.0 : 0.0)) * r2;
     const double x3 = fma(-l32, x2, fma(-l31, x1, fma(-l30, x0, c == 3 ? 1.0 : 0.0))) * r3;
-    const double m = i == 0 ? x0 : i == 1 ? x1 : i == 2 ? x2 : x3;
+    PanelStep s{};
+    s.m = i == 0 ? x0 : i == 1 ? x1 : i == 2 ? x2 : x3;
     if ((r >> 2) == KB) myinv = i == 0 ? r0 : i == 1 ? r1 : i == 2 ? r2 : r3;
-    const double xq = mma4(m, q, 0.0);
+    const double xq = mma4(s.m, q, 0.0);
     const double x = r >= 4 * KB + c ? xq : 0.0;
     Q[KB] = x;
-    double y1 = 0.0, y2 = 0.0, y3 = 0.0;
     if constexpr (KB < 3) {
         // the next diagonal block first
-        y1 = -quad_bcast<(KB + 1) & 3>(x);
-        Q[KB + 1] = mma4(y1, x, Q[KB + 1]);
+        s.y1 = -quad_bcast<(KB + 1) & 3>(x);
+        Q[KB + 1] = mma4(s.y1, x, Q[KB + 1]);
     }
     if constexpr (KB < 2) {
-        y2 = -quad_bcast<(KB + 2) & 3>(x);
-        Q[KB + 2] = mma4(y2, x, Q[KB + 2]);
+        s.y2 = -quad_bcast<(KB + 2) & 3>(x);
+        Q[KB + 2] = mma4(s.y2, x, Q[KB + 2]);
     }
     if constexpr (KB < 1) {
-        y3 = -quad_bcast<3>(x);
-        Q[3] = mma4(y3, x, Q[3]);
+        s.y3 = -quad_bcast<3>(x);
+        Q[3] = mma4(s.y3, x, Q[3]);
     }
-    auto other = [&](double (&t)[4]) {
-        const double z = mma4(m, t[KB], 0.0);
-        t[KB] = z;
-        if constexpr (KB < 3) t[KB + 1] = mma4(y1, z, t[KB + 1]);
-        if constexpr (KB < 2) t[KB + 2] = mma4(y2, z, t[KB + 2]);
-        if constexpr (KB < 1) t[3] = mma4(y3, z, t[3]);
-    };
-    other(E);
-#pragma unroll
-    for (int t = 0; t < TB; ++t) other(S[t]);
+    return s;
 }
-
+template <int KB, class V>
+__device__ __forceinline__ void panel_apply(V& t, const PanelStep& s) {
+    const double z = mma4(s.m, t[KB], 0.0);
+    t[KB] = z;
+    if constexpr (KB < 3) t[KB + 1] = mma4(s.y1, z, t[KB + 1]);
+    if constexpr (KB < 2) t[KB + 2] = mma4(s.y2, z, t[KB + 2]);
+    if constexpr (KB < 1) t[3] = mma4(s.y3, z, t[3]);
+}
+template <int TB, int KB, class V>
+__device__ __forceinline__ void panel_rest(V& E, V (&S)[TB], const PanelStep& s) {
+    panel_apply<KB>(E, s);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) panel_apply<KB>(S[t], s);
+}
 // Blocked Cholesky of the lower triangle of an NP x NP LDS block by all NW
 // wavefronts of the workgroup (every thread must call it), in 16-column
 // panels.  Each panel wavefront holds the diagonal tile (every one repeats
@@ -236,14 +215,12 @@ __device__ __forceinline__ void panel_step(double (&Q)[4], double (&E)[4], doubl
 // The factored diagonal tile and its inverse stay in wavefront 0's registers
 // until the barrier (the other panel wavefronts read the unfactored tile).
 // On return: L in the lower triangle (tiles above the diagonal untouched),
-// 1/L_jj in invd, the inverted diagonal tiles: INV 1 in the array inv (row
-// stride kLDI; the strict upper part of each diagonal tile zero), INV 2
-// transposed in the strict upper part of each diagonal tile.  *fail (LDS, 0 on
-// entry) becomes 1 on a non-positive or NaN pivot; the result is then false
-// for every thread.
-template <int NP, int LD, int NW, class Lay = SquareLds<LD>, int INV = 1>
-__device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __restrict__ invd,
-                                              double (*__restrict__ inv)[kT * kLDI], int* fail) {
+// 1/L_jj in invd, the inverse of each diagonal tile transposed in its strict
+// upper part.  *fail (LDS, 0 on entry) becomes 1 on a non-positive or NaN
+// pivot; the result is then false for every thread.
+template <int NP, int NW>
+__device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __restrict__ invd, int* fail) {
+    using Lay = PackedLds;
     constexpr int NTL = NP / kT;
     constexpr int LT = Lay::LDT;
     // tiles below the diagonal tile per panel wavefront (one where that leaves
@@ -269,10 +246,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         bool ok = true;
 #pragma unroll
         for (int j = 0; j < 4; ++j) E[j] = 4 * j + c == r ? 1.0 : 0.0;
-        panel_step<TB, 0>(Q, E, S, myinv, ok, lane);
-        panel_step<TB, 1>(Q, E, S, myinv, ok, lane);
-        panel_step<TB, 2>(Q, E, S, myinv, ok, lane);
-        panel_step<TB, 3>(Q, E, S, myinv, ok, lane);
+        panel_rest<TB, 0>(E, S, panel_diag<0>(Q, myinv, ok, lane));
+        panel_rest<TB, 1>(E, S, panel_diag<1>(Q, myinv, ok, lane));
+        panel_rest<TB, 2>(E, S, panel_diag<2>(Q, myinv, ok, lane));
+        panel_rest<TB, 3>(E, S, panel_diag<3>(Q, myinv, ok, lane));
         if (!ok && lane == 0) *fail = 1;
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
@@ -290,8 +267,7 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         double* T = Lay::tile(A, q, q);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            T[r * LT + 4 * j + c] = INV == 2 && r < 4 * j + c ? E[j] : Q[j];
-            if constexpr (INV == 1) inv[q][(4 * j + c) * kLDI + r] = E[j];
+            T[r * LT + 4 * j + c] = r < 4 * j + c ? E[j] : Q[j];
         }
     };
     // A_ab -= L_ap L_bp^T
@@ -354,40 +330,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
     return true;
 }
 
-// L_ii (lower triangle of the NP x NP LDS block src, row stride NP+1) and its
-// inverted diagonal tiles inv (row stride kLDI) to an n x n global block as
-// type D: L below and on the diagonal, each tile's inverse transposed in the
-// strict upper part of its tile.
-template <int NP, class D, class S>
-__device__ __forceinline__ void store_factor_lds(D* __restrict__ dst, const S* __restrict__ src,
-                                                 const S (*__restrict__ inv)[kT * kLDI], int n, int t, int nt) {
-    for (int idx = t; idx < NP * NP; idx += nt) {
-        const int r = idx / NP, c = idx % NP;
-        if (r < n && c < n && c / kT <= r / kT)
-            dst[(size_t)r * n + c] = (D)(c <= r ? src[r * (NP + 1) + c] : inv[r / kT][(c % kT) * kLDI + r % kT]);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // FP32 tiles
 
 __device__ __forceinline__ int acc32_r(int v, int lane) { return 4 * (lane >> 4) + v; }
-
-// acc += (NEG ? -1 : 1) * sum_{kk<K} opA[ra+i][ka+kk] * opB[kb+kk][cb+j] in FP32
-template <int LDA, int LDB, bool TA, bool TB, bool NEG>
-__device__ __forceinline__ void mma_tile32(f4& acc, const float* __restrict__ A, int ra, int ka,
-                                           const float* __restrict__ B, int cb, int kb, int K) {
-    const int lane = threadIdx.x & 63;
-    const int i = lane & 15, q = lane >> 4;
-#pragma unroll 4
-    for (int kk = 0; kk < K; kk += 4) {
-        const int k1 = ka + kk + q, k2 = kb + kk + q;
-        float a = TA ? A[k1 * LDA + ra + i] : A[(ra + i) * LDA + k1];
-        const float b = TB ? B[(cb + i) * LDB + k2] : B[k2 * LDB + cb + i];
-        if (NEG) a = -a;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-    }
-}
 
 // acc += (NEG ? -1 : 1) * sum_{kk<K} opA[ra+i][ka+kk] * opB[kb+kk][cb+j] with the
 // operands rounded to BF16 (round to nearest even) and FP32 accumulation
@@ -413,48 +359,6 @@ __device__ __forceinline__ void mma_tile_bf16(f4& acc, const float* __restrict__
             b[e] = (__bf16)bv;
         }
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-    }
-}
-
-// Schur / fill product of the mixed kernels: FP32 or BF16 operands.
-template <bool BF16, int LDA, int LDB, bool TA, bool TB, bool NEG>
-__device__ __forceinline__ void mma_prod(f4& acc, const float* __restrict__ A, int ra, int ka,
-                                         const float* __restrict__ B, int cb, int kb, int K) {
-    if constexpr (BF16)
-        mma_tile_bf16<LDA, LDB, TA, TB, NEG>(acc, A, ra, ka, B, cb, kb, K);
-    else
-        mma_tile32<LDA, LDB, TA, TB, NEG>(acc, A, ra, ka, B, cb, kb, K);
-}
-
-template <int LD>
-__device__ __forceinline__ void acc32_load_lds(f4& acc, const float* __restrict__ S, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = S[(r0 + acc32_r(v, lane)) * LD + c0 + acc_c(lane)];
-}
-
-template <int LD>
-__device__ __forceinline__ void acc32_store_lds(const f4& acc, float* __restrict__ S, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) S[(r0 + acc32_r(v, lane)) * LD + c0 + acc_c(lane)] = acc[v];
-}
-
-// FP64 LDS tile -= FP32 accumulator (Schur update of an FP64 block by a
-// product formed in lower precision)
-template <int LD>
-__device__ __forceinline__ void acc32_sub_from_lds64(const f4& acc, double* __restrict__ S, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) S[(r0 + acc32_r(v, lane)) * LD + c0 + acc_c(lane)] -= (double)acc[v];
-}
-
-__device__ __forceinline__ void acc32_store_global(const f4& acc, float* __restrict__ dst, int n, int r0, int c0) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int r = r0 + acc32_r(v, lane), c = c0 + acc_c(lane);
-        if (r < n && c < n) dst[(size_t)r * n + c] = acc[v];
     }
 }
 

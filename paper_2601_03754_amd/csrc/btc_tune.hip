@@ -3,10 +3,11 @@
 // that times the candidates on a caller's instance.
 //
 // Tunable choices:
-//   factor, FP64, padded size 16 or 32: 0 = matrix-core kernel, 1 = vector-ALU
-//     kernel; padded size 64, every precision: 0 = one workgroup per node,
-//     1 = the tile-parallel step (different rounding orders; level bucket 0 =
-//     level 0, which has no deferred updates, 1 = the other levels)
+//   factor (different rounding orders; level bucket 0 = level 0, which has no
+//     deferred updates, 1 = the other levels): 0 = one workgroup per node on
+//     the matrix cores; FP64, padded size 16 or 32: 1 = the vector-ALU kernel;
+//     FP64 32: 2, mixed 32: 1 = the tile-parallel step; padded size 64, every
+//     precision: 0 = the tile-parallel step, 1 = one workgroup per node
 //   forward / backward sweep and residual, nrhs > 1: 0 = four right-hand-side
 //     columns per dependency chain group, 1 = one (bitwise identical results)
 #include <hip/hip_runtime.h>
@@ -84,9 +85,10 @@ void save_tune_cache() {
     (void)rename(tmp.c_str(), path);
 }
 
-// Variant of a key nobody has set: measured on MI355X, the tile-parallel
-// step beats the one-workgroup-per-node kernel at padded size 64 (it needs
-// less LDS per workgroup, so several nodes share a compute unit); 0 elsewhere.
+// Variant of a key nobody has set: the one-workgroup-per-node step, which is
+// variant 1 at padded size 64 (measured, N = 4096, factorization, node / tile-
+// parallel step: n = 64 FP64 534 / 547 us, mixed 448 / 523, BF16 458 / 533;
+// n = 48 FP64 406 / 506, mixed 355 / 494).
 int default_variant(int op, int np) { return (op == BTC_OP_FACTOR && np == 64) ? 1 : 0; }
 
 int tune_variant(int op, int kind, int np, int bucket) {
