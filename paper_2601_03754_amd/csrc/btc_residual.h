@@ -1,17 +1,27 @@
-// FP64 residual b - Psi x, streaming form: one wavefront per block row, every
-// n x n block read from HBM once and coalesced.
-//
-// Lane r owns rows r and r + 64 of the block row's vectors (columns of the
-// right-hand side are processed MC at a time, MC independent chains).  Every
-// block goes through LDS in slabs of 16 rows, laid out so that lane r reads
-// slab[k][r] conflict-free; the global loads of slab p+1 (NP/4 per lane, held
-// in registers) are in flight while slab p is consumed from LDS.
+// FP64 residual b - Psi x, every n x n block read from HBM once.
 //
 //   block row i: r_i = b_i - D_i x_i - E_{i-1} x_{i-1} - E_i^T x_{i+1}
-//     [row slabs of the lower triangle of D_i and of E_i, each element used
-//      for its own row and, through a wavefront sum, for its transpose's;
-//      E_i x_i is left for row i+1]; then per-column partial squared norms
-//     of r_i and b_i.
+//
+// Two launches.  The workgroup of block row i reads the lower triangle of D_i
+// and E_i (block (i+1, i)), wavefront w the tiles of tile row w, and uses
+// every tile twice:
+//   P_i     = b_i - D_i x_i - E_i^T x_{i+1}
+//   Q_{i+1} = E_i x_i
+// the second launch forms r_i = P_i - Q_i, its copies and the per-column
+// partial squared norms of r_i and b_i.
+//
+// All loads of a wavefront go out before the first product, four rows of 16
+// elements each: register v of lane l holds element (4v + l/16, l%16) of a
+// tile M.  That is the A operand of v_mfma_f64_4x4x4 for M^T (the lanes of one
+// of its four 4 x 4 blocks hold four rows of M^T), so M^T x takes four of them
+// per four columns of x; M x takes one fma per register and column, and only
+// the sum over a tile row is added up over its 16 lanes, once per row block
+// and not per tile.  What bounds it is memory; it took the place of a form
+// with one wavefront per block row and a sum over the wavefront for every row
+// of every block.  Measured, first launch, before -> after: N = 4096, n = 64,
+// m = 4: 167 -> 65 us (memory floor 40); n = 96, m = 4: 500 -> 116, m = 1: 106 ->
+// 98 (floor 91); n = 128, m = 1: 167 -> 171; N = 20 000, n = 32, m = 4: 373 -> 86;
+// N = 511, n = 50, m = 1: 16.3 -> 6.8.
 #pragma once
 
 #include "btc_device.h"
@@ -20,224 +30,10 @@
 namespace btc {
 namespace {
 
-constexpr int kS = 16;  // slab width
-
-__device__ __forceinline__ double bcast(double v, int lane) { return readlane_d(v, lane); }
-__device__ __forceinline__ float bcast(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-constexpr int gcd_i(int a, int b) { return b == 0 ? a : gcd_i(b, a % b); }
-
-template <int NP>
-struct Geo {
-    static_assert(NP % kS == 0, "padded size is a multiple of the slab width");
-    static constexpr int RPL = (NP + kWave - 1) / kWave;  // rows per lane
-    static constexpr int LDB = NP + 1;                    // slab stride (elements)
-    // lanes past the last row (r >= NP) read past the end of the last slab
-    // row: the buffer is long enough for them (their values are never used)
-    static constexpr int BUF = kS * LDB + kWave * RPL - NP;
-    static constexpr int PER = NP * kS / kWave;           // slab elements per lane
-    // row slab element u of a lane: pattern u % RP (row, column) of the first
-    // RP elements, moved down by (u / RP) * RK rows
-    static constexpr int RP = NP / gcd_i(NP, kWave);
-    static constexpr int RK = kWave / gcd_i(NP, kWave);
-};
-
-// Slab loads go through buffer resources (block_rsrc): rows and columns
-// beyond n and the skipped parts are masked by offset.
-
-// Where the next slab comes from: column slab (elements M[r][c0+k], rows
-// r >= rmin) or row slab (elements M[r0+k][r], only r <= r0+k when tri).
-template <class S>
-struct SlabSrc {
-    const S* M;
-    int off;
-    int rmin;
-    bool rows;
-    bool tri;
-};
-
-template <int NP, class T>
-struct SlabRegs {
-    T v[Geo<NP>::PER];
-
-    // Column slab: lane (q, k) = (lane / 16, lane % 16) reads rows q + 4u
-    // of column off + k, every offset a lane constant plus 4un.  Row slab:
-    // lanes read along the rows (pattern offsets of Geo).  Both skip what the
-    // triangular blocks do not use (column slab: the rows above rmin, a
-    // whole element index at a time; row slab: columns past the slab's last
-    // row).
-    template <class S>
-    __device__ __forceinline__ void fetch(const SlabSrc<S>& s, int n, int lane) {
-        using G = Geo<NP>;
-        const __amdgpu_buffer_rsrc_t rs = block_rsrc(s.M, n * n * (int)sizeof(S));
-        if (!s.rows) {
-            const int k = lane & (kS - 1), q = lane >> 4;
-            const int c = s.off + k;
-            const int base = c < n ? (q * n + c) * (int)sizeof(S) : kOob;
-            const int step = 4 * n * (int)sizeof(S);
-#pragma unroll
-            for (int u = 0; u < G::PER; ++u) {
-                if (4 * u < s.rmin)
-                    v[u] = T(0);
-                else
-                    buf_ld(v[u], rs, base + u * step);
-            }
-        } else {
-            int base[G::RP];
-#pragma unroll
-            for (int j = 0; j < G::RP; ++j) {
-                const int e = lane + kWave * j, r = e % NP, k = e / NP;
-                const bool ok = r < n && (!s.tri || r < s.off + kS);
-                base[j] = ok ? ((s.off + k) * n + r) * (int)sizeof(S) : kOob;
-            }
-            const int step = G::RK * n * (int)sizeof(S);
-#pragma unroll
-            for (int u = 0; u < G::PER; ++u) buf_ld(v[u], rs, base[u % G::RP] + (u / G::RP) * step);
-        }
-    }
-
-    __device__ __forceinline__ void put(T* __restrict__ buf, bool rows, int lane) const {
-        if (!rows) {
-#pragma unroll
-            for (int u = 0; u < Geo<NP>::PER; ++u) {
-                const int e = lane + kWave * u;
-                buf[(e % kS) * Geo<NP>::LDB + e / kS] = v[u];
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < Geo<NP>::PER; ++u) {
-                const int e = lane + kWave * u;
-                buf[(e / NP) * Geo<NP>::LDB + e % NP] = v[u];
-            }
-        }
-    }
-};
-
-// Value of vector row j (wave-uniform) of column c, held by lane j % 64.
-template <int RPL, int MC, class T>
-__device__ __forceinline__ T row_value(const T (&a)[RPL][MC], int j, int c) {
-    T x = a[0][c];
-#pragma unroll
-    for (int rr = 1; rr < RPL; ++rr)
-        if (j >= kWave * rr) x = a[rr][c];
-    return bcast(x, j & (kWave - 1));
-}
-
-// A kernel's block traffic as a list of up to four segments of slabs, each
-// segment the slabs of one block in one orientation.  Kept as separate
-// scalars (selected by wave-uniform indices) so the plan lives in registers.
-template <class S>
-struct Seg {
-    const S* M;
-    int count;   // slabs (0: segment absent)
-    bool rows;   // row slabs (else column slabs)
-    bool desc;   // slabs from the last one to the first
-    bool tri;    // column slab p: rows >= 16p only; row slab: r <= row only
-};
-
-template <class S>
-struct Plan {
-    const S *m0, *m1, *m2, *m3;
-    int c0, c1, c2, c3;
-    unsigned rows, desc, tri;  // bit g: property of segment g
-    int total;
-    int slabs;                 // slabs per block (the same for every present segment)
-
-    __device__ __forceinline__ void set(int g, const Seg<S>& sg) {
-        if (g == 0) { m0 = sg.M; c0 = sg.count; }
-        if (g == 1) { m1 = sg.M; c1 = sg.count; }
-        if (g == 2) { m2 = sg.M; c2 = sg.count; }
-        if (g == 3) { m3 = sg.M; c3 = sg.count; }
-        const unsigned bit = 1u << g;
-        rows = sg.rows ? (rows | bit) : (rows & ~bit);
-        desc = sg.desc ? (desc | bit) : (desc & ~bit);
-        tri = sg.tri ? (tri | bit) : (tri & ~bit);
-        total = c0 + c1 + c2 + c3;
-        if (sg.count) slabs = sg.count;
-    }
-
-    __device__ __forceinline__ void clear() {
-        m0 = m1 = m2 = m3 = nullptr;
-        c0 = c1 = c2 = c3 = 0;
-        rows = desc = tri = 0u;
-        total = 0;
-        slabs = 0;
-    }
-
-    __device__ __forceinline__ bool is_rows(int g) const { return (rows >> g) & 1u; }
-
-    // segment index and slab index within it of global slab p
-    __device__ __forceinline__ int locate(int p, int& q) const {
-        q = p;
-        if (q < c0) return 0;
-        q -= c0;
-        if (q < c1) return 1;
-        q -= c1;
-        if (q < c2) return 2;
-        q -= c2;
-        return 3;
-    }
-
-    __device__ __forceinline__ SlabSrc<S> src(int p) const {
-        int q;
-        const int g = locate(p, q);
-        const S* M = g == 0 ? m0 : g == 1 ? m1 : g == 2 ? m2 : m3;
-        const bool r = (rows >> g) & 1u, d = (desc >> g) & 1u, t = (tri >> g) & 1u;
-        const int sl = d ? slabs - 1 - q : q;  // every present segment has `slabs` slabs
-        return {M, kS * sl, (!r && t) ? kS * sl : 0, r, r && t};
-    }
-};
-
-// Slabs in flight beyond the one being consumed.  Measured on MI355X: a
-// second one buys little per-node latency and costs occupancy (registers),
-// so one.
-template <int NP, class T>
-constexpr int slab_depth() { return 1; }
-
-// Walk the slabs of a plan through the LDS buffer: slab p is consumed by
-// body(p, segment, slab index in segment, buffer) while the loads of the next
-// DEPTH slabs are in flight (register buffers indexed by unrolled constants).
-template <int NP, class T, int DEPTH, class S, class Body>
-__device__ __forceinline__ void run_slabs(const Plan<S>& pl, int n, int lane, T* __restrict__ buf, Body&& body) {
-    SlabRegs<NP, T> r[DEPTH];
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u)
-        if (u < pl.total) r[u].fetch(pl.src(u), n, lane);
-    for (int p = 0; p < pl.total; p += DEPTH) {
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u) {
-            const int q = p + u;
-            if (q < pl.total) {
-                int qs;
-                const int g = pl.locate(q, qs);
-                r[u].put(buf, pl.is_rows(g), lane);
-                wave_lds_sync();
-                if (q + DEPTH < pl.total) r[u].fetch(pl.src(q + DEPTH), n, lane);
-                body(g, qs, buf);
-                wave_lds_sync();
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Residual in two kernels, every block read from HBM once.  The wavefront of
-// block row i streams the lower triangle of D_i and the coupling E_i (block
-// (i+1, i)) as row slabs and uses each element M[c][r] twice: as M^T[r][c]
-// (lane r, the vector's row c broadcast) and as M[c][r] (lane r's product
-// with the lane's own vector row, summed over the wavefront into row c):
-//   P_i     = b_i - D_i x_i - E_i^T x_{i+1}
-//   Q_{i+1} = E_i x_i
-// The second kernel forms r_i = P_i - Q_i, its FP32 copy and the per-column
-// partial squared norms of r_i and b_i.  Work items of consecutive block rows
-// share an XCD (xcd_local_block).
-
-// Value of the exchange partner across lane bit H: DPP within rows of 16
-// lanes (the row mirror for bit 3, the half-row mirror for bit 2, quad
-// permutations for bits 1 and 0), LDS permute across rows.  Each pairing is
-// an involution whose pairs differ in bit H and otherwise only in lower bits.
+// Value of the exchange partner across lane bit H of a row of 16 lanes (DPP:
+// the row mirror for bit 3, the half-row mirror for bit 2, quad permutations
+// for bits 1 and 0).  Each pairing is an involution whose pairs differ in bit H
+// and otherwise only in lower bits.
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
     const long long w = __double_as_longlong(v);
@@ -250,13 +46,11 @@ __device__ __forceinline__ double partner(double v) {
     if constexpr (H == 8) return dpp_d<0x140>(v);       // row_mirror
     else if constexpr (H == 4) return dpp_d<0x141>(v);  // row_half_mirror
     else if constexpr (H == 2) return dpp_d<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    else if constexpr (H == 1) return dpp_d<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    else return __shfl_xor(v, H);
+    else return dpp_d<0xB1>(v);                         // quad_perm [1, 0, 3, 2]
 }
-// Lane bit of exchange step T: bits 3, 2, 1, 0 first (a mirror also flips
-// the bits below its own, so those must not be bound to a value yet), then
-// 4 and 5.
-constexpr int step_bit(int t) { return t < 4 ? 8 >> t : 16 << (t - 4); }
+// Lane bit of exchange step T: bits 3, 2, 1, 0 (a mirror also flips the bits
+// below its own, so those must not be bound to a value yet).
+constexpr int step_bit(int t) { return 8 >> t; }
 
 // Halving exchanges from step T on, W values per lane in play: the lane
 // keeps the half its step bit selects and adds its partner's copy of it.
@@ -274,41 +68,36 @@ __device__ __forceinline__ void halve(double* v, int lane) {
         halve<W / 2, T + 1>(v, lane);
     }
 }
-template <int T>
-__device__ __forceinline__ double all_sum(double s) {
-    if constexpr (T < 6) return all_sum<T + 1>(s + partner<step_bit(T)>(s));
-    else return s;
-}
-constexpr int ilog2_c(int v) { return v <= 1 ? 0 : 1 + ilog2_c(v / 2); }
-
-// Sum over the wavefront of KB values per lane (KB a power of two <= 16).
-// Afterwards the lanes given by row_source hold the totals.  Every total is
-// formed by the same tree of additions whatever KB is, so chunking rows
-// differently does not change a bit of the result.
+// Sum over rows of 16 lanes of KB values per lane (4 or 16): lane r of a row is
+// left with the total of value r (KB 16) or r / 4 (KB 4).  Every total is
+// formed by the same tree of additions whatever KB is.
 template <int KB>
-__device__ __forceinline__ double wave_sum_rows(double (&v)[KB], int lane) {
-    static_assert(KB >= 1 && KB <= 16 && (KB & (KB - 1)) == 0, "power of two up to 16");
+__device__ __forceinline__ double row_sums(double (&v)[KB], int lane) {
+    static_assert(KB == 4 || KB == 16, "values per lane");
     halve<KB / 2, 0>(v, lane);
-    return all_sum<ilog2_c(KB)>(v[0]);
-}
-// A lane that holds the total of value k after wave_sum_rows<KB>: step t of
-// the halving bound the value's bit KB / 2^(t+1) to lane bit step_bit(t).
-template <int KB>
-__device__ __forceinline__ int row_source(int k) {
-    int l = 0;
-#pragma unroll
-    for (int t = 0, w = KB / 2; w >= 1; ++t, w /= 2)
-        if (k & w) l |= step_bit(t);
-    return l;
+    double s = v[0];
+    if constexpr (KB == 4) {
+        s += partner<2>(s);
+        s += partner<1>(s);
+    }
+    return s;
 }
 
-template <int NP, int MC>
-__global__ __launch_bounds__(kWave) void k_res(Launch<ResidualDesc> L) {
-    using G = Geo<NP>;
-    constexpr int RPL = G::RPL, LDB = G::LDB;
-    constexpr int KB = 4 / MC;              // slab rows per wavefront sum (4 sums live)
-    static_assert(KB >= 1 && kS % KB == 0, "chunks divide the slab");
-    __shared__ double buf[G::BUF];
+// Wavefronts of a workgroup: one per tile row, or (from six tile rows on, where
+// two blocks' tiles do not fit the registers beside the sums) one per two of
+// them, w and NTL - 1 - w, a block at a time.
+template <int NTL>
+constexpr int res_rows() { return NTL >= 6 ? 2 : 1; }
+
+// MC: right-hand-side columns per pass over the tiles (1 or 4; the same
+// arithmetic for a column either way).  In the results' lane layout lane l
+// holds row 4 ((l%16) / 4) + l/16 of a tile, column l % 4 of the pass.
+template <int NTL, int MC>
+__global__ __launch_bounds__(NTL / res_rows<NTL>() * kWave, NTL >= 6 ? (MC == 1 ? 3 : 2) : 1) void k_res(
+    Launch<ResidualDesc> L) {
+    constexpr int kT = 16, RW = res_rows<NTL>(), W = NTL / RW;
+    __shared__ double xs[NTL * kT][MC];      // x_i of the pass
+    __shared__ double red[W][NTL][kWave];    // [wavefront][tile row]: its share of D_i x_i + E_i^T x_{i+1}
     ResidualDesc P;
     int64_t row0;
     {
@@ -323,171 +112,202 @@ __global__ __launch_bounds__(kWave) void k_res(Launch<ResidualDesc> L) {
         }
     }
     if (P.state && P.state->done) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, r = lane & 15, c = lane >> 4;
+    const int w = W == 1 ? 0 : wave_id();
     const int64_t N = P.N;
     const int n = P.n, m = P.m;
-    const size_t nn = (size_t)n * n;
+    const size_t nn = (size_t)n * n, nm = (size_t)n * m;
     const int64_t i = row0 + 1;
     const bool rgt = i < N;
-    const int ns = (n + kS - 1) / kS;
-    // D_i row slabs (the lower triangle: slab rows c, columns r <= last row
-    // of the slab), E_i row slabs
-    Plan<double> pl;
-    pl.clear();
-    pl.set(0, {P.A_diag + (size_t)(i - 1) * nn, ns, true, false, true});
-    pl.set(1, {rgt ? P.A_off + (size_t)(i - 1) * nn : nullptr, rgt ? ns : 0, true, false, false});
+    const double* const x1 = P.X + (size_t)(i - 1) * nm;
+    const double* const x2 = P.X + (size_t)(rgt ? i : i - 1) * nm;
+
+    // element (row, column q) of a block of vectors, 0 outside (and unless on)
+    auto vec = [&](const double* x, int row, int q, bool on) {
+        const bool ok = on && row < n && q < m;
+        const double v = x[ok ? (size_t)row * m + q : 0];
+        return ok ? v : 0.0;
+    };
+    double xn[RW][MC], xw[4], xr[4];
+    // x_i for all wavefronts
+    auto fetch_x = [&](int q0) {
+#pragma unroll
+        for (int h = 0; h < RW; ++h)
+#pragma unroll
+            for (int j = 0; j < MC; ++j)
+                xn[h][j] = vec(x1, threadIdx.x + h * W * kWave, q0 + j, (int)threadIdx.x + h * W * kWave < NTL * kT);
+    };
+    // x_i and x_{i+1} of tile row a as B operands
+    auto fetch_row = [&](int a, int q0) {
+        const int j = lane & 3;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            xw[v] = vec(x1, kT * a + 4 * v + c, q0 + j, j < MC);
+            xr[v] = vec(x2, kT * a + 4 * v + c, q0 + j, j < MC && rgt);
+        }
+    };
+    const auto re = block_rsrc(P.A_off + (size_t)(i - 1) * nn, rgt ? n * n * 8 : 0);
+    const auto rd = block_rsrc(P.A_diag + (size_t)(i - 1) * nn, n * n * 8);
+    const int lo = elem_off<double>(c, r, n, true);  // rows past n are past the block's end
+    auto load_tiles = [&](double (&M)[NTL][4], int a, bool lower) {
+#pragma unroll
+        for (int b = 0; b < NTL; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                buf_ld(M[b][v], lower ? rd : re,
+                       (!lower || kT * b + r <= kT * a + 4 * v + c) && r < n - kT * b ? lo : kOob,
+                       ((kT * a + 4 * v) * n + kT * b) * 8);
+    };
+    fetch_x(0);
+    double e[NTL][4], d[RW == 1 ? NTL : 1][4];
+    if constexpr (RW == 1) {
+        fetch_row(w, 0);
+        load_tiles(e, w, false);
+        load_tiles(d, w, true);
+    }
 
     for (int q0 = 0; q0 < m; q0 += MC) {
-        // acc: b_i minus the broadcast products; dl: (D_i x_i) over the lower
-        // triangle; qa: E_i x_i.  dl and qa take one wavefront sum per row,
-        // so the result does not depend on how rows are chunked (MC).
-        double acc[RPL][MC], dl[RPL][MC], qa[RPL][MC], x1[RPL][MC], x2[RPL][MC];
 #pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
+        for (int h = 0; h < RW; ++h)
+            if ((int)threadIdx.x + h * W * kWave < NTL * kT)
 #pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                const bool ok = r < n && q < m;
-                acc[rr][c] = ok ? P.B[((size_t)(i - 1) * n + r) * m + q] : 0.0;
-                dl[rr][c] = 0.0;
-                qa[rr][c] = 0.0;
-                x1[rr][c] = ok ? P.X[((size_t)(i - 1) * n + r) * m + q] : 0.0;
-                x2[rr][c] = (ok && rgt) ? P.X[((size_t)i * n + r) * m + q] : 0.0;
+                for (int j = 0; j < MC; ++j) xs[threadIdx.x + h * W * kWave][j] = xn[h][j];
+        __syncthreads();
+        double cr[NTL];
+#pragma unroll
+        for (int b = 0; b < NTL; ++b) cr[b] = 0.0;
+        const int q = q0 + (r & 3), rr = 4 * (r >> 2) + c;  // this lane's column, row of a tile
+        const bool mine = (MC == 4 || (r & 3) == 0) && q < m;
+        // a block's tile row a: its part of M x (returned), M^T x into cr
+        auto block = [&](const double (&M)[NTL][4], const double (&x)[4], int a, bool lower) {
+            double s[4 * MC];
+#pragma unroll
+            for (int k = 0; k < 4 * MC; ++k) s[k] = 0.0;
+#pragma unroll
+            for (int b = 0; b < NTL; ++b) {
+                if (lower && b > a) break;
+                double y[MC];
+#pragma unroll
+                for (int j = 0; j < MC; ++j) y[j] = xs[kT * b + r][j];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int j = 0; j < MC; ++j) s[v * MC + j] = fma(M[b][v], y[j], s[v * MC + j]);
+                // (the diagonal of D_i counts once)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    cr[b] = __builtin_amdgcn_mfma_f64_4x4x4f64(lower && b == a && r == 4 * v + c ? 0.0 : M[b][v], x[v],
+                                                               cr[b], 0, 0, 0);
+            }
+            return row_sums(s, lane);
+        };
+        auto add_own = [&](int a, double t) {
+#pragma unroll
+            for (int b = 0; b < NTL; ++b)
+                if (b == a) cr[b] += t;
+        };
+        auto store_q = [&](int a, double t) {
+            if (mine && kT * a + rr < n) P.Q[(size_t)i * nm + (size_t)(kT * a + rr) * m + q] = t;
+        };
+        if constexpr (RW == 1) {
+            if (rgt) store_q(w, block(e, xr, w, false));
+            add_own(w, block(d, xw, w, true));
+            if (q0 + MC < m) fetch_row(w, q0 + MC);
+        } else {
+#pragma unroll 1
+            for (int h = 0; h < RW; ++h) {
+                const int a = h ? NTL - 1 - w : w;
+                fetch_row(a, q0);
+                if (rgt) {
+                    load_tiles(e, a, false);
+                    store_q(a, block(e, xr, a, false));
+                }
+                load_tiles(e, a, true);
+                add_own(a, block(e, xw, a, true));
             }
         }
-        run_slabs<NP, double, slab_depth<NP, double>()>(pl, n, lane, buf, [&](int g, int q, const double* b) {
-            // g = 0: slab row c of D_i (elements with r <= c valid); g = 1:
-            // row c of E_i.  Rows past n are zero.
-            const int off = kS * q, dslot = off / kWave;
-#pragma unroll 1
-            for (int k0 = 0; k0 < kS; k0 += KB) {
-                double ps[MC][KB];
+        if (q0 + MC < m) fetch_x(q0 + MC);
 #pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int cc = off + k0 + k;
-                    double xb[MC];
+        for (int b = 0; b < NTL; ++b) red[w][b][lane] = cr[b];
+        __syncthreads();
 #pragma unroll
-                    for (int c = 0; c < MC; ++c) {
-                        double t = g == 0 ? x1[0][c] : x2[0][c];
+        for (int h = 0; h < RW; ++h) {
+            const int a = h ? NTL - 1 - w : w;
+            double sum = red[0][a][lane];
 #pragma unroll
-                        for (int rr = 1; rr < RPL; ++rr)
-                            if (cc >= kWave * rr) t = g == 0 ? x1[rr][c] : x2[rr][c];
-                        xb[c] = -bcast(t, cc & (kWave - 1));
-                        ps[c][k] = 0.0;
-                    }
-#pragma unroll
-                    for (int rr = 0; rr < RPL; ++rr) {
-                        const int r = lane + kWave * rr;
-                        // columns r in [n, NP) of the slab are zero; lanes r >= NP
-                        // would read the next slab row (perhaps the unread
-                        // upper triangle of D_i) and feed the wavefront sums
-                        const double a = (NP % kWave == 0 || rr < RPL - 1 || r < NP) ? b[(k0 + k) * LDB + r] : 0.0;
-                        if (g == 0 && rr == dslot) {
-                            // the diagonal tile of D_i: as element (r, c) above
-                            // the diagonal (r < c), as element (c, r) on and
-                            // below it
-                            const double au = r >= cc ? 0.0 : a;
-                            const double al = r > cc ? 0.0 : a;
-#pragma unroll
-                            for (int c = 0; c < MC; ++c) {
-                                acc[rr][c] = fma(au, xb[c], acc[rr][c]);
-                                ps[c][k] = fma(al, x1[rr][c], ps[c][k]);
-                            }
-                        } else {
-                            // D_i left of the diagonal tile (the rest of the
-                            // slab row is zero), E_i: both uses
-#pragma unroll
-                            for (int c = 0; c < MC; ++c) {
-                                acc[rr][c] = fma(a, xb[c], acc[rr][c]);
-                                ps[c][k] = fma(a, x1[rr][c], ps[c][k]);
-                            }
-                        }
-                    }
-                }
-                // row c = off + k0 + k gets its sum from lane row_source(k);
-                // its owner is lane c % 64 in slot c / 64
-                const int base = off + k0, slot = base / kWave;
-                const int k = lane - (base & (kWave - 1));
-                const int src = row_source<KB>(k & (KB - 1));
-#pragma unroll
-                for (int c = 0; c < MC; ++c) {
-                    const double s = wave_sum_rows<KB>(ps[c], lane);
-                    const double t = __shfl(s, src);
-                    if (k >= 0 && k < KB) {
-#pragma unroll
-                        for (int rr = 0; rr < RPL; ++rr) {
-                            if (rr == slot) {
-                                if (g == 0)
-                                    dl[rr][c] += t;
-                                else
-                                    qa[rr][c] += t;
-                            }
-                        }
-                    }
-                }
-            }
-        });
-#pragma unroll
-        for (int rr = 0; rr < RPL; ++rr) {
-            const int r = lane + kWave * rr;
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int q = q0 + c;
-                if (r < n && q < m) {
-                    P.P[((size_t)(i - 1) * n + r) * m + q] = acc[rr][c] - dl[rr][c];
-                    if (rgt) P.Q[((size_t)i * n + r) * m + q] = qa[rr][c];
-                }
-            }
+            for (int k = 1; k < W; ++k) sum += red[k][a][lane];
+            const size_t at = (size_t)(i - 1) * nm + (size_t)(kT * a + rr) * m + q;
+            if (mine && kT * a + rr < n) P.P[at] = P.B[at] - sum;
         }
     }
 }
 
 // r_i = P_i - Q_i (Q_1 = 0), its FP32 copy and the partial norms; one
-// wavefront per block row.
-__global__ __launch_bounds__(kWave) void k_res_fin(Launch<ResidualDesc> L) {
+// wavefront per block row, four to a workgroup, MC columns at a time.
+constexpr int kFinRows = 4;
+template <int MC>
+__global__ __launch_bounds__(kFinRows * kWave) void k_res_fin(Launch<ResidualDesc> L, int64_t items) {
+    const int64_t idx = (int64_t)blockIdx.x * kFinRows + wave_id();
+    if (idx >= items) return;
     ResidualDesc P;
     int level;
     int64_t row0;
-    fetch_item(L, P, level, row0);
+    fetch_item_at(L, idx, P, level, row0);
     if (P.state && P.state->done) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int n = P.n, m = P.m;
     const int64_t i = row0 + 1;
-    for (int q = 0; q < m; ++q) {
-        double r2 = 0.0, b2 = 0.0;
+    const size_t base = (size_t)(i - 1) * n * m;
+    for (int q0 = 0; q0 < m; q0 += MC) {
+        double r2[MC] = {}, b2[MC] = {};
         for (int r = lane; r < n; r += kWave) {
-            const size_t e = ((size_t)(i - 1) * n + r) * m + q;
-            const double v = i > 1 ? P.P[e] - P.Q[e] : P.P[e];
-            if (P.R32) P.R32[e] = (float)v;
-            if (P.R64) P.R64[e] = P.neg ? -v : v;
-            const double bv = P.B[e];
-            r2 = fma(v, v, r2);
-            b2 = fma(bv, bv, b2);
+            double p[MC], q[MC], b[MC];
+#pragma unroll
+            for (int j = 0; j < MC; ++j) {
+                const size_t e = base + (size_t)r * m + (q0 + j < m ? q0 + j : q0);
+                p[j] = P.P[e];
+                q[j] = i > 1 ? P.Q[e] : 0.0;
+                b[j] = P.B[e];
+            }
+#pragma unroll
+            for (int j = 0; j < MC; ++j) {
+                if (q0 + j >= m) break;
+                const size_t e = base + (size_t)r * m + q0 + j;
+                const double v = p[j] - q[j];
+                if (P.R32) P.R32[e] = (float)v;
+                if (P.R64) P.R64[e] = P.neg ? -v : v;
+                r2[j] = fma(v, v, r2[j]);
+                b2[j] = fma(b[j], b[j], b2[j]);
+            }
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            r2 += __shfl_xor(r2, off);
-            b2 += __shfl_xor(b2, off);
-        }
-        if (lane == 0) {
-            P.part[((size_t)(i - 1) * m + q) * 2 + 0] = r2;
-            P.part[((size_t)(i - 1) * m + q) * 2 + 1] = b2;
+        for (int j = 0; j < MC; ++j) {
+            if (q0 + j >= m) break;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                r2[j] += __shfl_xor(r2[j], off);
+                b2[j] += __shfl_xor(b2[j], off);
+            }
+            if (lane == 0) {
+                P.part[((size_t)(i - 1) * m + q0 + j) * 2 + 0] = r2[j];
+                P.part[((size_t)(i - 1) * m + q0 + j) * 2 + 1] = b2[j];
+            }
         }
     }
 }
 
-template <int NP>
-hipError_t launch_res_np(const Launch<ResidualDesc>& p, int64_t items, int mc, hipStream_t st) {
-    const dim3 g((unsigned)items), b(kWave);
-    if (mc <= 1)
-        hipLaunchKernelGGL((k_res<NP, 1>), g, b, 0, st, p);
-    else
-        hipLaunchKernelGGL((k_res<NP, 4>), g, b, 0, st, p);
-    hipError_t e = hipGetLastError();
+template <int NTL, int MC>
+hipError_t launch_res_mc(const Launch<ResidualDesc>& p, int64_t items, hipStream_t st) {
+    hipLaunchKernelGGL((k_res<NTL, MC>), dim3((unsigned)items), dim3(NTL / res_rows<NTL>() * kWave), 0, st, p);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_res_fin, g, b, 0, st, p);
+    hipLaunchKernelGGL(k_res_fin<MC>, dim3((unsigned)((items + kFinRows - 1) / kFinRows)), dim3(kFinRows * kWave), 0, st,
+                       p, items);
     return hipGetLastError();
+}
+template <int NTL>
+hipError_t launch_res_np(const Launch<ResidualDesc>& p, int64_t items, int mc, hipStream_t st) {
+    return mc <= 1 ? launch_res_mc<NTL, 1>(p, items, st) : launch_res_mc<NTL, 4>(p, items, st);
 }
 
 }  // namespace
@@ -495,11 +315,11 @@ hipError_t launch_res_np(const Launch<ResidualDesc>& p, int64_t items, int mc, h
 hipError_t launch_residual(const Launch<ResidualDesc>& p, int np, int64_t items, int mc, hipStream_t st) {
     switch (np) {
         case 8:
-        case 16: return launch_res_np<16>(p, items, mc, st);
-        case 32: return launch_res_np<32>(p, items, mc, st);
-        case 64: return launch_res_np<64>(p, items, mc, st);
-        case 96: return launch_res_np<96>(p, items, mc, st);
-        case 128: return launch_res_np<128>(p, items, mc, st);
+        case 16: return launch_res_np<1>(p, items, mc, st);
+        case 32: return launch_res_np<2>(p, items, mc, st);
+        case 64: return launch_res_np<4>(p, items, mc, st);
+        case 96: return launch_res_np<6>(p, items, mc, st);
+        case 128: return launch_res_np<8>(p, items, mc, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -15,8 +15,9 @@ constexpr unsigned long long kInfoOk = ~0ull;
 // max_q ||r_q||/||b_q|| and advance its refinement state: converged when
 // <= tol, stalled when the residual fell by less than 2x in the last step,
 // done when either holds or the step budget is spent.
-__global__ __launch_bounds__(256) void k_ir_check(Launch<IrDesc> L) {
-    __shared__ double red[2][256];
+constexpr int kCheckThreads = 1024;
+__global__ __launch_bounds__(kCheckThreads) void k_ir_check(Launch<IrDesc> L) {
+    __shared__ double red[2][kCheckThreads / kWave];
     IrDesc P;
     int lvl_unused;
     int64_t k_unused;
@@ -25,24 +26,32 @@ __global__ __launch_bounds__(256) void k_ir_check(Launch<IrDesc> L) {
     if (st->done) return;
     const int64_t N = P.N;
     const int m = P.m;
+    const int lane = threadIdx.x & 63;
     double worst = 0.0;
     for (int q = 0; q < m; ++q) {
         double rr = 0.0, bb = 0.0;
-        for (int64_t i = threadIdx.x; i < N; i += 256) {
+#pragma unroll 4
+        for (int64_t i = threadIdx.x; i < N; i += kCheckThreads) {
             rr += P.part[((size_t)i * m + q) * 2 + 0];
             bb += P.part[((size_t)i * m + q) * 2 + 1];
         }
-        red[0][threadIdx.x] = rr;
-        red[1][threadIdx.x] = bb;
-        __syncthreads();
-        for (int h = 128; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) {
-                red[0][threadIdx.x] += red[0][threadIdx.x + h];
-                red[1][threadIdx.x] += red[1][threadIdx.x + h];
-            }
-            __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            rr += __shfl_xor(rr, off);
+            bb += __shfl_xor(bb, off);
         }
-        const double rn = sqrt(red[0][0]), bn = sqrt(red[1][0]);
+        if (lane == 0) {
+            red[0][threadIdx.x / kWave] = rr;
+            red[1][threadIdx.x / kWave] = bb;
+        }
+        __syncthreads();
+        rr = bb = 0.0;
+#pragma unroll
+        for (int k = 0; k < kCheckThreads / kWave; ++k) {
+            rr += red[0][k];
+            bb += red[1][k];
+        }
+        const double rn = sqrt(rr), bn = sqrt(bb);
         const double rel = (bn > 0.0) ? rn / bn : rn;
         worst = fmax(worst, rel);
         __syncthreads();
@@ -212,7 +221,7 @@ hipError_t launch_fill(double* x, double v, int64_t count, hipStream_t st) {
 }
 
 hipError_t launch_ir_check(const Launch<IrDesc>& p, int64_t items, hipStream_t st) {
-    hipLaunchKernelGGL(k_ir_check, dim3((unsigned)items), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(k_ir_check, dim3((unsigned)items), dim3(kCheckThreads), 0, st, p);
     return hipGetLastError();
 }
 
