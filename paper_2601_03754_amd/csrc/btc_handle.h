@@ -463,8 +463,15 @@ inline hipError_t launch_factor_kind(int kind, const btc::Launch<btc::FactorDesc
     }
 }
 
-inline hipError_t launch_factor_any(btc_handle h, const btc::Launch<btc::FactorDesc>& L, int64_t items, hipStream_t st) {
+// Padded size of a level's launch: the one-workgroup-per-node kernels have one
+// for n 33..48 too.
+inline int factor_launch_np(btc_handle h, int kind) {
     const int np = factor_np(h);
+    return np == 64 && h->n <= 48 && !tiled_kind(kind) ? 48 : np;
+}
+
+inline hipError_t launch_factor_any(btc_handle h, const btc::Launch<btc::FactorDesc>& L, int64_t items, hipStream_t st) {
+    const int np = factor_launch_np(h, factor_kind(h, L.level));
     const bool deferred = L.level > 0 && !(L.single.flags & btc::kFactorDeferredDone);
     return launch_factor_kind(factor_kind(h, L.level), L, np, deferred, items, st);
 }

@@ -35,7 +35,9 @@
 // parallel there: 16.4 -> 11.3), n = 8 (vector ALUs) 7.9 -> 6.5; at n = 33..64
 // the tile-parallel step takes as long per node in FP64 (24.1 / 26.3 at n =
 // 64) and longer in mixed precision (27.2 / 22.4), and is slower on wide levels
-// (2048 nodes of n = 64: 156 / 137).
+// (2048 nodes of n = 64: 156 / 137).  n = 33..48 has a kernel of three tile rows
+// (N = 32 768, n = 48: 1 778 us with four, 1 584 with three; mixed 1 460, 1 302;
+// an inner level 21.2 and 18.9).
 //
 // MODE 0: FP64.  MODE 1 (mixed precision): S_j, the Cholesky factorization and
 // the triangular solves in FP64; L_ii, R_i, T_i and the fill rounded to FP32;
@@ -110,35 +112,39 @@ __device__ __forceinline__ void sub_abt(d4& x, const d4& a, const d4& b) {
 constexpr int kImg = kT * kT;
 __device__ __forceinline__ int img_pos(int row, int col) { return kT * col + (row ^ col); }
 
-// Wavefronts per SIMD the register budget is set for: at NTL = 4 two
-// workgroups share a compute unit, below that three wavefronts share a SIMD.
-constexpr int node_waves(int ntl) { return ntl > 1 ? 2 : 3; }
+// Wavefronts per SIMD the register budget is set for: two workgroups of three
+// or four wavefronts share a compute unit, four of two, twelve of one.
+constexpr int node_waves(int ntl) { return ntl == 1 ? 3 : 2; }
 
 template <int NTL, int MODE>
 __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(Launch<FactorDesc> L) {
     using PR = Prod<MODE>;
     using F = typename PR::F;
     using Acc = typename PR::Acc;
-    static_assert(NTL == 1 || NTL == 2 || NTL == 4, "tile rows");
+    static_assert(NTL >= 1 && NTL <= 4, "tile rows");
     // tile pairs {w, (w + d) % NTL} of wavefront w cover the lower triangle
     constexpr int D = NTL / 2 + 1;
     constexpr int TB = NTL == 1 ? 2 : 3;  // tiles of a panel besides the diagonal one
     constexpr int kTri = NTL * (NTL + 1) / 2;
-    // LDS: images of R_i and T_i; at NTL = 4 those of T' and T'' share R_i's
-    // place and those of S_i start in T_i's, barriers between
+    // Three tile rows: the row of L_ii that a wavefront carries stays in LDS, in
+    // S_i's images (four tile rows in FP64 have no room for those beside R_i's
+    // and T_i's)
+    constexpr bool kRowLds = NTL == 3;
+    // LDS: images of R_i and T_i; from NTL = 3 on those of T' and T'' share
+    // R_i's place, at NTL = 4 those of S_i start in T_i's, barriers between
     constexpr int kR = NTL == 1 ? 0 : NTL * NTL * kImg * (int)sizeof(F);
     constexpr int kS = kTri * kImg * 8;
     constexpr int kOverlay = kR + (NTL == 4 ? (kR > kS ? kR : kS) : kR + kS);
     constexpr int kL = NTL == 4 ? (NTL - 1 + NTL - 2 + 2) * kImg * 8 : 0;
-    __shared__ bool run;
     constexpr int kStage = NTL == 2 ? NTL * kImg * 8 : 0;
+    __shared__ bool run;
     __shared__ __align__(16) char lds[kOverlay + kL + kStage];
     F* const iR = (F*)lds;                             // [tile row][tile column]
     F* const iT = iR + NTL * NTL * kImg;               // [tile column][tile row]
     double* const iS = (double*)(lds + (NTL == 4 ? kR : 2 * kR));  // lower tiles
     double* const iL = (double*)(lds + kOverlay);      // tiles below the diagonal of panels p and p + 1
-    // one image per wavefront to turn tiles in, before S_i's and L_ii's are there
-    double* const iStage = NTL == 1 ? iS : iL;
+    // one image per wavefront to turn tiles in, before what is there later
+    double* const iStage = NTL == 1 ? iS : kRowLds ? (double*)iT : iL;
     double* const iQ = iL + (2 * NTL - 3) * kImg;      // updated diagonal tiles p and p + 1
 
     FactorDesc P;
@@ -265,7 +271,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
                 F o[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    o[v] = d == 0 ? own[p][v] : NTL == 4 ? img[(other(d) * NTL + p) * kImg + po[v]] : oth[p][v];
+                    o[v] = d == 0 ? own[p][v] : NTL >= 3 ? img[(other(d) * NTL + p) * kImg + po[v]] : oth[p][v];
                 PR::template tile<MODE == 0>(acc, o, own[p]);
             }
             if constexpr (MODE == 0) x[d] = acc;
@@ -283,7 +289,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
     };
 
     // 1. all loads, then S_i and S_{i+s} with their deferred updates
-    d4 X[3][NTL];  // R_i (tile row w), T_i^T (tile column w), L_ii (tile row a)
+    d4 X[kRowLds ? 2 : 3][NTL];  // R_i (tile row w), T_i^T (tile column w), L_ii (tile row a)
     d4 sep[D];
     const int a = NTL == 2 ? 1 : w;  // (two tile rows: both wavefronts carry the lower one)
     d4 Q;
@@ -318,18 +324,18 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) load_pair(sep[d], d, rp);
-        if constexpr (NTL < 4) load_cols(t2, w, r2, true);
+        if constexpr (NTL < 3) load_cols(t2, w, r2, true);
         if constexpr (NTL == 2) load_cols(o2, other(1), r2, pair_on(1));
         __builtin_amdgcn_sched_barrier(0);
 
         if (def_self) {
-            if constexpr (NTL == 4) {
+            if constexpr (NTL >= 3) {
                 put_img(iR, t1);
                 __syncthreads();
             }
             syrk(self, t1, o1, iR);
         }
-        if constexpr (NTL == 4) load_cols(t2, w, r2, true);  // (registers of T')
+        if constexpr (NTL >= 3) load_cols(t2, w, r2, true);  // (registers of T')
         if (MODE == 0 || lvl > 0) turn(x[0]);
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
             if (!run) return;
         }
         if (def_sep) {
-            if constexpr (NTL == 4) {
+            if constexpr (NTL >= 3) {
                 put_img(iR, t2);  // (T' has been read before the barrier above)
                 __syncthreads();
             }
@@ -377,21 +383,33 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         for (int v = 0; v < 4; ++v) x[v] = img[po[v]];
     };
     load_img(Q, iS);
+    if constexpr (!kRowLds) {
 #pragma unroll
-    for (int b = 0; b < NTL; ++b) {
-        X[2][b] = d4{0.0, 0.0, 0.0, 0.0};
-        if (NTL > 1 && a > 0 && a < nt && b <= a) load_img(X[2][b], iS + (a * (a + 1) / 2 + b) * kImg);
+        for (int b = 0; b < NTL; ++b) {
+            X[2][b] = d4{0.0, 0.0, 0.0, 0.0};
+            if (NTL > 1 && a > 0 && a < nt && b <= a) load_img(X[2][b], iS + (a * (a + 1) / 2 + b) * kImg);
+        }
     }
+    auto tri = [](int x, int y) { return (x * (x + 1) / 2 + y) * kImg; };
+    auto store_img = [&](double* img, const d4& x) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) img[po[v]] = x[v];
+    };
+    const int lo = elem_off<F>(c, r, n, true);
     const auto rL = rsrc(Lf + (size_t)pi * nn, true);
     const auto rR = rsrc(Rf + (size_t)pi * nn, has_r), rT = rsrc(Tf + (size_t)pi * nn, has_l);
-#pragma unroll (NTL == 4 ? 1 : NTL)
-    for (int p = 0; p < (NTL == 4 ? nt : NTL); ++p) {
+#pragma unroll (NTL >= 3 ? 1 : NTL)
+    for (int p = 0; p < (NTL >= 3 ? nt : NTL); ++p) {
         d4 E;
 #pragma unroll
         for (int v = 0; v < 4; ++v) E[v] = 4 * v + c == r ? 1.0 : 0.0;
         d4 Y[TB];
 #pragma unroll
-        for (int t = 0; t < TB; ++t) Y[t] = X[t][0];
+        for (int t = 0; t < (kRowLds ? 2 : TB); ++t) Y[t] = X[t][0];
+        if constexpr (kRowLds) {
+            Y[2] = d4{0.0, 0.0, 0.0, 0.0};
+            if (a > p && a < nt) load_img(Y[2], iS + tri(a, p));
+        }
         bool ok = true;
         double inv;
         const int left = n - kT * p;  // steps past n are the identity
@@ -423,7 +441,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         const int own = (rows * n + c) * (int)sizeof(F);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            buf_st((F)Y[1][v], rT, elem_off<F>(c, rows, n, rows < n), (kT * p + 4 * v) * n * (int)sizeof(F));
+            buf_st((F)Y[1][v], rT, rows < n ? lo : kOob, ((kT * p + 4 * v) * n + kT * w) * (int)sizeof(F));
             if (w == p)
                 buf_st((F)(r < 4 * v + c ? E[v] : Q[v]), rL, 4 * v + c < left && r < left ? own : kOob,
                        col + 4 * v * (int)sizeof(F));
@@ -433,27 +451,33 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         X[0][0] = Y[0];
         X[1][0] = Y[1];
         if constexpr (NTL == 1) continue;
-        if constexpr (NTL == 4) {
+        if constexpr (NTL >= 3) {
             if (p + 1 < nt) {
+                double* const img = kRowLds ? iS + tri(a, p) : iL + ((p & 1) * (NTL - 1) + a - 1 - p) * kImg;
                 if (below) {
-                    double* const img = iL + ((p & 1) * (NTL - 1) + a - 1 - p) * kImg;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) img[po[v]] = Y[TB - 1][v];
+                    store_img(img, Y[TB - 1]);
                     wave_lds_sync();
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        buf_st((F)img[tp[v]], rL, elem_off<F>(c, r, n, true), ((kT * w + 4 * v) * n + kT * p) * (int)sizeof(F));
+                        buf_st((F)img[tp[v]], rL, lo, ((kT * w + 4 * v) * n + kT * p) * (int)sizeof(F));
                 }
+                double* const next = kRowLds ? iS + tri(p + 1, p + 1) : iQ + (p & 1) * kImg;
                 if (a == p + 1) {
-                    sub_abt(X[2][1], Y[TB - 1], Y[TB - 1]);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) iQ[(p & 1) * kImg + po[v]] = X[2][1][v];
+                    if constexpr (kRowLds) {
+                        d4 x;
+                        load_img(x, next);
+                        sub_abt(x, Y[TB - 1], Y[TB - 1]);
+                        store_img(next, x);
+                    } else {
+                        sub_abt(X[2][1], Y[TB - 1], Y[TB - 1]);
+                        store_img(next, X[2][1]);
+                    }
                 }
                 __syncthreads();
-                load_img(Q, iQ + (p & 1) * kImg);
+                load_img(Q, next);
             }
         }
-        // the images for step 3 (at NTL = 4 in the place of others, which all
+        // the images for step 3 (from NTL = 3 on in the place of others, which all
         // wavefronts have read before the barrier above)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -464,19 +488,27 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         for (int q = 1; q < NTL; ++q) {
             if (p + q >= nt) break;
             d4 lq;
-            if constexpr (NTL == 4) load_img(lq, iL + ((p & 1) * (NTL - 1) + q - 1) * kImg);
+            if constexpr (kRowLds) load_img(lq, iS + tri(p + q, p));
+            else if constexpr (NTL >= 3) load_img(lq, iL + ((p & 1) * (NTL - 1) + q - 1) * kImg);
             else lq = Y[TB - 1];
             sub_abt(X[0][q], X[0][0], lq);
             sub_abt(X[1][q], X[1][0], lq);
-            if (NTL == 2 || (q > 1 ? p + q <= a : a > p + 1)) sub_abt(X[2][q], Y[TB - 1], lq);
+            if (NTL == 2 || (q > 1 ? p + q <= a : a > p + 1)) {
+                if constexpr (kRowLds) {
+                    d4 x;
+                    load_img(x, iS + tri(a, p + q));
+                    sub_abt(x, Y[TB - 1], lq);
+                    store_img(iS + tri(a, p + q), x);
+                } else {
+                    sub_abt(X[2][q], Y[TB - 1], lq);
+                }
+            }
         }
         if constexpr (NTL == 2) Q = X[2][1];
 #pragma unroll
-        for (int q = 1; q < NTL; ++q) {
-            X[0][q - 1] = X[0][q];
-            X[1][q - 1] = X[1][q];
-            X[2][q - 1] = X[2][q];
-        }
+        for (int q = 1; q < NTL; ++q)
+#pragma unroll
+            for (int t = 0; t < (kRowLds ? 2 : TB); ++t) X[t][q - 1] = X[t][q];
     }
     if (!has_r) return;
     if constexpr (NTL > 1) {
@@ -493,7 +525,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
             if (p >= nt) break;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                buf_st(img[p * kImg + tp[v]], rR, elem_off<F>(c, r, n, r < n - kT * p),
+                buf_st(img[p * kImg + tp[v]], rR, r < n - kT * p ? lo : kOob,
                        ((kT * w + 4 * v) * n + kT * p) * (int)sizeof(F));
         }
     }
@@ -575,6 +607,7 @@ hipError_t launch_factor_node(const Launch<FactorDesc>& p, int np, int64_t items
         case 8:
         case 16: hipLaunchKernelGGL((k_factor_node<1, MODE>), g, dim3(kWave), 0, st, p); break;
         case 32: hipLaunchKernelGGL((k_factor_node<2, MODE>), g, dim3(2 * kWave), 0, st, p); break;
+        case 48: hipLaunchKernelGGL((k_factor_node<3, MODE>), g, dim3(3 * kWave), 0, st, p); break;
         case 64: hipLaunchKernelGGL((k_factor_node<4, MODE>), g, dim3(4 * kWave), 0, st, p); break;
         default: return hipErrorInvalidValue;
     }

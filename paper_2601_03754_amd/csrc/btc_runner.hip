@@ -422,8 +422,8 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
                 h->factored = true;
                 h->failed_known = false;
             }
-            const int np = factor_np(h);
             const int kind = factor_kind(h, s.level);
+            const int np = factor_launch_np(h, kind);
             Group& g = groups[std::make_tuple(s.stage, s.op, kind, np)];
             g.stage = s.stage;
             g.op = s.op;

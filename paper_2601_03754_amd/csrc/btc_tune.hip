@@ -88,7 +88,7 @@ void save_tune_cache() {
 // Variant of a key nobody has set: the one-workgroup-per-node step, which is
 // variant 1 at padded size 64 (measured, N = 4096, factorization, node / tile-
 // parallel step: n = 64 FP64 534 / 547 us, mixed 448 / 523, BF16 458 / 533;
-// n = 48 FP64 406 / 506, mixed 355 / 494).
+// n = 48 FP64 371 / 506, mixed 317 / 494).
 int default_variant(int op, int np) { return (op == BTC_OP_FACTOR && np == 64) ? 1 : 0; }
 
 int tune_variant(int op, int kind, int np, int bucket) {
