@@ -28,6 +28,7 @@
 #include "btc.h"
 #include "btc_device.h"
 #include "btc_handle.h"
+#include "btc_tiled.h"
 
 using namespace btc;
 using namespace btc_host;
@@ -35,22 +36,21 @@ using namespace btc_host;
 namespace {
 
 constexpr int kTipMax = 128;      // largest tip (m) of an arrow
-constexpr int kT = 256;           // threads of the elementwise kernels
+constexpr int kThreads = 256;     // threads of the elementwise kernels
 constexpr int kChunksMax = 256;   // partial tiles of a tall-skinny product
-typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Super-blocks of a block-banded matrix.  One thread per element of D2
 // (N2 blocks of order n2 = b n) and of E2 (N2 - 1 blocks, E2[I-1] the block
 // at super-row I, super-column I-1).  Element (R, C) of super-block (I, J)
 // is element (R % n, C % n) of block (b I + R / n, b J + C / n).
-__global__ __launch_bounds__(kT) void k_band_pack(const double* __restrict__ A, int64_t N, int n, int b,
+__global__ __launch_bounds__(kThreads) void k_band_pack(const double* __restrict__ A, int64_t N, int n, int b,
                                                   int64_t N2, double* __restrict__ D2, double* __restrict__ E2) {
     const int n2 = b * n;
     const int64_t per = (int64_t)n2 * n2;
     const int64_t total = (2 * N2 - 1) * per;
     const size_t nn = (size_t)n * n;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total; e += (int64_t)gridDim.x * kT) {
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total; e += (int64_t)gridDim.x * kThreads) {
         const bool diag = e < N2 * per;
         const int64_t sb = diag ? e / per : (e - N2 * per) / per;  // super-block (I, or I-1 for E2)
         const int64_t rc = diag ? e % per : (e - N2 * per) % per;
@@ -81,19 +81,19 @@ __global__ __launch_bounds__(kT) void k_band_pack(const double* __restrict__ A, 
 }
 
 // dst = src for the first `rows` rows, 0 for the rest (rows of q values).
-__global__ __launch_bounds__(kT) void k_pad_rows(const double* __restrict__ src, int64_t rows, int64_t rows_pad,
+__global__ __launch_bounds__(kThreads) void k_pad_rows(const double* __restrict__ src, int64_t rows, int64_t rows_pad,
                                                  int64_t q, double* __restrict__ dst) {
     const int64_t total = rows_pad * q;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total; e += (int64_t)gridDim.x * kT)
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total; e += (int64_t)gridDim.x * kThreads)
         dst[e] = e < rows * q ? src[e] : 0.0;
 }
 
-__global__ __launch_bounds__(kT) void k_copy(const double* __restrict__ src, int64_t count, double* __restrict__ dst) {
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < count; e += (int64_t)gridDim.x * kT) dst[e] = src[e];
+__global__ __launch_bounds__(kThreads) void k_copy(const double* __restrict__ src, int64_t count, double* __restrict__ dst) {
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < count; e += (int64_t)gridDim.x * kThreads) dst[e] = src[e];
 }
 
 unsigned grid_for(int64_t elems) {
-    const int64_t g = (elems + kT - 1) / kT;
+    const int64_t g = (elems + kThreads - 1) / kThreads;
     return (unsigned)(g < 8192 ? (g > 0 ? g : 1) : 8192);
 }
 
@@ -103,23 +103,35 @@ unsigned grid_for(int64_t elems) {
 // rows [chunk*rows, (chunk+1)*rows) of F and Y, one 16 x 16 quadrant per
 // wavefront on the FP64 matrix cores (lane (i, kq) feeds F[k + kq][row0 + i]
 // and Y[k + kq][col0 + i]; accumulator v of the lane holds output row
-// 4 v + kq, column i).  Pass 2 sums the chunks in order.
+// 4 v + kq, column i).  Pass 2 sums the chunks: kFinParts threads per output
+// element, each every kFinParts-th chunk in order, then their sums in order (a
+// thread per element took 61 us for 250 chunks of 40 x 40).
 __global__ __launch_bounds__(256) void k_tsk_part(const double* __restrict__ F, const double* __restrict__ Y,
                                                   int64_t K, int m, int q, int64_t rows, double* __restrict__ part) {
     const int tq = (q + 31) / 32;
     const int tm = (int)blockIdx.y / tq, tc = (int)blockIdx.y % tq;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
     const int r0 = 32 * tm + 16 * (w >> 1), c0 = 32 * tc + 16 * (w & 1);
+    if (r0 >= m || c0 >= q) return;
     const int64_t k0 = (int64_t)blockIdx.x * rows, k1 = k0 + rows < K ? k0 + rows : K;
     const bool okr = r0 + i < m, okc = c0 + i < q;
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int64_t k = k0; k < k1; k += 4) {
-        const int64_t kk = k + kq;
-        const bool okk = kk < k1;
-        const double a = (okk && okr) ? F[kk * m + r0 + i] : 0.0;
-        const double y = (okk && okc) ? Y[kk * q + c0 + i] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, y, acc, 0, 0, 0);
+    const double* const f = F + (okr ? r0 + i : 0);
+    const double* const g = Y + (okc ? c0 + i : 0);
+    tiles::d4 acc = {0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 8;  // steps whose loads are in flight together
+    for (int64_t k = k0; k < k1; k += 4 * U) {
+        double a[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t kk = k + 4 * u + kq, at = kk < k1 ? kk : k0;
+            a[u] = f[at * m];
+            y[u] = g[at * q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool ok = k + 4 * u + kq < k1;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ok && okr ? a[u] : 0.0, ok && okc ? y[u] : 0.0, acc, 0, 0, 0);
+        }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -128,26 +140,38 @@ __global__ __launch_bounds__(256) void k_tsk_part(const double* __restrict__ F, 
     }
 }
 
-// out[r][c] = C0[r][c] - sum over chunks (in order) of part[chunk][r][c];
-// sym: C0 symmetric with its lower triangle read.
-__global__ __launch_bounds__(kT) void k_tsk_fin(const double* __restrict__ part, int chunks, const double* __restrict__ C0,
-                                                int m, int q, bool sym, double* __restrict__ out) {
-    const int64_t total = (int64_t)m * q;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total; e += (int64_t)gridDim.x * kT) {
-        const int r = (int)(e / q), c = (int)(e % q);
-        double s = 0.0;
-        for (int t = 0; t < chunks; ++t) s += part[(size_t)t * total + e];
-        const double c0 = (sym && c > r) ? C0[(size_t)c * q + r] : C0[e];
-        out[e] = c0 - s;
+// out[r][c] = C0[r][c] - sum over chunks of part[chunk][r][c]; sym: C0
+// symmetric with its lower triangle read.
+constexpr int kFinParts = 16, kFinElems = kThreads / kFinParts;
+__global__ __launch_bounds__(kThreads) void k_tsk_fin(const double* __restrict__ part, int chunks,
+                                                      const double* __restrict__ C0, int m, int q, bool sym,
+                                                      double* __restrict__ out) {
+    __shared__ double sums[kFinParts][kFinElems];
+    const int64_t total = (int64_t)m * q, e = (int64_t)blockIdx.x * kFinElems + threadIdx.x % kFinElems;
+    const int g = threadIdx.x / kFinElems;
+    double s = 0.0;
+    if (e < total) {
+#pragma unroll 8
+        for (int t = g; t < chunks; t += kFinParts) s += part[(size_t)t * total + e];
     }
+    sums[g][threadIdx.x % kFinElems] = s;
+    __syncthreads();
+    if (g > 0 || e >= total) return;
+#pragma unroll
+    for (int k = 1; k < kFinParts; ++k) s += sums[k][threadIdx.x];
+    const int r = (int)(e / q), c = (int)(e % q);
+    const double c0 = (sym && c > r) ? C0[(size_t)c * q + r] : C0[e];
+    out[e] = c0 - s;
 }
 
 // ---------------------------------------------------------------------------
 // Cholesky of the m x m tip S (row-major, lower triangle read) in place by
-// one workgroup: the packed lower triangle in LDS, column by column (pivot
-// square root, column scaled, trailing triangle updated by all threads).
-// Writes L_S (strict upper part 0) and *info = 0, or the 1-based column of
-// the first non-positive (or NaN) pivot.
+// one workgroup.  Writes L_S (strict upper part 0) and *info = 0, or the
+// 1-based column of the first non-positive (or NaN) pivot.  The blocked
+// factorization on the matrix cores does not say which pivot failed: where one
+// did, S is factored again column by column (pivot square root, column scaled,
+// trailing triangle updated by all threads), which took 33 us at m = 40 when
+// every tip went that way.
 __device__ __forceinline__ int tri_at(int r, int c) { return r * (r + 1) / 2 + c; }
 __device__ __forceinline__ void tri_rc(int e, int& r, int& c) {
     r = (int)((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
@@ -156,12 +180,29 @@ __device__ __forceinline__ void tri_rc(int e, int& r, int& c) {
     c = e - r * (r + 1) / 2;
 }
 
-__global__ __launch_bounds__(256) void k_tip_chol(double* __restrict__ S, int m, unsigned long long* __restrict__ info) {
-    __shared__ double a[kTipMax * (kTipMax + 1) / 2];
+template <int NP, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_tip_chol(double* __restrict__ S, int m,
+                                                         unsigned long long* __restrict__ info) {
+    constexpr int NT = NW * kWave;
+    __shared__ double a[tiles::packed_lds_elems<NP>()];
+    __shared__ double invd[NP];
     __shared__ int fail;
+    static_assert(tiles::packed_lds_elems<NP>() >= NP * (NP + 1) / 2, "room for the packed triangle");
     const int tid = threadIdx.x;
+    if (tid == 0) fail = 0;
+    stage_lower_packed<NP, NT>(a, S, m, tid);
+    __syncthreads();
+    if (tiles::potrf_blocked<NP, NW>(a, invd, &fail)) {
+        for (int e = tid; e < m * m; e += NT) {
+            const int r = e / m, c = e % m;
+            S[e] = c <= r ? tiles::PackedLds::tile(a, r / 16, c / 16)[(r % 16) * tiles::kLDI + c % 16] : 0.0;
+        }
+        if (tid == 0) *info = 0;
+        return;
+    }
+    __syncthreads();
     const int tot = m * (m + 1) / 2;
-    for (int e = tid; e < tot; e += 256) {
+    for (int e = tid; e < tot; e += NT) {
         int r, c;
         tri_rc(e, r, c);
         a[e] = S[(size_t)r * m + c];
@@ -179,10 +220,10 @@ __global__ __launch_bounds__(256) void k_tip_chol(double* __restrict__ S, int m,
         __syncthreads();
         if (fail) break;
         const double dj = a[tri_at(j, j)];
-        for (int r = j + 1 + tid; r < m; r += 256) a[tri_at(r, j)] /= dj;
+        for (int r = j + 1 + tid; r < m; r += NT) a[tri_at(r, j)] /= dj;
         __syncthreads();
         const int t = m - j - 1;
-        for (int e = tid; e < t * (t + 1) / 2; e += 256) {
+        for (int e = tid; e < t * (t + 1) / 2; e += NT) {
             int rr, cc;
             tri_rc(e, rr, cc);
             const int r = j + 1 + rr, c = j + 1 + cc;
@@ -190,45 +231,59 @@ __global__ __launch_bounds__(256) void k_tip_chol(double* __restrict__ S, int m,
         }
         __syncthreads();
     }
-    for (int e = tid; e < m * m; e += 256) {
+    for (int e = tid; e < m * m; e += NT) {
         const int r = e / m, c = e % m;
         S[e] = c <= r ? a[tri_at(r, c)] : 0.0;
     }
     if (tid == 0) *info = (unsigned long long)fail;
 }
 
-// X2 (m x q) <- L_S^{-T} L_S^{-1} X2, one wavefront per column: lane r holds
-// rows r and r + 64; each step broadcasts the finished value by readlane.
+hipError_t launch_tip_chol(double* S, int m, unsigned long long* info, hipStream_t st) {
+    if (m <= 32) hipLaunchKernelGGL((k_tip_chol<32, 4>), dim3(1), dim3(4 * kWave), 0, st, S, m, info);
+    else if (m <= 64) hipLaunchKernelGGL((k_tip_chol<64, 4>), dim3(1), dim3(4 * kWave), 0, st, S, m, info);
+    else hipLaunchKernelGGL((k_tip_chol<128, 8>), dim3(1), dim3(8 * kWave), 0, st, S, m, info);
+    return hipGetLastError();
+}
+
+// X2 (m x q) <- L_S^{-T} L_S^{-1} X2, one wavefront per column, L_S in LDS (from
+// memory every step waited for its column: 21 us at m = 40): lane r holds rows
+// r and r + 64; each step broadcasts the finished value by readlane.
 __global__ __launch_bounds__(64) void k_tip_solve(const double* __restrict__ Ls, int m, double* __restrict__ X2,
                                                   int q) {
+    constexpr int LD = kTipMax + 1;
+    __shared__ double a[kTipMax * LD];
+    __shared__ double inv[kTipMax];
     const int col = blockIdx.x, lane = threadIdx.x;
     double x0 = lane < m ? X2[(size_t)lane * q + col] : 0.0;
     double x1 = lane + 64 < m ? X2[(size_t)(lane + 64) * q + col] : 0.0;
+#pragma unroll 8
+    for (int e = lane; e < m * m; e += 64) a[(e / m) * LD + e % m] = Ls[e];
+    __syncthreads();
+    for (int j = lane; j < m; j += 64) inv[j] = 1.0 / a[j * LD + j];
+    __syncthreads();
+    // rows past m: any finite factor row does, their values are never used
+    const int r0 = lane < m ? lane : m - 1, r1 = lane + 64 < m ? lane + 64 : m - 1;
     for (int j = 0; j < m; ++j) {
-        double xj = j < 64 ? readlane_d(x0, j) : readlane_d(x1, j - 64);
-        xj = xj / Ls[(size_t)j * m + j];
-        if (lane == j) x0 = xj;
-        if (lane + 64 == j) x1 = xj;
-        if (lane > j && lane < m) x0 = fma(-Ls[(size_t)lane * m + j], xj, x0);
-        if (lane + 64 > j && lane + 64 < m) x1 = fma(-Ls[(size_t)(lane + 64) * m + j], xj, x1);
+        const double xj = (j < 64 ? readlane_d(x0, j) : readlane_d(x1, j - 64)) * inv[j];
+        const double a0 = a[r0 * LD + j], a1 = a[r1 * LD + j];
+        x0 = lane == j ? xj : lane > j ? fma(-a0, xj, x0) : x0;
+        x1 = lane + 64 == j ? xj : lane + 64 > j ? fma(-a1, xj, x1) : x1;
     }
     for (int j = m - 1; j >= 0; --j) {
-        double xj = j < 64 ? readlane_d(x0, j) : readlane_d(x1, j - 64);
-        xj = xj / Ls[(size_t)j * m + j];
-        if (lane == j) x0 = xj;
-        if (lane + 64 == j) x1 = xj;
-        if (lane < j) x0 = fma(-Ls[(size_t)j * m + lane], xj, x0);
-        if (lane + 64 < j) x1 = fma(-Ls[(size_t)j * m + lane + 64], xj, x1);
+        const double xj = (j < 64 ? readlane_d(x0, j) : readlane_d(x1, j - 64)) * inv[j];
+        const double a0 = a[j * LD + r0], a1 = a[j * LD + r1];
+        x0 = lane == j ? xj : lane < j ? fma(-a0, xj, x0) : x0;
+        x1 = lane + 64 == j ? xj : lane + 64 < j ? fma(-a1, xj, x1) : x1;
     }
     if (lane < m) X2[(size_t)lane * q + col] = x0;
     if (lane + 64 < m) X2[(size_t)(lane + 64) * q + col] = x1;
 }
 
 // X1 (K x q) -= Z (K x m) X2 (m x q).
-__global__ __launch_bounds__(kT) void k_arrow_update(const double* __restrict__ Z, int64_t K, int m,
+__global__ __launch_bounds__(kThreads) void k_arrow_update(const double* __restrict__ Z, int64_t K, int m,
                                                      const double* __restrict__ X2, int q, double* __restrict__ X1) {
     const int64_t total = K * q;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total; e += (int64_t)gridDim.x * kT) {
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total; e += (int64_t)gridDim.x * kThreads) {
         const int64_t r = e / q;
         const int c = (int)(e % q);
         double acc = 0.0;
@@ -251,7 +306,7 @@ int tsk(const Allocator& al, const double* F, const double* Y, int64_t K, int m,
     const int tiles = ((m + 31) / 32) * ((q + 31) / 32);
     hipLaunchKernelGGL(k_tsk_part, dim3((unsigned)chunks, (unsigned)tiles), dim3(256), 0, st, F, Y, K, m, q, rows,
                        (double*)part);
-    hipLaunchKernelGGL(k_tsk_fin, dim3(grid_for((int64_t)m * q)), dim3(kT), 0, st, (const double*)part, chunks, C0, m, q,
+    hipLaunchKernelGGL(k_tsk_fin, dim3((unsigned)(((int64_t)m * q + kFinElems - 1) / kFinElems)), dim3(kThreads), 0, st, (const double*)part, chunks, C0, m, q,
                        sym, out);
     const hipError_t e = hipGetLastError();
     dev_free_async(al, part, st);
@@ -274,7 +329,7 @@ struct btc_banded_s {
 namespace {
 int band_pack(btc_banded s, const double* A_band, hipStream_t st) {
     const int64_t total = (2 * s->N2 - 1) * s->n2 * s->n2;
-    hipLaunchKernelGGL(k_band_pack, dim3(grid_for(total)), dim3(kT), 0, st, A_band, s->N, (int)s->n, (int)s->b, s->N2,
+    hipLaunchKernelGGL(k_band_pack, dim3(grid_for(total)), dim3(kThreads), 0, st, A_band, s->N, (int)s->n, (int)s->b, s->N2,
                        s->D2, s->E2);
     return hipGetLastError() == hipSuccess ? 0 : BTC_ERR_HIP;
 }
@@ -336,11 +391,11 @@ BTC_API int btc_banded_solve(btc_banded s, const double* B, double* X, int64_t n
         return BTC_ERR_OOM;
     double* B2 = (double*)mem;
     double* X2 = B2 + (size_t)rows2 * nrhs;
-    hipLaunchKernelGGL(k_pad_rows, dim3(grid_for(rows2 * nrhs)), dim3(kT), 0, st, B, rows, rows2, nrhs, B2);
+    hipLaunchKernelGGL(k_pad_rows, dim3(grid_for(rows2 * nrhs)), dim3(kThreads), 0, st, B, rows, rows2, nrhs, B2);
     int rc = hipGetLastError() == hipSuccess ? 0 : BTC_ERR_HIP;
     if (rc == 0) rc = btc_solve(s->h, B2, X2, nrhs, stream, info);
     if (rc == 0) {
-        hipLaunchKernelGGL(k_copy, dim3(grid_for(rows * nrhs)), dim3(kT), 0, st, (const double*)X2, rows * nrhs, X);
+        hipLaunchKernelGGL(k_copy, dim3(grid_for(rows * nrhs)), dim3(kThreads), 0, st, (const double*)X2, rows * nrhs, X);
         rc = hipGetLastError() == hipSuccess ? 0 : BTC_ERR_HIP;
     }
     dev_free_async(s->alloc, mem, st);
@@ -386,14 +441,13 @@ int arrow_tip(btc_arrow s, const double* F, const double* C, hipStream_t st) {
     const int m = (int)s->m;
     s->last = st;
     if (m == 0) return 0;
-    hipLaunchKernelGGL(k_copy, dim3(grid_for(K * m)), dim3(kT), 0, st, F, K * m, s->F);
+    hipLaunchKernelGGL(k_copy, dim3(grid_for(K * m)), dim3(kThreads), 0, st, F, K * m, s->F);
     if (hipGetLastError() != hipSuccess) return BTC_ERR_HIP;
     int rc = btc_solve(s->h, s->F, s->Z, m, st, nullptr);
     if (rc == BTC_ERR_NOT_SPD) return 0;  // Psi broke down: btc_arrow_status reports it
     if (rc == 0) rc = tsk(s->alloc, s->F, s->Z, K, m, m, C, true, s->Ls, st);
     if (rc != 0) return rc;
-    hipLaunchKernelGGL(k_tip_chol, dim3(1), dim3(256), 0, st, s->Ls, m, s->tip_info);
-    return hipGetLastError() == hipSuccess ? 0 : BTC_ERR_HIP;
+    return launch_tip_chol(s->Ls, m, s->tip_info, st) == hipSuccess ? 0 : BTC_ERR_HIP;
 }
 }  // namespace
 
@@ -468,7 +522,7 @@ BTC_API int btc_arrow_solve(btc_arrow s, const double* B, double* X, int64_t nrh
     rc = tsk(s->alloc, s->F, X, K, m, q, B + (size_t)K * q, false, X2, st);  // b2 - F^T y
     if (rc != 0) return rc;
     hipLaunchKernelGGL(k_tip_solve, dim3((unsigned)q), dim3(64), 0, st, (const double*)s->Ls, m, X2, q);
-    hipLaunchKernelGGL(k_arrow_update, dim3(grid_for(K * q)), dim3(kT), 0, st, (const double*)s->Z, K, m,
+    hipLaunchKernelGGL(k_arrow_update, dim3(grid_for(K * q)), dim3(kThreads), 0, st, (const double*)s->Z, K, m,
                        (const double*)X2, q, X);
     return hipGetLastError() == hipSuccess ? 0 : BTC_ERR_HIP;
 }
