@@ -531,10 +531,27 @@ inline int launch_factor(btc_handle h, const double* A_diag, const double* A_off
 // per node, nothing to wait for), or the levels from l0 up in one launch
 // (k_sweep_flow: the workgroups wait for each other's flags, which saves a
 // launch, the start of its workgroups and the first loads of its blocks per
-// level).  A level of the first kind costs nothing more while it has work for
-// the whole GPU; measured on one instance (FP64, n = 96, m = 1), levels with
-// at most kFlowNodes nodes are faster in one launch.
-constexpr int64_t kFlowNodes = 1024;
+// level, but costs a ticket per workgroup and lets few of them wait at once).
+// Levels with at most flow_limit() nodes are faster in one launch.
+// Measured, both sweeps of one instance (m = 1, FP64) with a limit of 1024 / 256
+// / 128 / 64 nodes: N = 2000, n = 16: 103 / 67 / 63 / 63 us; N = 1000, n = 32: 81 /
+// 70 / 64 / 65; N = 400, n = 64: 80 / 80 / 74 / 78; N = 2000, n = 64: 137 / 132 /
+// 127 / 129; N = 2000, n = 96: 237 / 235 / 235 / 243; N = 200, n = 8: 42 / 42 / 42 /
+// 44.  Refined solves launch the rounds after the last as well: N = 1000, n =
+// 32: 235 / 222 / 224 / 236; N = 800, n = 64: 292 / 290 / 293 / 306.  Above n = 96
+// a level of some hundred nodes fills the GPU with block loads either way: N =
+// 1023, n = 128, m = 5: 290 with 1024, 304 with 128.
+inline int64_t flow_limit(int32_t prec, int64_t n) {
+    return n > 96 ? 1024 : is_mixed(prec) ? 256 : 128;
+}
+// Many instances in one call: the limit counts the nodes of all of them, in
+// launches per block size, and a call of its own costs host time.  Measured
+// with 1024 / 4096 / 16 384 nodes: 40 instances of N up to 300, mixed 3 088 / 2 332 /
+// 2 342 us, FP64 1 383 / 1 052 / 1 066; 200 up to 1000, mixed 9 446 / 9 608 / 8 719,
+// FP64 4 407 / 4 090 / 4 063; 512 up to 2048, FP64 15 473 / 14 999 / 14 838.
+constexpr int64_t kFlowNodesBatch = 16384;
+// Served instances, which share launches as they happen to meet.
+constexpr int64_t kFlowNodesServed = 1024;
 // Sweep launch shapes (tune key BTC_TUNE_SWEEP_SHAPE): 0 as above, 1 one
 // launch per level, 2 all levels in one launch.
 inline int sweep_shape(int32_t prec, int64_t n) {
@@ -543,10 +560,10 @@ inline int sweep_shape(int32_t prec, int64_t n) {
 
 // First level of the range in one launch (levels: none): nodes[l] nodes at
 // level l.
-inline int flow_start(const int64_t* nodes, int levels, int shape) {
+inline int flow_start(const int64_t* nodes, int levels, int shape, int64_t limit) {
     if (shape == 1) return levels;
     int l = 0;
-    while (shape != 2 && l < levels && nodes[l] > kFlowNodes) ++l;
+    while (shape != 2 && l < levels && nodes[l] > limit) ++l;
     return l + 1 < levels ? l : levels;  // one level alone is no range
 }
 
@@ -558,10 +575,10 @@ inline int range_bounds(int flow, int levels, int* bounds) {
     if (flow < levels) bounds[++r] = levels;
     return r;
 }
-inline int sweep_ranges(int64_t N, int levels, int* bounds, int shape) {
+inline int sweep_ranges(int64_t N, int levels, int* bounds, int shape, int64_t limit) {
     int64_t nodes[66];
     for (int l = 0; l < levels; ++l) nodes[l] = level_nodes(N, l);
-    return range_bounds(flow_start(nodes, levels, shape), levels, bounds);
+    return range_bounds(flow_start(nodes, levels, shape, limit), levels, bounds);
 }
 
 // Nodes of the levels l0 .. l1-1.
@@ -612,7 +629,8 @@ inline hipError_t sweeps(btc_handle h, const btc::SweepDesc<T>& d, hipStream_t s
     int b[66];
     // the levels of the multi-stage order (all of them, or the first k), in
     // ranges; a k-stage order solves along its chain in between
-    const int r = sweep_ranges(h->N, h->nd_levels, b, d.flow ? sweep_shape(h->precision, h->n) : 1);
+    const int r = sweep_ranges(h->N, h->nd_levels, b, d.flow ? sweep_shape(h->precision, h->n) : 1,
+                               flow_limit(h->precision, h->n));
     for (int k = 0; k < r; ++k) {
         hipError_t e = sweep_range(h, L, b[k], b[k + 1], false, st);
         if (e != hipSuccess) return e;

@@ -995,7 +995,7 @@ BTC_API int btc_solve_batched(btc_runner r, int32_t count, const btc_handle* h, 
         for (int l = 0; l < h[k]->levels; ++l) nodes[l] += level_nodes(h[k]->N, l);
     for (int32_t k = 0; k < count; ++k) {
         bounds[(size_t)k].resize(66);
-        const int flow = flow_start(nodes, h[k]->levels, sweep_shape(h[k]->precision, h[k]->n));
+        const int flow = flow_start(nodes, h[k]->levels, sweep_shape(h[k]->precision, h[k]->n), kFlowNodesBatch);
         const int nr = range_bounds(flow, h[k]->levels, bounds[(size_t)k].data());
         bounds[(size_t)k].resize((size_t)nr + 1);
         max_ranges = std::max(max_ranges, nr);

@@ -281,7 +281,7 @@ void build_plan(btc_server s, Req* r, Client& c) {
     if (!s->opt.sweep_ranges)
         for (int l = 0; l <= L; ++l) b[l] = l;
     else
-        nr = sweep_ranges(h->N, L, b, sweep_shape(h->precision, h->n));
+        nr = sweep_ranges(h->N, L, b, sweep_shape(h->precision, h->n), kFlowNodesServed);
     auto push = [&](const btc_step& t, bool par) {
         r->plan.push_back(t);
         r->joint.push_back(0);

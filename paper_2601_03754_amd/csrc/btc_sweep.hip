@@ -665,9 +665,10 @@ template <int NP, class T, int NG, bool BWD>
 __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<SweepDesc<T>> L) {
     __shared__ T lds[Team<NP, T, NG>::LDS(BWD)];
     __shared__ int slot;
-    // an instance alone in its launch skips as a whole, without taking tickets
-    // (2048 of them in turn: 25 us instead of 5)
-    if (!L.items && skip_item(L.single)) return;
+    // a refinement that is done, alone in its launch, skips as a whole, without
+    // taking tickets (2048 of them in turn: 25 us instead of 5)
+    const bool whole = !L.items && L.single.skip;
+    if (whole && skip_item(L.single)) return;
     if (threadIdx.x == 0) {
         const int t = __hip_atomic_fetch_add(L.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t == (int)gridDim.x - 1) flag_store(L.ticket, 0);
@@ -689,7 +690,7 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<Swe
         if ((N >> lvl) < left) --lvl;
         kk = p - (N - (N >> lvl));
     }
-    if (L.items && skip_item(P)) return;
+    if (!whole && skip_item(P)) return;
     const Flow fl{P.flow, l0, l1};
     if constexpr (BWD)
         bwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
