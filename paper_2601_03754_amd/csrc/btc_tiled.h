@@ -1,21 +1,22 @@
-// Tile-parallel factorization level step for large blocks (padded sizes 96
-// and 128), FP64 or mixed precision.
+// Tile-parallel factorization level step, FP64 or mixed precision: for large
+// blocks (padded sizes 96 and 128), at 32 and 64 a variant the autotuner may
+// choose.
 //
 // A node whose four n x n blocks no longer fit in LDS together is split over
 // three launches per level (the same per-node algebra as the single-kernel
 // paths, Algorithm 4):
 //   K1  deferred syrk: S_i -= T'^T T' and S_{i+s} -= T''^T T'', one 256-thread
 //       workgroup per 32 x 32 lower tile (panels of T' staged in LDS)
-//   K2  one workgroup (8 wavefronts; 4 at padded size 128) per node: the
-//       whole pivot block in LDS (FP64), blocked
-//       Cholesky in 16-column panels (diagonal tiles factored and inverted by
-//       one wavefront, panel and trailing updates on the matrix cores), then
-//       R_i = C_{i+s,i} L_ii^{-T} and T_i = L_ii^{-1} C_{i,i-s} strip by strip
-//       (one 16-row or 16-column strip per wavefront at a time, blocked
-//       substitution with the inverted diagonal tiles, all products MFMA,
-//       the solved tiles kept in registers as the products' B operand)
-//   K4  one 256-thread workgroup per 32 x 32 tile of S_{i+s} -= R_i R_i^T
-//       (lower tiles) and of the fill -R_i T_i
+//   K2  one workgroup (8 wavefronts from padded size 96 on, 4 below; one per
+//       strip in small launches) per node: the whole pivot block in LDS (FP64),
+//       blocked Cholesky in 16-column panels (the panel's tiles in registers,
+//       4-column steps on the matrix cores, which also invert the diagonal
+//       tiles), then R_i = C_{i+s,i} L_ii^{-T} and T_i = L_ii^{-1} C_{i,i-s}
+//       strip by strip (one 16-row or 16-column strip per wavefront at a time,
+//       blocked substitution with the inverted diagonal tiles, all products
+//       MFMA, the solved tiles kept in registers as the products' B operand)
+//   K4  S_{i+s} -= R_i R_i^T (lower tiles) and the fill -R_i T_i: from 192
+//       nodes on one workgroup per node, below one per 32 x 32 tile
 // In mixed precision the Schur complements and K2 stay FP64 (its solves too;
 // R_i and T_i are rounded to FP32 when stored) and the products of K1 and K4
 // run on FP32 matrix cores (FP32 factor storage); the BF16
@@ -261,8 +262,7 @@ __global__ __launch_bounds__(256) void k_tiled_syrk_deferred(Launch<FactorDesc> 
 // 64 four nodes of four wavefronts per CU beat five (whose register budget
 // of 96 spills) and three of eight; at 96 two of eight beat three of four,
 // whose strips take three rounds; at 128, one node per CU, eight wavefronts
-// beat four: 16 strips in two rounds instead of four, N = 4096 level 0
-// 1 492 -> 1 376 us FP64, 1 148 -> 964 us mixed).
+// beat four: 16 strips in two rounds instead of four).
 template <int NP>
 constexpr int k2_waves() { return NP >= 96 ? 8 : 4; }
 // The register budget is held to the workgroups per CU (the second launch
@@ -272,10 +272,10 @@ constexpr int k2_blocks() { return NP <= 64 ? 4 : NP <= 96 ? 2 : 1; }
 
 // A launch of at most one node per compute unit is bound by one node's
 // latency, not by the throughput of nodes sharing a unit: it takes one
-// wavefront per strip, so that all strips are solved in one round (padded
-// size 96: twelve wavefronts, measured at N = 4096: 38 against 43 us per
-// launch of the upper levels, FP64; 44 against 53 mixed; padded size 64:
-// eight).
+// wavefront per strip, so that all strips are solved in one round (measured
+// when the rule was made, N = 4096, upper levels, padded size 96, twelve
+// wavefronts against eight: 38 / 43 us FP64, 44 / 53 mixed; now 29 and 30 with
+// twelve; padded size 64 eight, 128 sixteen).
 constexpr int kK2LatencyWaves = 12;
 constexpr int64_t kK2LatencyItems = 256;
 template <int NP>
@@ -373,10 +373,23 @@ __global__ __launch_bounds__(NW * kWave, (NB * NW + 3) / 4) void k_tiled_potrf_t
             } else {
                 F x;
                 buf_ld(x, rf, elem_off<F>(gr, gc, n, ok));
-                acc[v] = x;
+                if constexpr (MIXED) acc[v] = __hiloint2double(0, __float_as_int(x));
+                else acc[v] = x;
             }
         }
         return acc;
+    };
+    // a loaded tile as values: FP32 couplings are converted where they are used
+    // (converted at the load they were waited for there, two tiles early: n =
+    // 96, 1024 nodes 139 -> 108 us, one node 34.3 -> 30.0; n = 128 309 -> 241, 54.5
+    // -> 49.7)
+    auto values = [&](Acc t) {
+        if constexpr (MIXED) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                t[v] = lvl == 0 ? t[v] : (double)__int_as_float(__double2loint(t[v]));
+        }
+        return t;
     };
     constexpr int NS = (2 * NT16 + NW - 1) / NW;  // strips per wavefront (w, w + NW, ...)
     stage_lower_packed<NP, NW * kWave>(sS, src, n, tid);
@@ -405,7 +418,8 @@ __global__ __launch_bounds__(NW * kWave, (NB * NW + 3) / 4) void k_tiled_potrf_t
         if (NT16 > 1) nx1 = load_coupling(isR, t, 1, true);
 #pragma unroll
         for (int p = 0; p < NT16; ++p) {
-            Acc acc = isR ? rows_to_acc(nx0) : nx0;
+            const Acc c0 = values(nx0);
+            Acc acc = isR ? rows_to_acc(c0) : c0;
             nx0 = nx1;
             if (p + 2 < NT16) nx1 = load_coupling(isR, t, p + 2, true);
             // acc -= L_p,qq X_qq (A from LDS, B = X_qq's registers)
