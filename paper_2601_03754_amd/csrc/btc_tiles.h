@@ -149,7 +149,7 @@ struct PanelStep {
     double y1, y2, y3;  // minus the factored column's blocks below the diagonal, as A operands
 };
 template <int KB, class V>
-__device__ __forceinline__ PanelStep panel_diag(V& Q, double& myinv, bool& ok, int lane) {
+__device__ __forceinline__ PanelStep panel_diag(V& Q, bool& ok, int lane) {
     const int r = lane & 15, c = lane >> 4, i = lane & 3;
     const double q = Q[KB];
     const double d00 = readlane_d(q, 4 * KB), d10 = readlane_d(q, 4 * KB + 1), d20 = readlane_d(q, 4 * KB + 2),
@@ -171,9 +171,14 @@ __device__ __forceinline__ PanelStep panel_diag(V& Q, double& myinv, bool& ok, i
     const double x3 = fma(-l32, x2, fma(-l31, x1, fma(-l30, x0, c == 3 ? 1.0 : 0.0))) * r3;
     PanelStep s{};
     s.m = i == 0 ? x0 : i == 1 ? x1 : i == 2 ? x2 : x3;
-    if ((r >> 2) == KB) myinv = i == 0 ? r0 : i == 1 ? r1 : i == 2 ? r2 : r3;
     const double xq = mma4(s.m, q, 0.0);
-    const double x = r >= 4 * KB + c ? xq : 0.0;
+    // the block's own rows are the factor as computed above: Q M^T would repeat
+    // them with an error that grows with the block's condition
+    const double l0 = i == 0 ? d00 * r0 : i == 1 ? l10 : i == 2 ? l20 : l30;
+    const double l1 = i == 1 ? p1 * r1 : i == 2 ? l21 : l31;
+    const double l2 = i == 2 ? p2 * r2 : l32;
+    const double own = c == 0 ? l0 : c == 1 ? l1 : c == 2 ? l2 : p3 * r3;
+    const double x = (r >> 2) == KB ? own : xq;
     Q[KB] = x;
     if constexpr (KB < 3) {
         // the next diagonal block first
@@ -236,7 +241,6 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
     const int lane = tid & 63;
     const int r = lane & 15, c = lane >> 4;
     double Q[4], E[4], S[TB][4];
-    double myinv = 1.0;
     auto load_tile = [&](double (&t)[4], const double* T) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) t[j] = T[r * LT + 4 * j + c];
@@ -246,10 +250,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         bool ok = true;
 #pragma unroll
         for (int j = 0; j < 4; ++j) E[j] = 4 * j + c == r ? 1.0 : 0.0;
-        panel_rest<TB, 0>(E, S, panel_diag<0>(Q, myinv, ok, lane));
-        panel_rest<TB, 1>(E, S, panel_diag<1>(Q, myinv, ok, lane));
-        panel_rest<TB, 2>(E, S, panel_diag<2>(Q, myinv, ok, lane));
-        panel_rest<TB, 3>(E, S, panel_diag<3>(Q, myinv, ok, lane));
+        panel_rest<TB, 0>(E, S, panel_diag<0>(Q, ok, lane));
+        panel_rest<TB, 1>(E, S, panel_diag<1>(Q, ok, lane));
+        panel_rest<TB, 2>(E, S, panel_diag<2>(Q, ok, lane));
+        panel_rest<TB, 3>(E, S, panel_diag<3>(Q, ok, lane));
         if (!ok && lane == 0) *fail = 1;
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
@@ -259,7 +263,8 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
 #pragma unroll
             for (int j = 0; j < 4; ++j) T[r * LT + 4 * j + c] = S[t][j];
         }
-        if (w == 0 && lane < kT) invd[q * kT + lane] = myinv;
+        // the inverse's diagonal
+        if (w == 0 && c == (r & 3)) invd[q * kT + r] = r < 4 ? E[0] : r < 8 ? E[1] : r < 12 ? E[2] : E[3];
     };
     // wavefront 0's factored diagonal tile q and its inverse into place
     auto place_diag = [&](int q) {
