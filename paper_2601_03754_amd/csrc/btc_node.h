@@ -256,29 +256,26 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
             wave_lds_sync();
         }
     };
-    // S -= T^T T of the wavefront's pairs: tile columns own and other(d)
+    // S -= T^T T of the wavefront's pairs, the products summed before they are
+    // subtracted (subtracted from S one after the other, each would be rounded
+    // to S's magnitude): tile columns own and other(d)
     // (NTL 2: loaded by this wavefront too; NTL 4: from the images of the
     // wavefronts that carry them)
     auto syrk = [&](d4 (&x)[D], const F (&own)[NTL][4], const F (&oth)[NTL][4], const F* img) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             if (!pair_on(d)) continue;
-            Acc acc;
-            if constexpr (MODE == 0) acc = x[d];
-            else acc = Acc{0.f, 0.f, 0.f, 0.f};
+            Acc acc = {};
 #pragma unroll
             for (int p = 0; p < NTL; ++p) {
                 F o[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     o[v] = d == 0 ? own[p][v] : NTL >= 3 ? img[(other(d) * NTL + p) * kImg + po[v]] : oth[p][v];
-                PR::template tile<MODE == 0>(acc, o, own[p]);
+                PR::template tile<false>(acc, o, own[p]);
             }
-            if constexpr (MODE == 0) x[d] = acc;
-            else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) x[d][v] -= (double)acc[v];
-            }
+            for (int v = 0; v < 4; ++v) x[d][v] -= (double)acc[v];
         }
     };
     auto put_img = [&](F* img, const F (&x)[NTL][4]) {
@@ -542,24 +539,17 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             if (!pair_on(d)) continue;
-            Acc acc;
-            if constexpr (MODE == 0) acc = sep[d];
-            else acc = Acc{0.f, 0.f, 0.f, 0.f};
+            Acc acc = {};
 #pragma unroll
             for (int p = 0; p < NTL; ++p) {
                 if (!full && p >= nt) break;
                 F x[4], y[4];
                 load_op(x, iR + (other(d) * NTL + p) * kImg, X[0][0]);
                 load_op(y, iR + (w * NTL + p) * kImg, X[0][0]);
-                PR::template tile<MODE == 0>(acc, x, y);
+                PR::template tile<false>(acc, x, y);
             }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                double e;
-                if constexpr (MODE == 0) e = acc[v];
-                else e = sep[d][v] - (double)acc[v];
-                buf_st(e, rp, at(d, v), v * step(d));
-            }
+            for (int v = 0; v < 4; ++v) buf_st(sep[d][v] - (double)acc[v], rp, at(d, v), v * step(d));
         }
     };
     Acc f[NTL];

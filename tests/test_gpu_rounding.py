@@ -1,5 +1,6 @@
 """Rounding of the FP64 path: the solve's componentwise backward error on
-ill-conditioned blocks."""
+ill-conditioned blocks, and Schur sums of products far below the block they
+are subtracted from."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +58,25 @@ def test_backward_error_of_ill_conditioned_blocks(n, digits):
     f.close()
     levels = N.bit_length()
     assert backward_error(D, E, B, X) <= 3 * (2 * levels + 1) * n * U
+
+
+# the Schur sum of block k is formed by: the separator update of its left
+# neighbour, its own deferred update, the deferred update its left neighbour
+# applies for it
+@pytest.mark.parametrize("N,coupling,k", [(2, 1, 2), (3, 2, 2), (5, 4, 4)])
+@pytest.mark.parametrize("n", [48, 64])
+def test_schur_sums_of_small_products(n, N, coupling, k):
+    """D_i = I and one coupling block of entries 2^-28: S_k = I - n 2^-56, whose
+    first element is representable.  Subtracted one at a time (or four) the
+    products of 2^-56 would each be lost against 1.  L_11^2 then is 1 - n 2^-56
+    to the four roundoffs of a square of a square root."""
+    from paper_2601_03754_amd import btc
+
+    D = np.broadcast_to(np.eye(n), (N, n, n)).copy()
+    E = np.zeros((N - 1, n, n))
+    E[coupling - 1] = 2.0 ** -28
+    f = btc.Factor(dev(D), dev(E))
+    L = f.export()[0][k - 1]
+    f.close()
+    S = np.longdouble(1) - np.longdouble(n) * np.longdouble(2) ** -56
+    assert abs(np.longdouble(L[0, 0]) ** 2 - S) <= 4.5 * U
