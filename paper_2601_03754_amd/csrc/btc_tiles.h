@@ -12,6 +12,7 @@
 #pragma once
 
 #include "btc_device.h"
+#include "btc_failword.h"
 
 namespace btc {
 namespace tiles {
@@ -221,8 +222,9 @@ __device__ __forceinline__ void panel_rest(V& E, V (&S)[TB], const PanelStep& s)
 // until the barrier (the other panel wavefronts read the unfactored tile).
 // On return: L in the lower triangle (tiles above the diagonal untouched),
 // 1/L_jj in invd, the inverse of each diagonal tile transposed in its strict
-// upper part.  *fail (LDS, 0 on entry) becomes 1 on a non-positive or NaN
-// pivot; the result is then false for every thread.
+// upper part.  *fail (LDS, 0 on entry) becomes the mark of the first panel with a
+// non-positive or NaN pivot; the result is then false for every thread, after the
+// same barrier.
 template <int NP, int NW>
 __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __restrict__ invd, int* fail) {
     using Lay = PackedLds;
@@ -254,7 +256,7 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         panel_rest<TB, 1>(E, S, panel_diag<1>(Q, ok, lane));
         panel_rest<TB, 2>(E, S, panel_diag<2>(Q, ok, lane));
         panel_rest<TB, 3>(E, S, panel_diag<3>(Q, ok, lane));
-        if (!ok && lane == 0) *fail = 1;
+        if (!ok && lane == 0) __hip_atomic_store(fail, panel_mark(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             const int ta = q + 1 + TB * w + t;
@@ -283,6 +285,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         mma_tile<LT, LT, false, true, true>(acc, Lay::tile(A, ta, p), 0, 0, Lay::tile(A, tb, p), 0, 0, kT);
         acc_store_lds<LT>(acc, Tab, 0, 0);
     };
+    // (after panel q's barrier)
+    auto broke_down = [&](int q) {
+        return panel_failed(__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), q);
+    };
     if (w < pwaves(0)) {
         load_tile(Q, Lay::tile(A, 0, 0));
 #pragma unroll
@@ -291,7 +297,7 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         factor(0);
     }
     __syncthreads();
-    if (*fail) return false;
+    if (broke_down(0)) return false;
 #pragma unroll 1
     for (int p = 0; p + 1 < NTL; ++p) {
         const int q = p + 1;
@@ -328,7 +334,7 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
             }
         }
         __syncthreads();
-        if (*fail) return false;
+        if (broke_down(q)) return false;
     }
     place_diag(NTL - 1);
     __syncthreads();
