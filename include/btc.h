@@ -446,7 +446,9 @@ BTC_API void btc_graph_destroy(btc_graph g);
  * (kernel variants and the strategy choices of btc_autotune_strategy) is
  * read from that file when the library first consults it, and written back
  * after every btc_tune_set / btc_autotune / btc_autotune_strategy (text, one
- * entry per line).
+ * entry per line, the first naming the format).  The factor's two variants at
+ * n 33..64 once had each other's numbers; files without a format line may hold
+ * either numbering, and their lines for these keys are ignored.
  * Other keys have the single variant 0 (btc_tune_set accepts only 0 there).
  * btc_autotune times every variant of the handle's tunable families on the
  * caller's matrix (reps timed repetitions after one warm-up each, per-level

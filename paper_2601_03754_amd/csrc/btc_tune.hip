@@ -36,9 +36,13 @@ std::map<std::tuple<int, int, int, int>, int> g_tune;
 std::map<std::tuple<int, int64_t, int>, std::pair<int32_t, int32_t>> g_strategy;
 bool g_loaded = false;
 
-// The table file named by BTC_TUNE_CACHE: lines "v op kind np bucket
-// variant" and "s precision N np strategy stages".  Called with the lock
-// held.
+// The table file named by BTC_TUNE_CACHE: a line "f format", then lines "v op
+// kind np bucket variant" and "s precision N np strategy stages".  Format 2
+// numbers the factor's variants at padded size 64 as btc.h does; files without
+// the line numbered them the other way round or the same way, depending on the
+// library that wrote them, so their lines for those keys say nothing and are
+// left out.  Called with the lock held.
+constexpr int kCacheFormat = 2;
 void load_cache_locked() {
     if (g_loaded) return;
     g_loaded = true;
@@ -47,11 +51,14 @@ void load_cache_locked() {
     FILE* f = fopen(path, "r");
     if (!f) return;
     char tag[4];
+    int format = 1;
     while (fscanf(f, "%3s", tag) == 1) {
         if (tag[0] == 'v') {
             int op, kind, np, bucket, variant;
             if (fscanf(f, "%d %d %d %d %d", &op, &kind, &np, &bucket, &variant) != 5) break;
-            g_tune[std::make_tuple(op, kind, np, bucket)] = variant;
+            if (format >= 2 || op != BTC_OP_FACTOR || np != 64) g_tune[std::make_tuple(op, kind, np, bucket)] = variant;
+        } else if (tag[0] == 'f') {
+            if (fscanf(f, "%d", &format) != 1 || format > kCacheFormat) break;
         } else if (tag[0] == 's') {
             int prec, np, strategy, stages;
             long long N;
@@ -75,6 +82,7 @@ void save_tune_cache() {
     const std::string tmp = std::string(path) + ".tmp";
     FILE* f = fopen(tmp.c_str(), "w");
     if (!f) return;
+    fprintf(f, "f %d\n", kCacheFormat);
     for (auto& kv : g_tune)
         fprintf(f, "v %d %d %d %d %d\n", std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first),
                 std::get<3>(kv.first), kv.second);
