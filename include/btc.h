@@ -440,8 +440,8 @@ BTC_API void btc_graph_destroy(btc_graph g);
  *     dependency-chain group, 1 one (identical results)
  *   BTC_TUNE_SWEEP_SHAPE, any precision, any n (level ignored): the launch
  *     shape of both sweeps: 0 one launch per level for levels of many nodes,
- *     the levels above them in one launch, 1 one launch per level, 2 all
- *     levels in one launch; identical results
+ *     the levels above them in one launch, 1 one launch per level, 2 as 0,
+ *     the shared launch starting one level lower; identical results
  * With the environment variable BTC_TUNE_CACHE naming a file, the table
  * (kernel variants and the strategy choices of btc_autotune_strategy) is
  * read from that file when the library first consults it, and written back

@@ -553,7 +553,9 @@ constexpr int64_t kFlowNodesBatch = 16384;
 // Served instances, which share launches as they happen to meet.
 constexpr int64_t kFlowNodesServed = 1024;
 // Sweep launch shapes (tune key BTC_TUNE_SWEEP_SHAPE): 0 as above, 1 one
-// launch per level, 2 all levels in one launch.
+// launch per level, 2 the shared launch starting at twice the limit, one level
+// lower (all levels of a large batch in one launch would make its sweeps four
+// times slower: a ticket and a wait per node).
 inline int sweep_shape(int32_t prec, int64_t n) {
     return tune_variant(BTC_TUNE_SWEEP_SHAPE, is_mixed(prec) ? 1 : 0, btc::padded_block((int)n), 0);
 }
@@ -562,8 +564,9 @@ inline int sweep_shape(int32_t prec, int64_t n) {
 // level l.
 inline int flow_start(const int64_t* nodes, int levels, int shape, int64_t limit) {
     if (shape == 1) return levels;
+    if (shape == 2) limit *= 2;
     int l = 0;
-    while (shape != 2 && l < levels && nodes[l] > limit) ++l;
+    while (l < levels && nodes[l] > limit) ++l;
     return l + 1 < levels ? l : levels;  // one level alone is no range
 }
 

@@ -1,0 +1,54 @@
+"""Launch shapes of the sweeps in calls of many nodes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2601_03754_amd import inputs
+
+pytestmark = pytest.mark.gpu
+SHAPE, FORWARD, BACKWARD = 6, 1, 2
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_wide_levels_of_a_batch_keep_launches_of_their_own(precision):
+    """Shape 2 starts the shared launch one level lower than shape 0; the levels
+    below still have a launch each (kind 0 / 1 of the launch profile, the
+    shared one kind 2 / 3), and the results stay the same."""
+    from paper_2601_03754_amd import btc
+
+    N, n = 140001, 5
+    pr = inputs.block_tridiag(N, n, seed=5)
+    D, E, B = dev(pr.D), dev(pr.E), dev(pr.B)
+    before = btc.btc_tune_get(SHAPE, precision, n, 0)
+    launches, out = {}, {}
+    try:
+        for shape in (0, 1, 2):
+            btc.btc_tune_set(SHAPE, precision, n, 0, shape)
+            r = btc.Runner()
+            h = btc.btc_create(N, n, precision)
+            X = torch.empty_like(B)
+            r.factor_batched([h], [D], [E])
+            r.profile(FORWARD)
+            r.solve_batched([h], [B], [X])
+            stats = r.profile_read()
+            rounds = 1 if precision == 0 else 5
+            launches[shape] = {k: sum(s["launches"] for s in stats if s["op"] == FORWARD and s["kind"] == k) / rounds
+                               for k in (precision, 2 + precision)}
+            out[shape] = X.cpu().numpy()
+            btc.btc_destroy(h)
+            r.close()
+    finally:
+        btc.btc_tune_set(SHAPE, precision, n, 0, before)
+    levels = N.bit_length()
+    own = {s: launches[s][precision] for s in launches}
+    shared = {s: launches[s][2 + precision] for s in launches}
+    assert (own[1], shared[1]) == (levels, 0)
+    assert shared[0] == shared[2] == 1 and own[2] == own[0] - 1 >= 1
+    assert oracle.relres(pr.D, pr.E, out[0], pr.B) <= (1e-12 if precision == 0 else 1e-10)
+    for s in (1, 2):
+        assert np.array_equal(out[s], out[0])
