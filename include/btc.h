@@ -259,9 +259,8 @@ BTC_API void btc_destroy(btc_handle h);
 
 /*
  * btc_footprint_bytes -- device bytes a handle of this shape holds after one
- * solve with nrhs right-hand sides (for admission control), not counting the
- * 8 (N + 1) bytes of synchronisation words that btc_solve takes on its first
- * call.  0 on invalid arguments.
+ * solve with nrhs right-hand sides (for admission control).  0 on invalid
+ * arguments.
  */
 BTC_API size_t btc_footprint_bytes(int64_t N, int64_t n, int32_t precision, int64_t nrhs);
 

@@ -79,7 +79,7 @@ BTC_API size_t btc_footprint_bytes(int64_t N, int64_t n, int32_t precision, int6
     if (N < 1 || n < 1 || n > BTC_MAX_BLOCK || nrhs < 0) return 0;
     if (precision != BTC_FP64 && !is_mixed(precision)) return 0;
     size_t b = factor_bytes(N, n, precision) + sizeof(unsigned long long);
-    if (nrhs > 0) b += workspace_bytes(N, n, precision, nrhs);
+    if (nrhs > 0) b += handle_workspace_bytes(N, n, precision, nrhs);
     return b;
 }
 
@@ -543,9 +543,9 @@ BTC_API int btc_solve(btc_handle h, const double* B, double* X, int64_t nrhs, vo
         if (rc != BTC_OK) return rc;
     }
     if (own) {
-        rc = ensure_flow(h, st);
-        if (rc != BTC_OK) return rc;
         const Workspace w = carve(h, h->ws_m);  // one layout per allocation
+        rc = clear_words(h, w, st);
+        if (rc != BTC_OK) return rc;
         h->stream = st;
         rc = solve_with(h, w, B, X, nrhs, st, info);
         if (!h->ws_ev && hipEventCreateWithFlags(&h->ws_ev, hipEventDisableTiming) != hipSuccess) h->ws_ev = nullptr;
@@ -555,12 +555,11 @@ BTC_API int btc_solve(btc_handle h, const double* B, double* X, int64_t nrhs, vo
     }
     void* mem = nullptr;
     const Allocator a = current_allocator();
-    const size_t ws = (workspace_bytes(h->N, h->n, h->precision, nrhs) + 255) & ~(size_t)255;
-    hipError_t e = dev_alloc_async(a, &mem, ws + flow_bytes(h->N), st);
+    hipError_t e = dev_alloc_async(a, &mem, handle_workspace_bytes(h->N, h->n, h->precision, nrhs), st);
     if (e != hipSuccess) return to_code(e);
     Workspace w = carve_at(mem, h->N, h->n, h->precision, nrhs);
-    w.flow = (int*)((char*)mem + ws);
-    e = launch_zero_words(w.flow, 2 * h->N + 2, st);
+    w.flow = words_at(mem, h->N, h->n, h->precision, nrhs);
+    e = launch_zero_words(w.flow, flow_words(h->N, h->n, h->precision), st);
     if (e != hipSuccess) {
         dev_free_async(a, mem, st);
         return to_code(e);

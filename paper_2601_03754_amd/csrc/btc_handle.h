@@ -108,7 +108,9 @@ struct btc_handle_s {
     // stream before that point takes a workspace of its own)
     void* ws = nullptr;
     int64_t ws_m = 0;
-    int* flow = nullptr;  // flags of the sweeps that use ws
+    // the sweep words at the end of ws are zero between the solves queued so
+    // far (not yet: the next solve clears them first)
+    bool words_clear = false;
     hipStream_t ws_stream = nullptr;
     hipEvent_t ws_ev = nullptr;
     bool ws_ev_valid = false;
@@ -186,7 +188,6 @@ inline void free_all(btc_handle h) {
     dfree(h, h->T32);
     dfree(h, h->info);
     dfree(h, h->ws);
-    dfree(h, h->flow);
 }
 
 inline hipEvent_t take_event(btc_handle h) {
@@ -249,13 +250,46 @@ struct Workspace {
     double* part = nullptr;
     double *rp = nullptr, *rq = nullptr;  // residual scratch
     btc::IrState* ir = nullptr;
-    int* flow = nullptr;  // flags and counters of the sweeps (flow_bytes; null: one launch per level)
+    int* flow = nullptr;  // words of the shared sweep launches (null: one launch per level)
 };
 
-// Flags (one per node and direction) and two work counters of the sweeps that
-// take several levels per launch; all 0 between launches.
-inline size_t flow_bytes(int64_t N) { return (2 * (size_t)N + 2) * sizeof(int); }
+
+// Level ranges of a sweep, one launch each: a single level (one workgroup
+// per node, nothing to wait for), or the levels from l0 up in one launch
+// (k_sweep_flow: the workgroups wait for each other's flags, which saves a
+// launch, the start of its workgroups and the first loads of its blocks per
+// level, but costs a ticket per workgroup and lets few of them wait at once).
+// Levels with at most flow_limit() nodes are faster in one launch.
+// Measured, both sweeps of one instance (m = 1, FP64) with a limit of 1024 / 256
+// / 128 / 64 nodes: N = 2000, n = 16: 103 / 67 / 63 / 63 us; N = 1000, n = 32: 81 /
+// 70 / 64 / 65; N = 400, n = 64: 80 / 80 / 74 / 78; N = 2000, n = 64: 137 / 132 /
+// 127 / 129; N = 2000, n = 96: 237 / 235 / 235 / 243; N = 200, n = 8: 42 / 42 / 42 /
+// 44.  Refined solves launch the rounds after the last as well: N = 1000, n =
+// 32: 235 / 222 / 224 / 236; N = 800, n = 64: 292 / 290 / 293 / 306.  Above n = 96
+// a level of some hundred nodes fills the GPU with block loads either way: N =
+// 1023, n = 128, m = 5: 290 with 1024, 304 with 128.
+inline int64_t flow_limit(int32_t prec, int64_t n) {
+    return n > 96 ? 1024 : is_mixed(prec) ? 256 : 128;
+}
+// Words of the shared sweep launches of one instance: a flag per node of the
+// range and direction and two work counters, all 0 between launches.  Sized for
+// the largest range, the levels from twice the limit down (sweep shape 2).
+inline int64_t flow_nodes(int64_t N, int64_t n, int32_t prec) {
+    int l = 0;
+    while (level_nodes(N, l) > 2 * flow_limit(prec, n)) ++l;
+    return N >> l;
+}
+inline int64_t flow_words(int64_t N, int64_t n, int32_t prec) { return 2 * flow_nodes(N, n, prec) + 2; }
 hipError_t launch_zero_words(int* p, int64_t count, hipStream_t st);
+
+// A handle's workspace: the solve workspace, then the sweep words.
+inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+inline size_t handle_workspace_bytes(int64_t N, int64_t n, int32_t prec, int64_t m) {
+    return align256(workspace_bytes(N, n, prec, m)) + (size_t)flow_words(N, n, prec) * sizeof(int);
+}
+inline int* words_at(void* base, int64_t N, int64_t n, int32_t prec, int64_t m) {
+    return (int*)((char*)base + align256(workspace_bytes(N, n, prec, m)));
+}
 
 // Workspace layout of an (N, n, precision) system with m right-hand sides in
 // the memory at `base` (workspace_bytes long, 256-byte aligned).
@@ -298,15 +332,18 @@ inline Workspace carve_at(void* base, int64_t N, int64_t n, int32_t prec, int64_
 
 inline Workspace carve(btc_handle h, int64_t m) {
     Workspace w = carve_at(h->ws, h->N, h->n, h->precision, m);
-    w.flow = h->flow;
+    w.flow = words_at(h->ws, h->N, h->n, h->precision, m);
     return w;
 }
 
-// The handle's sweep flags (taken on the first sweep over several levels).
-inline int ensure_flow(btc_handle h, hipStream_t st) {
-    if (h->flow) return BTC_OK;
-    hipError_t e = dev_alloc(h->alloc, (void**)&h->flow, flow_bytes(h->N), st);
-    if (e == hipSuccess) e = launch_zero_words(h->flow, 2 * h->N + 2, st);
+// Clear the sweep words of a workspace no solve has used yet.  Under capture
+// the clearing is only recorded: a solve outside the graph clears them again.
+inline int clear_words(btc_handle h, const Workspace& w, hipStream_t st) {
+    if (h->words_clear) return BTC_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(st, &cap);
+    if (e == hipSuccess) e = launch_zero_words(w.flow, flow_words(h->N, h->n, h->precision), st);
+    h->words_clear = e == hipSuccess && cap == hipStreamCaptureStatusNone;
     return to_code(e);
 }
 
@@ -319,7 +356,8 @@ inline int ensure_workspace(btc_handle h, int64_t m) {
     }
     h->ws_m = 0;
     h->ws_ev_valid = false;
-    hipError_t e = dev_alloc(h->alloc, &h->ws, workspace_bytes(h->N, h->n, h->precision, m), h->stream);
+    hipError_t e = dev_alloc(h->alloc, &h->ws, handle_workspace_bytes(h->N, h->n, h->precision, m), h->stream);
+    h->words_clear = false;
     if (e != hipSuccess) {
         h->ws = nullptr;
         return to_code(e);
@@ -527,23 +565,6 @@ inline int launch_factor(btc_handle h, const double* A_diag, const double* A_off
     return BTC_OK;
 }
 
-// Level ranges of a sweep, one launch each: a single level (one workgroup
-// per node, nothing to wait for), or the levels from l0 up in one launch
-// (k_sweep_flow: the workgroups wait for each other's flags, which saves a
-// launch, the start of its workgroups and the first loads of its blocks per
-// level, but costs a ticket per workgroup and lets few of them wait at once).
-// Levels with at most flow_limit() nodes are faster in one launch.
-// Measured, both sweeps of one instance (m = 1, FP64) with a limit of 1024 / 256
-// / 128 / 64 nodes: N = 2000, n = 16: 103 / 67 / 63 / 63 us; N = 1000, n = 32: 81 /
-// 70 / 64 / 65; N = 400, n = 64: 80 / 80 / 74 / 78; N = 2000, n = 64: 137 / 132 /
-// 127 / 129; N = 2000, n = 96: 237 / 235 / 235 / 243; N = 200, n = 8: 42 / 42 / 42 /
-// 44.  Refined solves launch the rounds after the last as well: N = 1000, n =
-// 32: 235 / 222 / 224 / 236; N = 800, n = 64: 292 / 290 / 293 / 306.  Above n = 96
-// a level of some hundred nodes fills the GPU with block loads either way: N =
-// 1023, n = 128, m = 5: 290 with 1024, 304 with 128.
-inline int64_t flow_limit(int32_t prec, int64_t n) {
-    return n > 96 ? 1024 : is_mixed(prec) ? 256 : 128;
-}
 // Many instances in one call: the limit counts the nodes of all of them, in
 // launches per block size, and a call of its own costs host time.  Measured
 // with 1024 / 4096 / 16 384 nodes: 40 instances of N up to 300, mixed 3 088 / 2 332 /
@@ -598,8 +619,10 @@ inline hipError_t sweep_range(btc_handle h, btc::Launch<btc::SweepDesc<T>>& L, i
     L.level = flow ? (l0 | (l1 << 8)) : l0;
     int* const words = L.single.flow;  // forward flags, backward flags, two counters
     if (flow) {
-        L.ticket = words + 2 * h->N + (bwd ? 1 : 0);
-        if (bwd) L.single.flow = words + h->N;
+        // the kernel's flags are indexed by permuted position
+        const int64_t nodes = flow_nodes(h->N, h->n, h->precision), first = h->N - (h->N >> l0);
+        L.ticket = words + 2 * nodes + (bwd ? 1 : 0);
+        L.single.flow = words + (bwd ? nodes : 0) - first;
     }
     const int64_t items = flow ? range_nodes(h->N, l0, l1) : level_nodes(h->N, l0);
     // profiled per range, attributed to its first level

@@ -94,8 +94,6 @@ struct Group {
     }
 };
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 // The groups of one runner call and the status words its level-0 factor
 // steps reset; offsets are into the device buffer the call is launched from.
 struct Call {
