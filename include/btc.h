@@ -233,12 +233,11 @@ BTC_API int btc_solve(btc_handle h, const double *B, double *X, int64_t nrhs, vo
  * library (BTC_NOALLOC_MAX_BYTES, one per GPU the library runs on, held until
  * the process ends) instead of allocated memory.  The workspace needs
  * 40 N n nrhs + 16 N nrhs + 1024 bytes (FP64) or 36 N n nrhs + 16 N nrhs +
- * 1024 (mixed precision), as btc_footprint_bytes counts it; larger requests
- * return BTC_ERR_UNSUPPORTED without enqueuing anything.  The current device
- * must be the handle's (-1 otherwise).  Every call on one GPU shares that
- * array: calls whose work overlaps on one GPU (other streams, other handles)
- * race and must be ordered by the caller.  Allocates nothing, also when info
- * is given.
+ * 1024 (mixed precision); larger requests return BTC_ERR_UNSUPPORTED without
+ * enqueuing anything.  The current device must be the handle's (-1 otherwise).
+ * Every call on one GPU shares that array: calls whose work overlaps on one
+ * GPU (other streams, other handles) race and must be ordered by the caller.
+ * Allocates nothing, also when info is given.
  */
 #define BTC_NOALLOC_MAX_BYTES (64u << 20)
 BTC_API int btc_solve_noalloc(btc_handle h, const double *B, double *X, int64_t nrhs, void *stream,

@@ -296,11 +296,13 @@ __device__ __forceinline__ void flag_store(int* p, int v) {
 }
 // The first wavefront waits until flags a and b (null: nothing to wait for)
 // are set and clears them; the others wait for it.  The nodes waited for have
-// smaller tickets, so they are running or done.
+// smaller tickets, so they are running or done.  (The wait gives up after some
+// seconds: launches that share words against the rules end all the same.)
+constexpr int kMaxPolls = 1 << 23;
 __device__ __forceinline__ void flow_wait(int* a, int* b, int wave) {
     if (wave == 0 && (a || b)) {
         int* f = (threadIdx.x & 1) ? b : a;
-        while (!__all(f == nullptr || flag_load(f) != 0)) __builtin_amdgcn_s_sleep(1);
+        for (int k = 0; k < kMaxPolls && !__all(f == nullptr || flag_load(f) != 0); ++k) __builtin_amdgcn_s_sleep(1);
         if (threadIdx.x < 2 && f) flag_store(f, 0);
     }
     __syncthreads();
@@ -676,6 +678,7 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<Swe
     }
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane(slot);
+    if (t < 0 || t >= (int)gridDim.x) return;  // (words shared against the rules)
     SweepDesc<T> P;
     int code, lvl;
     int64_t kk;
