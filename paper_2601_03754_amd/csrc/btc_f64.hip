@@ -1,6 +1,7 @@
-// FP64 factorization level kernel on the vector ALUs (block sizes n 9..32
-// where the autotuner prefers it to the matrix-core kernel): one workgroup per
-// block (node) of one level of the multi-stage elimination tree.
+// FP64 factorization level kernel on the vector ALUs (levels of many blocks of
+// n <= 8, and n 9..32 where the autotuner prefers it to the matrix-core kernel):
+// one workgroup per block (node) of one level of the multi-stage elimination
+// tree.
 //
 // Factorization (section "Multi-Stage Permutation", Algorithm 4, the hybrid
 // left/right-looking form): at level l (stride s) node i
@@ -137,25 +138,38 @@ __global__ __launch_bounds__(NT) void k_factor_level_f64(Launch<FactorDesc> L) {
 
     // 3. two trsm: thread v < NP solves row v of R (R^T = L^{-1} C_r^T),
     //    NP <= v < 2NP column v-NP of T (T = L^{-1} C_l); same recurrence.
+    //    Column c of every diagonal tile's inverse (16 x 16, or the whole block
+    //    when smaller) goes above the diagonal of L_ii: up to NP = 16 a third
+    //    group of threads of the wavefront solves for a unit vector along with
+    //    the others (a pass of its own took a sixth of a wide level's time at n =
+    //    8), at 32 the second wavefront solves within its tile.
+    constexpr int TS = NP < 16 ? NP : 16;
+    double* const Lg = P.Ld + (size_t)pi * nn;
+    const int col = tid - 2 * NP;
+    const bool do_i = col >= 0 && col < NP;
+    static_assert(NT >= 3 * NP, "one thread per vector");
     {
         const bool do_r = tid < NP && has_r;
         const bool do_l = tid >= NP && tid < 2 * NP && has_l;
-        if (do_r || do_l) {
-            double* base = do_r ? sB + tid * LD : sD + (tid - NP);
+        const bool unit = NP == TS && do_i;
+        if (do_r || do_l || unit) {
+            double* base = do_r ? sB + tid * LD : sD + (do_l ? tid - NP : 0);
             const int stride = do_r ? 1 : LD;
             double x[NP];
 #pragma unroll
-            for (int c = 0; c < NP; ++c) x[c] = base[c * stride];
+            for (int c = 0; c < NP; ++c) x[c] = unit ? (c == col ? 1.0 : 0.0) : base[c * stride];
             trsv_lower_reg<NP>(sA, invd, x);
+            if (unit) {
 #pragma unroll
-            for (int c = 0; c < NP; ++c) base[c * stride] = x[c];
+                for (int j = 1; j < NP; ++j)
+                    if (j > col && j < n) Lg[(size_t)col * n + j] = x[j];
+            } else {
+#pragma unroll
+                for (int c = 0; c < NP; ++c) base[c * stride] = x[c];
+            }
         }
     }
-    // inverse of every diagonal tile of L_ii (16 x 16, or the whole block when
-    // smaller), stored above the diagonal of L_ii: thread c of a group solves
-    // for column c of its tile
-    for (int col = (NT >= 3 * NP ? tid - 2 * NP : tid); col >= 0 && col < NP; col += NT) {
-        constexpr int TS = NP < 16 ? NP : 16;
+    if (NP > TS && do_i) {
         const int t0 = col / TS * TS, c = col % TS;
         double x[TS];
 #pragma unroll
@@ -166,10 +180,9 @@ __global__ __launch_bounds__(NT) void k_factor_level_f64(Launch<FactorDesc> L) {
 #pragma unroll
             for (int k = j + 1; k < TS; ++k) x[k] = fma(-sA[(t0 + k) * LD + t0 + j], x[j], x[k]);
         }
-        double* dst = P.Ld + (size_t)pi * nn + (size_t)col * n + t0;
 #pragma unroll
         for (int j = 1; j < TS; ++j)
-            if (j > c && t0 + j < n) dst[j] = x[j];
+            if (j > c && t0 + j < n) Lg[(size_t)col * n + t0 + j] = x[j];
     }
     __syncthreads();
 
@@ -217,6 +230,7 @@ int padded_block(int n) {
 hipError_t launch_factor_valu(const Launch<FactorDesc>& p, int np, int64_t items, hipStream_t st) {
     const dim3 g((unsigned)items);
     switch (np) {
+        case 8: hipLaunchKernelGGL((k_factor_level_f64<8, F64Cfg<8>::NT>), g, dim3(F64Cfg<8>::NT), 0, st, p); break;
         case 16: hipLaunchKernelGGL((k_factor_level_f64<16, F64Cfg<16>::NT>), g, dim3(F64Cfg<16>::NT), 0, st, p); break;
         case 32: hipLaunchKernelGGL((k_factor_level_f64<32, F64Cfg<32>::NT>), g, dim3(F64Cfg<32>::NT), 0, st, p); break;
         default: return hipErrorInvalidValue;

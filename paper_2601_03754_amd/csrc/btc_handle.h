@@ -429,8 +429,16 @@ inline bool partition_sizes(int64_t N, int64_t p, int64_t& n1, int64_t& nk) {
 }
 void strategy_set(int64_t N, int64_t n, int32_t prec, int32_t strategy, int32_t stages);
 
-// Factor kernel family of a handle at a level: 0 VALU FP64 (np 16/32 where the
-// autotuner chose it), 1 FP64 one workgroup per node, 2 mixed (likewise),
+// FP64, n <= 8: levels of at least this many nodes go to the vector ALUs.  A
+// wide level is bound by throughput, and the matrix-core kernel pads the block
+// to 16; in narrower ones its shorter chain counts.  Measured, vector ALUs /
+// matrix cores, us a level: n = 8, 200 000 nodes 272 / 348, 100 000 165 / 191,
+// 50 000 87 / 95, 25 000 48.0 / 50.2, 12 500 29.3 / 29.5, 781 9.5 / 7.5; n = 4,
+// 200 000 249 / 276, 100 000 151 / 149, 25 000 44.8 / 43.3.
+constexpr int64_t kValuNodes = 16384;
+
+// Factor kernel family of a handle at a level: 0 VALU FP64 (np 8 in wide
+// levels, np 16/32 where the autotuner chose it), 1 FP64 one workgroup per node, 2 mixed (likewise),
 // 3 tile-parallel FP64 (np > 64, or np 32/64 where the autotuner chose it),
 // 4 tile-parallel mixed, 5 mixed with BF16 products, 6 tile-parallel mixed
 // with BF16 products.  Variants of the tune table: np 64, 0 tile-parallel, 1
@@ -441,6 +449,7 @@ inline int tuned_factor_kind(btc_handle h, int level) {
     const bool mixed = is_mixed(h->precision);
     const int tiled = mixed ? (is_bf16(h->precision) ? 6 : 4) : 3;
     if (np > 64) return tiled;
+    if (np == 8 && !mixed && level_nodes(h->N, level) >= kValuNodes) return 0;
     const int bucket = level > 0 ? 1 : 0;
     const int v = tune_variant(BTC_OP_FACTOR, mixed ? (is_bf16(h->precision) ? 2 : 1) : 0, np, bucket);
     if (np == 64 && v == 0) return tiled;
