@@ -220,7 +220,6 @@ int solve_with(btc_handle h, const Workspace& w, const double* B, double* X, int
     const bool mixed = is_mixed(h->precision);
     if (mixed && h->refine == BTC_REFINE_GMRES) return solve_gmres(h, w, B, X, nrhs, st, info);
     hipError_t e = hipSuccess;
-    const int np = btc::padded_block((int)h->n);
     if (!mixed) {
         e = sweeps(h, sweep_desc64(h, w, B, X, nrhs), st);
         if (e != hipSuccess) return to_code(e);
@@ -232,7 +231,7 @@ int solve_with(btc_handle h, const Workspace& w, const double* B, double* X, int
         R.single = residual_desc(h, w, B, X, nrhs, false);
         e = btc::launch_ir_init(I, 1, st);
         if (e == hipSuccess)
-            e = timed(h, 3, 1, st, [&] { return btc::launch_residual(R, np, h->N, sweep_mc(BTC_OP_RESIDUAL, 0, np, nrhs), st); });
+            e = timed(h, 3, 1, st, [&] { return residual_launch(h, R, nrhs, st); });
         if (e == hipSuccess) e = btc::launch_ir_check(I, 1, st);
         if (e != hipSuccess) return to_code(e);
     } else {
@@ -253,7 +252,7 @@ int solve_with(btc_handle h, const Workspace& w, const double* B, double* X, int
         for (int it = 0; it <= h->max_refine; ++it) {
             e = sweeps(h, sweep_desc32(h, w, B, X, nrhs, it == 0), st);
             if (e == hipSuccess)
-                e = timed(h, 3, 1, st, [&] { return btc::launch_residual(R, np, h->N, sweep_mc(BTC_OP_RESIDUAL, 0, np, nrhs), st); });
+                e = timed(h, 3, 1, st, [&] { return residual_launch(h, R, nrhs, st); });
             if (e == hipSuccess) e = timed(h, 3, 2, st, [&] { return btc::launch_ir_check(I, 1, st); });
             if (e != hipSuccess) return to_code(e);
             if (info && it >= 1 && it < h->max_refine) {
@@ -296,13 +295,12 @@ hipError_t precond(btc_handle h, const Workspace& w, const double* in, double* o
 // negated).
 hipError_t matvec(btc_handle h, const Workspace& w, const double* zero, const double* x, double* out, int64_t m,
                   hipStream_t st) {
-    const int np = btc::padded_block((int)h->n);
     btc::Launch<btc::ResidualDesc> R{};
     R.single = residual_desc(h, w, zero, x, m, false);
     R.single.state = nullptr;
     R.single.R64 = out;
     R.single.neg = 1;
-    return btc::launch_residual(R, np, h->N, sweep_mc(BTC_OP_RESIDUAL, 0, np, m), st);
+    return residual_launch(h, R, m, st);
 }
 
 // Mixed-precision solve refined with GMRES corrections (BTC_REFINE_GMRES).
@@ -347,7 +345,6 @@ int solve_gmres(btc_handle h, const Workspace& w, const double* B, double* X, in
     Rs.single = residual_desc(h, w, B, X, m, false);
     Rs.single.state = nullptr;
     Rs.single.R64 = r;
-    const int np = btc::padded_block((int)h->n);
     auto fail = [&](hipError_t err) {
         rc = to_code(err);
         return rc;
@@ -367,7 +364,7 @@ int solve_gmres(btc_handle h, const Workspace& w, const double* B, double* X, in
     btc::IrState s{};
     for (int it = 0; it <= h->max_refine + 1 && rc == BTC_OK; ++it) {
         // residual of the current iterate and the convergence test
-        e = btc::launch_residual(Rs, np, h->N, sweep_mc(BTC_OP_RESIDUAL, 0, np, m), st);
+        e = residual_launch(h, Rs, m, st);
         if (e == hipSuccess) e = btc::launch_ir_check(I, 1, st);
         if (e == hipSuccess) e = hipMemcpyAsync(&s, w.ir, sizeof(s), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -636,7 +636,7 @@ inline hipError_t sweep_range(btc_handle h, btc::Launch<btc::SweepDesc<T>>& L, i
     const int64_t items = flow ? range_nodes(h->N, l0, l1) : level_nodes(h->N, l0);
     // profiled per range, attributed to its first level
     const hipError_t e =
-        timed(h, bwd ? 2 : 1, l0, st, [&] { return btc::launch_sweep(L, np, items, bwd, mc, st, flow); });
+        timed(h, bwd ? 2 : 1, l0, st, [&] { return btc::launch_sweep(L, btc::padded_sweep((int)h->n), items, bwd, mc, st, flow); });
     L.single.flow = words;
     return e;
 }
@@ -738,6 +738,11 @@ inline btc::ResidualDesc residual_desc(btc_handle h, const Workspace& w, const d
     r.n = (int32_t)h->n;
     r.m = (int32_t)m;
     return r;
+}
+
+inline hipError_t residual_launch(btc_handle h, const btc::Launch<btc::ResidualDesc>& R, int64_t m, hipStream_t st) {
+    const int mc = sweep_mc(BTC_OP_RESIDUAL, 0, btc::padded_block((int)h->n), m);
+    return btc::launch_residual(R, btc::padded_sweep((int)h->n), h->N, mc, st);
 }
 
 inline btc::IrDesc ir_desc(btc_handle h, const Workspace& w, int64_t m, double tol, int max_steps) {

@@ -191,6 +191,13 @@ constexpr int32_t kFactorDeferredDone = 2;
 // Padded compute tile for block size n (0 when unsupported).
 int padded_block(int n);
 int padded_block_mixed(int n);
+// Padded size of the sweep and residual launches: also 48 and 80 (a team of
+// three or five wavefronts instead of four or six).  The padding does not enter
+// the results.  Measured, n = 33, N = 36 730, one right-hand side, padded to 64 / 48:
+// forward level 0 134 / 109 us (FP64), 115 / 92 (FP32), residual 309 / 212; n = 65,
+// N = 9 467, padded to 96 / 80: forward 145 / 131, backward 159 / 139 (the residual
+// takes two tile rows a wavefront there and is no faster with five).
+inline int padded_sweep(int n) { return n > 32 && n <= 48 ? 48 : n > 64 && n <= 80 ? 80 : padded_block(n); }
 
 hipError_t launch_factor_valu(const Launch<FactorDesc>& p, int np, int64_t items, hipStream_t st);
 hipError_t launch_factor_mfma(const Launch<FactorDesc>& p, int np, int64_t items, hipStream_t st);

@@ -317,7 +317,9 @@ hipError_t launch_residual(const Launch<ResidualDesc>& p, int np, int64_t items,
         case 8:
         case 16: return launch_res_np<1>(p, items, mc, st);
         case 32: return launch_res_np<2>(p, items, mc, st);
+        case 48: return launch_res_np<3>(p, items, mc, st);
         case 64: return launch_res_np<4>(p, items, mc, st);
+        case 80:
         case 96: return launch_res_np<6>(p, items, mc, st);
         case 128: return launch_res_np<8>(p, items, mc, st);
         default: return hipErrorInvalidValue;

@@ -61,6 +61,7 @@ struct Group {
                // 2 / 3 the same over level ranges (subtree launches)
     bool deferred = false;  // FACTOR: some item has deferred updates to apply
     int m_max = 1;   // sweeps / residual: largest number of right-hand sides
+    int n_max = 1;   // sweeps / residual: largest block (the launch pads to it)
     int np;
     bool count = false;    // work accounted (profiler on)
     bool prof = false;     // bracketed by timing events
@@ -446,6 +447,7 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             g.kind = kind;
             g.np = np;
             g.m_max = std::max<int>(g.m_max, (int)s.nrhs);
+            g.n_max = std::max<int>(g.n_max, (int)h->n);
             int32_t inst;
             if (mixed) {
                 inst = (int32_t)(g.descs.size() / sizeof(btc::SweepDesc<float>));
@@ -470,6 +472,7 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
             g.kind = 0;
             g.np = np;
             g.m_max = std::max<int>(g.m_max, (int)s.nrhs);
+            g.n_max = std::max<int>(g.n_max, (int)h->n);
             const int32_t inst = (int32_t)(g.descs.size() / sizeof(btc::ResidualDesc));
             push_desc(g, residual_desc(h, w, s.B, s.X, s.nrhs, mixed));
             add_work(r, g, s, mixed);
@@ -620,15 +623,15 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
             case BTC_OP_BACKWARD: {
                 const bool bwd = g.op == BTC_OP_BACKWARD;
                 const bool range = g.kind >= 2;
-                const int fk = g.kind & 1;
+                const int fk = g.kind & 1, np = btc::padded_sweep(g.n_max), mc = sweep_cols(g.op, fk, g.np, g.m_max);
                 if (fk == 1)
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<float>>(g, dev), g.np, items, bwd, sweep_cols(g.op, 1, g.np, g.m_max), gs, range);
+                    e = btc::launch_sweep(make_launch<btc::SweepDesc<float>>(g, dev), np, items, bwd, mc, gs, range);
                 else
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), g.np, items, bwd, sweep_cols(g.op, 0, g.np, g.m_max), gs, range);
+                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), np, items, bwd, mc, gs, range);
                 break;
             }
             case BTC_OP_RESIDUAL:
-                e = btc::launch_residual(make_launch<btc::ResidualDesc>(g, dev), g.np, items, sweep_mc(BTC_OP_RESIDUAL, 0, g.np, g.m_max), gs);
+                e = btc::launch_residual(make_launch<btc::ResidualDesc>(g, dev), btc::padded_sweep(g.n_max), items, sweep_mc(BTC_OP_RESIDUAL, 0, g.np, g.m_max), gs);
                 break;
             case BTC_OP_REFINE_INIT:
                 e = btc::launch_ir_init(make_launch<btc::IrDesc>(g, dev), items, gs);

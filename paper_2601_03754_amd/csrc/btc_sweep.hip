@@ -740,7 +740,9 @@ hipError_t launch_sweep_t(const Launch<SweepDesc<T>>& p, int np, int64_t items, 
         case 8:
         case 16: return launch_np<16>(p, items, backward, mc, st, flow);
         case 32: return launch_np<32>(p, items, backward, mc, st, flow);
+        case 48: return launch_np<48>(p, items, backward, mc, st, flow);
         case 64: return launch_np<64>(p, items, backward, mc, st, flow);
+        case 80: return launch_np<80>(p, items, backward, mc, st, flow);
         case 96: return launch_np<96>(p, items, backward, mc, st, flow);
         case 128: return launch_np<128>(p, items, backward, mc, st, flow);
         default: return hipErrorInvalidValue;
