@@ -29,6 +29,7 @@ struct Launch {
     const WorkItem* items;  // explicit mode: item array (device); nullptr = implicit
     int32_t level;          // implicit mode: level of every item
     int* ticket;            // sweeps over a range of levels: work counter (0 between launches)
+    const int* live;        // the same, optional: nothing to do in any item while *live is 0
 };
 
 template <class D>
@@ -221,6 +222,11 @@ hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t item
                         hipStream_t st, bool flow = false);
 hipError_t launch_sweep(const Launch<SweepDesc<float>>& p, int np, int64_t items, bool backward, int mc,
                         hipStream_t st, bool flow = false);
+// *live = 1 if any of the descriptors has work to do (no breakdown, refinement
+// not finished), else 0.  A shared sweep launch without work costs a ticket of 12
+// ns per node (300 us for the upper levels of a large batch, of whose five rounds
+// usually three have none), with the word set by this launch ahead of it a few us.
+hipError_t launch_sweep_live(const SweepDesc<float>* descs, int count, int* live, hipStream_t st);
 // Two launches over the same items (every block row of each instance); mc:
 // right-hand-side columns per dependency-chain group (1 or 4; with 4,
 // instances with fewer columns mask the rest).

@@ -53,6 +53,10 @@ __global__ __launch_bounds__(256) void k_expand_items(const ItemRun* __restrict_
         out[q] = {r.inst, r.level, r.first + q};
 }
 
+// Mixed-precision sweeps over a range of more nodes than this find out in a
+// launch ahead whether any instance still has work (btc::launch_sweep_live).
+constexpr int64_t kLiveItems = 2048;
+
 // One group = one launch.
 struct Group {
     int stage = 0;
@@ -77,8 +81,8 @@ struct Group {
         items += count;
     }
     // sweeps over several levels: items in level order, one flag per node (of
-    // every instance in turn) and a work counter in the call's buffer, uploaded
-    // as 0
+    // every instance in turn), a work counter and the live word in the call's
+    // buffer, uploaded as 0
     struct Flags {
         int64_t first, pos;  // the instance's first flag, and the permuted position it stands for
     };
@@ -508,7 +512,7 @@ size_t layout_call(Call& c, size_t base, bool may_expand, size_t* upload) {
         g.off_desc = bytes;
         bytes = align256(bytes + g.descs.size());
         g.off_words = bytes;
-        if (g.words) bytes = align256(bytes + (size_t)(g.words + 1) * sizeof(int));
+        if (g.words) bytes = align256(bytes + (size_t)(g.words + 2) * sizeof(int));
         items += g.items;
         c.runs += g.runs.size();
     }
@@ -539,7 +543,7 @@ void write_call(const Call& c, char* host, char* dev) {
         const Group& g = kv.second;
         memcpy(host + g.off_desc, g.descs.data(), g.descs.size());
         if (g.words) {
-            memset(host + g.off_words, 0, (size_t)(g.words + 1) * sizeof(int));
+            memset(host + g.off_words, 0, (size_t)(g.words + 2) * sizeof(int));
             const size_t at = (g.kind & 1) ? offsetof(btc::SweepDesc<float>, flow) : offsetof(btc::SweepDesc<double>, flow);
             for (size_t k = 0; k < g.flags.size(); ++k) {
                 int* const p = (int*)(dev + g.off_words) + g.flags[k].first - g.flags[k].pos;
@@ -624,9 +628,15 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
                 const bool bwd = g.op == BTC_OP_BACKWARD;
                 const bool range = g.kind >= 2;
                 const int fk = g.kind & 1, np = btc::padded_sweep(g.n_max), mc = sweep_cols(g.op, fk, g.np, g.m_max);
-                if (fk == 1)
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<float>>(g, dev), np, items, bwd, mc, gs, range);
-                else
+                if (fk == 1) {
+                    auto L = make_launch<btc::SweepDesc<float>>(g, dev);
+                    if (range && items > kLiveItems) {
+                        int* const live = L.ticket + 1;
+                        e = btc::launch_sweep_live(L.descs, (int)(g.descs.size() / g.desc_size), live, gs);
+                        L.live = live;
+                    }
+                    if (e == hipSuccess) e = btc::launch_sweep(L, np, items, bwd, mc, gs, range);
+                } else
                     e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), np, items, bwd, mc, gs, range);
                 break;
             }

@@ -671,6 +671,7 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<Swe
     // taking tickets (2048 of them in turn: 25 us instead of 5)
     const bool whole = !L.items && L.single.skip;
     if (whole && skip_item(L.single)) return;
+    if (L.live && *L.live == 0) return;
     if (threadIdx.x == 0) {
         const int t = __hip_atomic_fetch_add(L.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t == (int)gridDim.x - 1) flag_store(L.ticket, 0);
@@ -699,6 +700,14 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<Swe
         bwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
     else
         fwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
+}
+
+__global__ __launch_bounds__(256) void k_sweep_live(const SweepDesc<float>* __restrict__ descs, int count,
+                                                    int* __restrict__ live) {
+    bool any = false;
+    for (int k = threadIdx.x; k < count; k += 256) any = any || !skip_item(descs[k]);
+    const int r = __syncthreads_or(any);
+    if (threadIdx.x == 0) *live = r != 0;
 }
 
 template <int NP, class T, int NG>
@@ -750,6 +759,11 @@ hipError_t launch_sweep_t(const Launch<SweepDesc<T>>& p, int np, int64_t items, 
 }
 
 }  // namespace
+
+hipError_t launch_sweep_live(const SweepDesc<float>* descs, int count, int* live, hipStream_t st) {
+    hipLaunchKernelGGL(k_sweep_live, dim3(1), dim3(256), 0, st, descs, count, live);
+    return hipGetLastError();
+}
 
 hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t items, bool backward, int mc,
                         hipStream_t st, bool flow) {

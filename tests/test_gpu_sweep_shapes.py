@@ -52,3 +52,34 @@ def test_wide_levels_of_a_batch_keep_launches_of_their_own(precision):
     assert oracle.relres(pr.D, pr.E, out[0], pr.B) <= (1e-12 if precision == 0 else 1e-10)
     for s in (1, 2):
         assert np.array_equal(out[s], out[0])
+
+
+@pytest.mark.parametrize("large", [700, 2600])
+def test_refinements_that_end_in_different_rounds(large):
+    """A shared launch of few nodes, and one of many (which first asks whether
+    any instance still has work): an instance that needs several corrections
+    beside ones that are done after the first, each as if alone."""
+    from paper_2601_03754_amd import btc
+
+    n = 12
+    prs = [inputs.block_tridiag(large, n, seed=1), inputs.block_tridiag(40, n, c=0.1, seed=2, margin=True),
+           inputs.block_tridiag(90, n, seed=3)]
+    Ds, Es, Bs = ([dev(getattr(p, a)) for p in prs] for a in "DEB")
+    precision = btc.BTC_BF16_IR
+    r = btc.Runner()
+    hs = [btc.btc_create(p.N, n, precision) for p in prs]
+    Xs = [torch.empty_like(b) for b in Bs]
+    r.factor_batched(hs, Ds, Es)
+    info = r.solve_batched(hs, Bs, Xs, 1, want_info=True)
+    steps = []
+    for k, p in enumerate(prs):
+        f = btc.Factor(Ds[k], Es[k], precision=precision)
+        X, alone = f.solve(Bs[k], want_info=True)
+        assert np.array_equal(X.cpu().numpy(), Xs[k].cpu().numpy()), k
+        assert info[k]["steps"] == alone["steps"] and info[k]["converged"]
+        steps.append(alone["steps"])
+        f.close()
+    assert steps[1] > max(steps[0], steps[2])
+    for h in hs:
+        btc.btc_destroy(h)
+    r.close()
