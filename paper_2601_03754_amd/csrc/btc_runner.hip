@@ -90,12 +90,17 @@ struct Group {
     int64_t words = 0;
     size_t off_desc = 0, off_items = 0, off_words = 0;
     // Items of all instances in level order: the launch's workgroups wait only
-    // for earlier ones.
+    // for earlier ones.  (By counting: sorting the 7 500 runs of 1 500 small
+    // instances took a tenth of their solve.)
     void level_order() {
         const bool down = op == BTC_OP_BACKWARD;
-        std::stable_sort(runs.begin(), runs.end(), [down](const ItemRun& a, const ItemRun& b) {
-            return down ? (a.level >> 16) > (b.level >> 16) : (a.level >> 16) < (b.level >> 16);
-        });
+        auto key = [down](const ItemRun& r) { return down ? 63 - (r.level >> 16) : r.level >> 16; };
+        size_t at[65] = {};
+        for (const ItemRun& r : runs) ++at[key(r) + 1];
+        for (int k = 0; k < 64; ++k) at[k + 1] += at[k];
+        std::vector<ItemRun> sorted(runs.size());
+        for (const ItemRun& r : runs) sorted[at[key(r)]++] = r;
+        runs.swap(sorted);
     }
 };
 
