@@ -296,13 +296,12 @@ __device__ __forceinline__ void flag_store(int* p, int v) {
 }
 // The first wavefront waits until flags a and b (null: nothing to wait for)
 // are set and clears them; the others wait for it.  The nodes waited for have
-// smaller tickets, so they are running or done.  (The wait gives up after some
-// seconds: launches that share words against the rules end all the same.)
-constexpr int kMaxPolls = 1 << 23;
+// smaller tickets, so they are running or done.  (No bound on the polls: a node
+// of millions of right-hand sides works for seconds.)
 __device__ __forceinline__ void flow_wait(int* a, int* b, int wave) {
     if (wave == 0 && (a || b)) {
         int* f = (threadIdx.x & 1) ? b : a;
-        for (int k = 0; k < kMaxPolls && !__all(f == nullptr || flag_load(f) != 0); ++k) __builtin_amdgcn_s_sleep(1);
+        while (!__all(f == nullptr || flag_load(f) != 0)) __builtin_amdgcn_s_sleep(1);
         if (threadIdx.x < 2 && f) flag_store(f, 0);
     }
     __syncthreads();
