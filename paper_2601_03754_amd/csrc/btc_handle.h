@@ -635,8 +635,10 @@ inline hipError_t sweep_range(btc_handle h, btc::Launch<btc::SweepDesc<T>>& L, i
     }
     const int64_t items = flow ? range_nodes(h->N, l0, l1) : level_nodes(h->N, l0);
     // profiled per range, attributed to its first level
-    const hipError_t e =
-        timed(h, bwd ? 2 : 1, l0, st, [&] { return btc::launch_sweep(L, btc::padded_sweep((int)h->n), items, bwd, mc, st, flow); });
+    const hipError_t e = timed(h, bwd ? 2 : 1, l0, st, [&] {
+        return btc::launch_sweep(L, btc::padded_sweep((int)h->n), items, bwd, mc, st, flow,
+                                 btc::wide_vectors(h->n, L.single.m));
+    });
     L.single.flow = words;
     return e;
 }

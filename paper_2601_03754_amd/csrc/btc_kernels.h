@@ -217,11 +217,15 @@ hipError_t launch_factor_tiled(const Launch<FactorDesc>& p, int np, int mode, in
 // flow: the items are the nodes of a range of levels l0 .. l1-1 in level order
 // (level field l0 | l1 << 8, explicit items also the node's level << 16),
 // which wait for each other through SweepDesc.flow; Launch.ticket is set.
-// Else independent nodes of single levels.
+// Else independent nodes of single levels.  wide: some instance's vectors are
+// too wide for 32-bit offsets (wide_vectors).
+// Sixteen rows of a node's vectors are addressed by 32-bit offsets below the one
+// that stands for no element (2^30); wider ones take 64-bit addresses.
+inline bool wide_vectors(int64_t n, int64_t m) { return (n < 16 ? n : 16) * m > ((int64_t)1 << 30) / 8; }
 hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool flow = false);
+                        hipStream_t st, bool flow = false, bool wide = false);
 hipError_t launch_sweep(const Launch<SweepDesc<float>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool flow = false);
+                        hipStream_t st, bool flow = false, bool wide = false);
 // *live = 1 if any of the descriptors has work to do (no breakdown, refinement
 // not finished), else 0.  A shared sweep launch without work costs a ticket of 12
 // ns per node (300 us for the upper levels of a large batch, of whose five rounds

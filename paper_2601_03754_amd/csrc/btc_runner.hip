@@ -66,6 +66,7 @@ struct Group {
     bool deferred = false;  // FACTOR: some item has deferred updates to apply
     int m_max = 1;   // sweeps / residual: largest number of right-hand sides
     int n_max = 1;   // sweeps / residual: largest block (the launch pads to it)
+    bool wide = false;  // sweeps: some instance's vectors need 64-bit addresses
     int np;
     bool count = false;    // work accounted (profiler on)
     bool prof = false;     // bracketed by timing events
@@ -465,6 +466,7 @@ void build_call(btc_runner r, int32_t count, const btc_step* steps, hipStream_t 
                 inst = (int32_t)(g.descs.size() / sizeof(btc::SweepDesc<double>));
                 push_desc(g, sweep_desc64(h, w, s.B, s.X, s.nrhs));
             }
+            g.wide = g.wide || btc::wide_vectors(h->n, s.nrhs);
             add_work(r, g, s, mixed);
             if (range) {
                 g.flags.push_back({g.words, h->N - (h->N >> s.level)});
@@ -640,9 +642,10 @@ int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
                         e = btc::launch_sweep_live(L.descs, (int)(g.descs.size() / g.desc_size), live, gs);
                         L.live = live;
                     }
-                    if (e == hipSuccess) e = btc::launch_sweep(L, np, items, bwd, mc, gs, range);
+                    if (e == hipSuccess) e = btc::launch_sweep(L, np, items, bwd, mc, gs, range, g.wide);
                 } else
-                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), np, items, bwd, mc, gs, range);
+                    e = btc::launch_sweep(make_launch<btc::SweepDesc<double>>(g, dev), np, items, bwd, mc, gs, range,
+                                          g.wide);
                 break;
             }
             case BTC_OP_RESIDUAL:

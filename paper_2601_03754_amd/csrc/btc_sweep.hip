@@ -226,6 +226,41 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t vec_rsrc(const T* v, int n, in
     return block_rsrc(v + (ok ? ((size_t)node * n + kTl * w) * m : 0), ok ? rows * m * (int)sizeof(T) : 0);
 }
 
+// Elements of those rows.  At: place of the element in row r, column q (not ok:
+// none, reads 0, writes dropped): a byte offset of T's array, or with WIDE, for
+// vectors too wide for 32-bit offsets (wide_vectors), an element index.  S may be
+// double where T is float.
+template <bool WIDE, class T>
+struct Rows {
+    using At = std::conditional_t<WIDE, int64_t, int>;
+    __device__ static At at(bool ok, int r, int m, int q) {
+        if constexpr (WIDE) return ok ? (int64_t)r * m + q : -1;
+        else return ok ? (r * m + q) * (int)sizeof(T) : kOob;
+    }
+    template <int AUX = 0, class S>
+    __device__ __forceinline__ static void ld(S& x, const S* v, int n, int m, int64_t node, bool present, int w,
+                                              At a) {
+        if constexpr (WIDE) {
+            const S* p = v + ((size_t)node * n + kTl * w) * m + a;
+            x = S(0);
+            if (present && a >= 0) x = AUX ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+        } else {
+            buf_ld<AUX>(x, vec_rsrc(v, n, m, node, present, w), sizeof(S) == sizeof(T) || a == kOob ? a : 2 * a);
+        }
+    }
+    template <int AUX = 0, class S>
+    __device__ __forceinline__ static void st(S x, S* v, int n, int m, int64_t node, bool present, int w, At a) {
+        if constexpr (WIDE) {
+            S* p = v + ((size_t)node * n + kTl * w) * m + a;
+            if (!present || a < 0) return;
+            if constexpr (AUX) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *p = x;
+        } else {
+            buf_st<AUX>(x, vec_rsrc(v, n, m, node, present, w), sizeof(S) == sizeof(T) || a == kOob ? a : 2 * a);
+        }
+    }
+};
+
 template <class T>
 __device__ __forceinline__ bool skip_item(const SweepDesc<T>& P) {
     // both flags in one round trip
@@ -331,11 +366,12 @@ struct Team {
 
 // ---------------------------------------------------------------------------
 // Forward step of node kk of level lvl by one team (wavefront w of it).
-template <int NP, class T, int NG, bool FLOW>
+template <int NP, class T, int NG, bool FLOW, bool WIDE>
 __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t kk, int w, T* __restrict__ lds,
                                          const Flow& fl) {
     using G = Team<NP, T, NG>;
     using E = Eng<T>;
+    using V = Rows<WIDE, T>;
     constexpr int W = G::W, CP = G::CP, SZ = (int)sizeof(T);
     const int lane = threadIdx.x & (kWave - 1);
     const int n = P.n, m = P.m;
@@ -358,7 +394,7 @@ __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t
         const int cols = m - q0 < CP ? m - q0 : CP;
         typename E::Acc acc[NG], u[NG], v[NG], sl[NG], sr[NG];
         double b64[NG][E::NV];
-        int vo[NG][E::NV];  // offsets of the lane's elements in a node's vectors
+        typename V::At vo[NG][E::NV];  // the lane's elements of a node's vectors
         const bool wide = sizeof(T) == 4 && P.B64;  // the right-hand side is FP64
         auto load_rhs = [&]() {
 #pragma unroll
@@ -367,11 +403,9 @@ __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t
 #pragma unroll
                 for (int x = 0; x < E::NV; ++x) {
                     const int r = E::row(x, lane);
-                    const bool ok = kTl * w + r < n && c < cols;
-                    vo[g][x] = ok ? (r * m + q0 + c) * SZ : kOob;
-                    buf_ld(acc[g].v[x], vec_rsrc(P.B, n, m, d.i - 1, !wide, w), vo[g][x]);
-                    if constexpr (SZ == 4)
-                        buf_ld(b64[g][x], vec_rsrc(P.B64, n, m, d.i - 1, wide, w), ok ? 2 * vo[g][x] : kOob);
+                    vo[g][x] = V::at(kTl * w + r < n && c < cols, r, m, q0 + c);
+                    V::ld(acc[g].v[x], P.B, n, m, d.i - 1, !wide, w, vo[g][x]);
+                    if constexpr (SZ == 4) V::ld(b64[g][x], P.B64, n, m, d.i - 1, wide, w, vo[g][x]);
                 }
             }
         };
@@ -381,10 +415,10 @@ __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t
             for (int g = 0; g < NG; ++g)
 #pragma unroll
                 for (int x = 0; x < E::NV; ++x) {
-                    buf_ld<AUX>(sl[g].v[x], vec_rsrc(P.U, n, m, kin.pl, kin.left, w), vo[g][x]);
-                    buf_ld<AUX>(sr[g].v[x], vec_rsrc(P.V, n, m, kin.pr, kin.right, w), vo[g][x]);
-                    buf_ld<AUX>(u[g].v[x], vec_rsrc(P.U, n, m, kin.pr, pass_u, w), vo[g][x]);
-                    buf_ld<AUX>(v[g].v[x], vec_rsrc(P.V, n, m, kin.pl, pass_v, w), vo[g][x]);
+                    V::template ld<AUX>(sl[g].v[x], P.U, n, m, kin.pl, kin.left, w, vo[g][x]);
+                    V::template ld<AUX>(sr[g].v[x], P.V, n, m, kin.pr, kin.right, w, vo[g][x]);
+                    V::template ld<AUX>(u[g].v[x], P.U, n, m, kin.pr, pass_u, w, vo[g][x]);
+                    V::template ld<AUX>(v[g].v[x], P.V, n, m, kin.pl, pass_v, w, vo[g][x]);
                 }
         };
         // the vectors go out ahead of the block loads; the children's sums
@@ -473,9 +507,9 @@ __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t
 #pragma unroll
             for (int x = 0; x < E::NV; ++x) {
                 constexpr int AUX = FLOW ? kCoherent : 0;
-                buf_st(acc[g].v[x], vec_rsrc(P.Y, n, m, d.pi, true, w), vo[g][x]);
-                buf_st<AUX>(u[g].v[x], vec_rsrc(P.U, n, m, d.pi, d.has_r, w), vo[g][x]);
-                buf_st<AUX>(v[g].v[x], vec_rsrc(P.V, n, m, d.pi, d.has_l, w), vo[g][x]);
+                V::st(acc[g].v[x], P.Y, n, m, d.pi, true, w, vo[g][x]);
+                V::template st<AUX>(u[g].v[x], P.U, n, m, d.pi, d.has_r, w, vo[g][x]);
+                V::template st<AUX>(v[g].v[x], P.V, n, m, d.pi, d.has_l, w, vo[g][x]);
             }
     };
     pass(0, std::true_type{});
@@ -488,11 +522,12 @@ __device__ __forceinline__ void fwd_team(const SweepDesc<T>& P, int lvl, int64_t
 
 // ---------------------------------------------------------------------------
 // Backward step of node kk of level lvl by one team.
-template <int NP, class T, int NG, bool FLOW>
+template <int NP, class T, int NG, bool FLOW, bool WIDE>
 __device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t kk, int w, T* __restrict__ lds,
                                          const Flow& fl) {
     using G = Team<NP, T, NG>;
     using E = Eng<T>;
+    using V = Rows<WIDE, T>;
     constexpr int W = G::W, CP = G::CP, SZ = (int)sizeof(T);
     const int lane = threadIdx.x & (kWave - 1);
     const int n = P.n, m = P.m;
@@ -512,16 +547,16 @@ __device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t
         T xr[PER], xl[PER];
         double x0[NG][E::NV];
         typename E::Acc acc[NG];
-        int vo[NG][E::NV];  // offsets of the lane's elements in a node's vectors
+        typename V::At vo[NG][E::NV];  // the lane's elements of a node's vectors
         // the neighbours' solutions (rows past n: zero)
         auto load_neighbours = [&]() {
             constexpr int AUX = FLOW ? kCoherent : 0;
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int e = lane + kWave * k, r = e / CP, c = e % CP;
-                const int off = (kTl * w + r < n && c < cols) ? (r * m + q0 + c) * SZ : kOob;
-                buf_ld<AUX>(xr[k], vec_rsrc(P.X, n, m, d.i + d.s - 1, d.has_r, w), off);
-                buf_ld<AUX>(xl[k], vec_rsrc(P.X, n, m, d.i - d.s - 1, d.has_l, w), off);
+                const auto at = V::at(kTl * w + r < n && c < cols, r, m, q0 + c);
+                V::template ld<AUX>(xr[k], P.X, n, m, d.i + d.s - 1, d.has_r, w, at);
+                V::template ld<AUX>(xl[k], P.X, n, m, d.i - d.s - 1, d.has_l, w, at);
             }
         };
         // the vectors go out ahead of the block loads (the neighbours' where
@@ -533,11 +568,9 @@ __device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t
 #pragma unroll
             for (int x = 0; x < E::NV; ++x) {
                 const int r = E::row(x, lane);
-                const bool ok = kTl * w + r < n && c < cols;
-                vo[g][x] = ok ? (r * m + q0 + c) * SZ : kOob;
-                buf_ld(acc[g].v[x], vec_rsrc(P.Y, n, m, d.pi, true, w), vo[g][x]);
-                if constexpr (SZ == 4)
-                    buf_ld(x0[g][x], vec_rsrc(P.X64, n, m, d.i - 1, P.X64 && !P.first, w), ok ? 2 * vo[g][x] : kOob);
+                vo[g][x] = V::at(kTl * w + r < n && c < cols, r, m, q0 + c);
+                V::ld(acc[g].v[x], P.Y, n, m, d.pi, true, w, vo[g][x]);
+                if constexpr (SZ == 4) V::ld(x0[g][x], P.X64, n, m, d.i - 1, P.X64 && !P.first, w, vo[g][x]);
             }
         }
         keep_order();
@@ -620,10 +653,9 @@ __device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t
         for (int g = 0; g < NG; ++g)
 #pragma unroll
             for (int x = 0; x < E::NV; ++x) {
-                buf_st<FLOW ? kCoherent : 0>(acc[g].v[x], vec_rsrc(P.X, n, m, d.i - 1, true, w), vo[g][x]);
-                if constexpr (SZ == 4)
-                    buf_st(x0[g][x] + (double)acc[g].v[x],  // first: the absent iterate reads 0
-                           vec_rsrc(P.X64, n, m, d.i - 1, P.X64, w), vo[g][x] == kOob ? kOob : 2 * vo[g][x]);
+                V::template st<FLOW ? kCoherent : 0>(acc[g].v[x], P.X, n, m, d.i - 1, true, w, vo[g][x]);
+                if constexpr (SZ == 4)  // (first: the absent iterate reads 0)
+                    V::st(x0[g][x] + (double)acc[g].v[x], P.X64, n, m, d.i - 1, P.X64 != nullptr, w, vo[g][x]);
             }
     };
     pass(0, std::true_type{});
@@ -640,7 +672,7 @@ __device__ __forceinline__ void bwd_team(const SweepDesc<T>& P, int lvl, int64_t
 
 // ---------------------------------------------------------------------------
 // One level of one or many instances: one workgroup (one team) per node.
-template <int NP, class T, int NG, bool BWD>
+template <int NP, class T, int NG, bool BWD, bool WIDE>
 __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_level(Launch<SweepDesc<T>> L) {
     __shared__ T lds[Team<NP, T, NG>::LDS(BWD)];
     SweepDesc<T> P;
@@ -650,9 +682,9 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_level(Launch<Sw
     if (skip_item(P)) return;
     const Flow none{nullptr, 0, 0};
     if constexpr (BWD)
-        bwd_team<NP, T, NG, false>(P, lvl, kk, wave_id(), lds, none);
+        bwd_team<NP, T, NG, false, WIDE>(P, lvl, kk, wave_id(), lds, none);
     else
-        fwd_team<NP, T, NG, false>(P, lvl, kk, wave_id(), lds, none);
+        fwd_team<NP, T, NG, false, WIDE>(P, lvl, kk, wave_id(), lds, none);
 }
 
 // A range of levels in one launch.  The item level field holds l0 | l1 << 8
@@ -662,7 +694,7 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_level(Launch<Sw
 // that started before it, so the launch always makes progress, whatever the
 // dispatch order and whatever else runs on the GPU.  The last ticket resets
 // the counter.
-template <int NP, class T, int NG, bool BWD>
+template <int NP, class T, int NG, bool BWD, bool WIDE>
 __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<SweepDesc<T>> L) {
     __shared__ T lds[Team<NP, T, NG>::LDS(BWD)];
     __shared__ int slot;
@@ -696,9 +728,9 @@ __global__ __launch_bounds__((Team<NP, T, NG>::TH)) void k_sweep_flow(Launch<Swe
     if (!whole && skip_item(P)) return;
     const Flow fl{P.flow, l0, l1};
     if constexpr (BWD)
-        bwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
+        bwd_team<NP, T, NG, true, WIDE>(P, lvl, kk, wave_id(), lds, fl);
     else
-        fwd_team<NP, T, NG, true>(P, lvl, kk, wave_id(), lds, fl);
+        fwd_team<NP, T, NG, true, WIDE>(P, lvl, kk, wave_id(), lds, fl);
 }
 
 __global__ __launch_bounds__(256) void k_sweep_live(const SweepDesc<float>* __restrict__ descs, int count,
@@ -709,19 +741,19 @@ __global__ __launch_bounds__(256) void k_sweep_live(const SweepDesc<float>* __re
     if (threadIdx.x == 0) *live = r != 0;
 }
 
-template <int NP, class T, int NG>
+template <int NP, class T, int NG, bool WIDE = false>
 hipError_t launch_ng(const Launch<SweepDesc<T>>& p, int64_t items, bool backward, hipStream_t st, bool flow) {
     const dim3 g((unsigned)items), b(Team<NP, T, NG>::TH);
     if (!flow) {
         if (backward)
-            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, true>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, true, WIDE>), g, b, 0, st, p);
         else
-            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, false>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_level<NP, T, NG, false, WIDE>), g, b, 0, st, p);
     } else {
         if (backward)
-            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, true>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, true, WIDE>), g, b, 0, st, p);
         else
-            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, false>), g, b, 0, st, p);
+            hipLaunchKernelGGL((k_sweep_flow<NP, T, NG, false, WIDE>), g, b, 0, st, p);
     }
     return hipGetLastError();
 }
@@ -743,7 +775,9 @@ hipError_t launch_np(const Launch<SweepDesc<float>>& p, int64_t items, bool back
 
 template <class T>
 hipError_t launch_sweep_t(const Launch<SweepDesc<T>>& p, int np, int64_t items, bool backward, int mc,
-                          hipStream_t st, bool flow) {
+                          hipStream_t st, bool flow, bool wide) {
+    // (one instantiation for every n: the padding does not enter the results)
+    if (wide) return launch_ng<128, T, 1, true>(p, items, backward, st, flow);
     switch (np) {
         case 8:
         case 16: return launch_np<16>(p, items, backward, mc, st, flow);
@@ -765,13 +799,13 @@ hipError_t launch_sweep_live(const SweepDesc<float>* descs, int count, int* live
 }
 
 hipError_t launch_sweep(const Launch<SweepDesc<double>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool flow) {
-    return launch_sweep_t<double>(p, np, items, backward, mc, st, flow);
+                        hipStream_t st, bool flow, bool wide) {
+    return launch_sweep_t<double>(p, np, items, backward, mc, st, flow, wide);
 }
 
 hipError_t launch_sweep(const Launch<SweepDesc<float>>& p, int np, int64_t items, bool backward, int mc,
-                        hipStream_t st, bool flow) {
-    return launch_sweep_t<float>(p, np, items, backward, mc, st, flow);
+                        hipStream_t st, bool flow, bool wide) {
+    return launch_sweep_t<float>(p, np, items, backward, mc, st, flow, wide);
 }
 
 }  // namespace btc
