@@ -412,17 +412,17 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         if (left > 12) {
             // each step's products on the other tiles run under the next
             // step's chain
-            const PanelStep s0 = panel_diag<0>(Q, ok, lane), s1 = panel_diag<1>(Q, ok, lane);
+            const PanelStep s0 = panel_diag<0, MODE == 0>(Q, ok, lane), s1 = panel_diag<1, MODE == 0>(Q, ok, lane);
             panel_rest<TB, 0>(E, Y, s0);
-            const PanelStep s2 = panel_diag<2>(Q, ok, lane);
+            const PanelStep s2 = panel_diag<2, MODE == 0>(Q, ok, lane);
             panel_rest<TB, 1>(E, Y, s1);
-            const PanelStep s3 = panel_diag<3>(Q, ok, lane);
+            const PanelStep s3 = panel_diag<3, MODE == 0>(Q, ok, lane);
             panel_rest<TB, 2>(E, Y, s2);
             panel_rest<TB, 3>(E, Y, s3);
         } else {
-            panel_rest<TB, 0>(E, Y, panel_diag<0>(Q, ok, lane));
-            if (left > 4) panel_rest<TB, 1>(E, Y, panel_diag<1>(Q, ok, lane));
-            if (left > 8) panel_rest<TB, 2>(E, Y, panel_diag<2>(Q, ok, lane));
+            panel_rest<TB, 0>(E, Y, panel_diag<0, MODE == 0>(Q, ok, lane));
+            if (left > 4) panel_rest<TB, 1>(E, Y, panel_diag<1, MODE == 0>(Q, ok, lane));
+            if (left > 8) panel_rest<TB, 2>(E, Y, panel_diag<2, MODE == 0>(Q, ok, lane));
         }
         if (!__builtin_amdgcn_readfirstlane((int)ok)) {  // every wavefront alike
             if (threadIdx.x == 0) atomicMin(P.info, (unsigned long long)i);

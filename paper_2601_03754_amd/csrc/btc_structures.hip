@@ -192,7 +192,7 @@ __global__ __launch_bounds__(NW * kWave) void k_tip_chol(double* __restrict__ S,
     if (tid == 0) fail = 0;
     stage_lower_packed<NP, NT>(a, S, m, tid);
     __syncthreads();
-    if (tiles::potrf_blocked<NP, NW>(a, invd, &fail)) {
+    if (tiles::potrf_blocked<NP, NW, true>(a, invd, &fail)) {
         for (int e = tid; e < m * m; e += NT) {
             const int r = e / m, c = e % m;
             S[e] = c <= r ? tiles::PackedLds::tile(a, r / 16, c / 16)[(r % 16) * tiles::kLDI + c % 16] : 0.0;

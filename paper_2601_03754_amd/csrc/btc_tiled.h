@@ -395,7 +395,7 @@ __global__ __launch_bounds__(NW * kWave, (NB * NW + 3) / 4) void k_tiled_potrf_t
     stage_lower_packed<NP, NW * kWave>(sS, src, n, tid);
     if (tid == 0) fail = 0;
     __syncthreads();
-    const bool ok = potrf_blocked<NP, NW>(sS, invd, &fail);
+    const bool ok = potrf_blocked<NP, NW, !MIXED>(sS, invd, &fail);
     if (!ok) {
         if (tid == 0) atomicMin(P.info, (unsigned long long)d.i);
         return;

@@ -149,7 +149,12 @@ struct PanelStep {
     double m;   // lane i + 4b + 16k: M[i][k]
     double y1, y2, y3;  // minus the factored column's blocks below the diagonal, as A operands
 };
-template <int KB, class V>
+// OWN: the block's own rows are the factor as computed.  Q M^T repeats them with
+// an error that grows with the block's condition, which the sweeps' tile inverse
+// does not share; a factor that is rounded to FP32 hides it up to a condition of
+// 5e8, beyond what its FP32 Schur products stand, and goes without (18 selects a
+// step: 2% of the factorization at n = 50).
+template <int KB, bool OWN, class V>
 __device__ __forceinline__ PanelStep panel_diag(V& Q, bool& ok, int lane) {
     const int r = lane & 15, c = lane >> 4, i = lane & 3;
     const double q = Q[KB];
@@ -173,13 +178,14 @@ __device__ __forceinline__ PanelStep panel_diag(V& Q, bool& ok, int lane) {
     PanelStep s{};
     s.m = i == 0 ? x0 : i == 1 ? x1 : i == 2 ? x2 : x3;
     const double xq = mma4(s.m, q, 0.0);
-    // the block's own rows are the factor as computed above: Q M^T would repeat
-    // them with an error that grows with the block's condition
-    const double l0 = i == 0 ? d00 * r0 : i == 1 ? l10 : i == 2 ? l20 : l30;
-    const double l1 = i == 1 ? p1 * r1 : i == 2 ? l21 : l31;
-    const double l2 = i == 2 ? p2 * r2 : l32;
-    const double own = c == 0 ? l0 : c == 1 ? l1 : c == 2 ? l2 : p3 * r3;
-    const double x = (r >> 2) == KB ? own : xq;
+    double x = r >= 4 * KB + c ? xq : 0.0;
+    if constexpr (OWN) {
+        const double l0 = i == 0 ? d00 * r0 : i == 1 ? l10 : i == 2 ? l20 : l30;
+        const double l1 = i == 1 ? p1 * r1 : i == 2 ? l21 : l31;
+        const double l2 = i == 2 ? p2 * r2 : l32;
+        const double own = c == 0 ? l0 : c == 1 ? l1 : c == 2 ? l2 : p3 * r3;
+        x = (r >> 2) == KB ? own : xq;
+    }
     Q[KB] = x;
     if constexpr (KB < 3) {
         // the next diagonal block first
@@ -225,7 +231,8 @@ __device__ __forceinline__ void panel_rest(V& E, V (&S)[TB], const PanelStep& s)
 // upper part.  *fail (LDS, 0 on entry) becomes the mark of the first panel with a
 // non-positive or NaN pivot; the result is then false for every thread, after the
 // same barrier.
-template <int NP, int NW>
+// OWN: as in panel_diag.
+template <int NP, int NW, bool OWN>
 __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __restrict__ invd, int* fail) {
     using Lay = PackedLds;
     constexpr int NTL = NP / kT;
@@ -252,10 +259,10 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
         bool ok = true;
 #pragma unroll
         for (int j = 0; j < 4; ++j) E[j] = 4 * j + c == r ? 1.0 : 0.0;
-        panel_rest<TB, 0>(E, S, panel_diag<0>(Q, ok, lane));
-        panel_rest<TB, 1>(E, S, panel_diag<1>(Q, ok, lane));
-        panel_rest<TB, 2>(E, S, panel_diag<2>(Q, ok, lane));
-        panel_rest<TB, 3>(E, S, panel_diag<3>(Q, ok, lane));
+        panel_rest<TB, 0>(E, S, panel_diag<0, OWN>(Q, ok, lane));
+        panel_rest<TB, 1>(E, S, panel_diag<1, OWN>(Q, ok, lane));
+        panel_rest<TB, 2>(E, S, panel_diag<2, OWN>(Q, ok, lane));
+        panel_rest<TB, 3>(E, S, panel_diag<3, OWN>(Q, ok, lane));
         if (!ok && lane == 0) __hip_atomic_store(fail, panel_mark(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
