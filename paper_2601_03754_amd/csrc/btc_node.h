@@ -1,5 +1,6 @@
 // Factorization level step with one workgroup per node for block sizes
-// n <= 64, every block in registers as 16 x 16 tiles.
+// n <= 64, every block in registers as 16 x 16 tiles (NTL of them a side, as many
+// as n needs: every tile row holds rows of the block).
 //
 // Per node i of level l (stride s, h = s/2; Algorithm 4, hybrid left/right-
 // looking, deterministic ownership):
@@ -165,7 +166,6 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
     const int w = NTL == 1 ? 0 : wave_id();
     const int64_t N = P.N;
     const int n = P.n;
-    const int nt = (n + kT - 1) / kT;
     const size_t nn = (size_t)n * n;
     const int64_t s = (int64_t)1 << lvl;
     const int64_t h = s >> 1;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
     // pair d of this wavefront: the other tile row, and whether there is one
     auto other = [&](int d) { return d == 0 ? w : (w + d) % NTL; };
     auto pair_on = [&](int d) {
-        return (2 * d < NTL || (2 * d == NTL && w < NTL / 2)) && w < nt && other(d) < nt;
+        return 2 * d < NTL || (2 * d == NTL && w < NTL / 2);
     };
     // Register v of pair d's accumulator is an element of tile (y, w) of S_i or
     // S_{i+s}, y = other(d), always one of the lower triangle's tile (ta, tb):
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
 #pragma unroll
         for (int b = 0; b < NTL; ++b) {
             X[2][b] = d4{0.0, 0.0, 0.0, 0.0};
-            if (NTL > 1 && a > 0 && a < nt && b <= a) load_img(X[2][b], iS + (a * (a + 1) / 2 + b) * kImg);
+            if (NTL > 1 && a > 0 && b <= a) load_img(X[2][b], iS + (a * (a + 1) / 2 + b) * kImg);
         }
     }
     auto tri = [](int x, int y) { return (x * (x + 1) / 2 + y) * kImg; };
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
     const auto rL = rsrc(Lf + (size_t)pi * nn, true);
     const auto rR = rsrc(Rf + (size_t)pi * nn, has_r), rT = rsrc(Tf + (size_t)pi * nn, has_l);
 #pragma unroll (NTL >= 3 ? 1 : NTL)
-    for (int p = 0; p < (NTL >= 3 ? nt : NTL); ++p) {
+    for (int p = 0; p < NTL; ++p) {
         d4 E;
 #pragma unroll
         for (int v = 0; v < 4; ++v) E[v] = 4 * v + c == r ? 1.0 : 0.0;
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         for (int t = 0; t < (kRowLds ? 2 : TB); ++t) Y[t] = X[t][0];
         if constexpr (kRowLds) {
             Y[2] = d4{0.0, 0.0, 0.0, 0.0};
-            if (a > p && a < nt) load_img(Y[2], iS + tri(a, p));
+            if (a > p) load_img(Y[2], iS + tri(a, p));
         }
         bool ok = true;
         const int left = n - kT * p;  // steps past n are the identity
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         // lane or past the block's end); R_i follows from its images.  L_ii
         // below and on the diagonal of a diagonal tile, its inverse transposed
         // above it
-        const bool below = NTL > 1 && a > p && a < nt;
+        const bool below = NTL > 1 && a > p;
         const int rows = kT * w + r, col = kT * p * (int)sizeof(F);
         const int own = (rows * n + c) * (int)sizeof(F);
 #pragma unroll
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         X[1][0] = Y[1];
         if constexpr (NTL == 1) continue;
         if constexpr (NTL >= 3) {
-            if (p + 1 < nt) {
+            if (p + 1 < NTL) {
                 double* const img = kRowLds ? iS + tri(a, p) : iL + ((p & 1) * (NTL - 1) + a - 1 - p) * kImg;
                 if (below) {
                     store_img(img, Y[TB - 1]);
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         }
 #pragma unroll
         for (int q = 1; q < NTL; ++q) {
-            if (p + q >= nt) break;
+            if (p + q >= NTL) break;
             d4 lq;
             if constexpr (kRowLds) load_img(lq, iS + tri(p + q, p));
             else if constexpr (NTL >= 3) load_img(lq, iL + ((p & 1) * (NTL - 1) + q - 1) * kImg);
@@ -514,17 +514,13 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         for (int v = 0; v < 4; ++v) ((F*)iS)[po[v]] = (F)X[0][0][v];
         wave_lds_sync();
     }
-    if (w < nt) {
-        const F* const img = NTL == 1 ? (const F*)iS : iR + w * NTL * kImg;
+    const F* const img = NTL == 1 ? (const F*)iS : iR + w * NTL * kImg;
 #pragma unroll
-        for (int p = 0; p < NTL; ++p) {
-            if (p >= nt) break;
+    for (int p = 0; p < NTL; ++p)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                buf_st(img[p * kImg + tp[v]], rR, r < n - kT * p ? lo : kOob,
-                       ((kT * w + 4 * v) * n + kT * p) * (int)sizeof(F));
-        }
-    }
+        for (int v = 0; v < 4; ++v)
+            buf_st(img[p * kImg + tp[v]], rR, r < n - kT * p ? lo : kOob,
+                   ((kT * w + 4 * v) * n + kT * p) * (int)sizeof(F));
 
     // 3. separator update and fill
     auto load_op = [&](F (&x)[4], const F* img, const d4& reg) {
@@ -535,48 +531,35 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
         }
     };
     const auto rp = rsrc(P.Ld + (size_t)pr * nn, true);
-    auto sep_update = [&](auto full) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (!pair_on(d)) continue;
-            Acc acc = {};
+    for (int d = 0; d < D; ++d) {
+        if (!pair_on(d)) continue;
+        Acc acc = {};
 #pragma unroll
-            for (int p = 0; p < NTL; ++p) {
-                if (!full && p >= nt) break;
-                F x[4], y[4];
-                load_op(x, iR + (other(d) * NTL + p) * kImg, X[0][0]);
-                load_op(y, iR + (w * NTL + p) * kImg, X[0][0]);
-                PR::template tile<false>(acc, x, y);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) buf_st(sep[d][v] - (double)acc[v], rp, at(d, v), v * step(d));
+        for (int p = 0; p < NTL; ++p) {
+            F x[4], y[4];
+            load_op(x, iR + (other(d) * NTL + p) * kImg, X[0][0]);
+            load_op(y, iR + (w * NTL + p) * kImg, X[0][0]);
+            PR::template tile<false>(acc, x, y);
         }
-    };
+#pragma unroll
+        for (int v = 0; v < 4; ++v) buf_st(sep[d][v] - (double)acc[v], rp, at(d, v), v * step(d));
+    }
+    if (!has_l) return;
     Acc f[NTL];
 #pragma unroll
     for (int b = 0; b < NTL; ++b) f[b] = Acc{};
-    auto fill = [&](auto full) {
 #pragma unroll
-        for (int p = 0; p < NTL; ++p) {
-            if (!full && p >= nt) break;
-            F y[4];
-            load_op(y, iT + (w * NTL + p) * kImg, X[1][0]);
+    for (int p = 0; p < NTL; ++p) {
+        F y[4];
+        load_op(y, iT + (w * NTL + p) * kImg, X[1][0]);
 #pragma unroll
-            for (int b = 0; b < NTL; ++b) {
-                if (!full && b >= nt) break;
-                F x[4];
-                load_op(x, iR + (b * NTL + p) * kImg, X[0][0]);
-                PR::template tile<true>(f[b], x, y);
-            }
+        for (int b = 0; b < NTL; ++b) {
+            F x[4];
+            load_op(x, iR + (b * NTL + p) * kImg, X[0][0]);
+            PR::template tile<true>(f[b], x, y);
         }
-    };
-    // (all tile rows in use: no branch between the products, so that the LDS
-    // reads of the next run under them)
-    if (nt == NTL) sep_update(std::true_type{});
-    else sep_update(std::false_type{});
-    if (!has_l || w >= nt) return;
-    if (nt == NTL) fill(std::true_type{});
-    else fill(std::false_type{});
+    }
     const int64_t lft = i - s, rgt = i + s;
     const auto rf = rsrc((((lft >> (lvl + 1)) & 1) != 0) ? Rf + (size_t)perm_pos(N, lvl + 1, lft) * nn
                                                          : Tf + (size_t)perm_pos(N, lvl + 1, rgt) * nn,
