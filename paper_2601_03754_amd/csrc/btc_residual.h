@@ -128,14 +128,13 @@ __global__ __launch_bounds__(NTL / res_rows<NTL>() * kWave, NTL >= 6 ? (MC == 1 
         const double v = x[ok ? (size_t)row * m + q : 0];
         return ok ? v : 0.0;
     };
-    double xn[RW][MC], xw[4], xr[4];
+    static_assert(W * kWave >= NTL * kT, "a thread per row");
+    const int row = threadIdx.x;
+    double xn[MC], xw[4], xr[4];
     // x_i for all wavefronts
     auto fetch_x = [&](int q0) {
 #pragma unroll
-        for (int h = 0; h < RW; ++h)
-#pragma unroll
-            for (int j = 0; j < MC; ++j)
-                xn[h][j] = vec(x1, threadIdx.x + h * W * kWave, q0 + j, (int)threadIdx.x + h * W * kWave < NTL * kT);
+        for (int j = 0; j < MC; ++j) xn[j] = vec(x1, row, q0 + j, row < NTL * kT);
     };
     // x_i and x_{i+1} of tile row a as B operands
     auto fetch_row = [&](int a, int q0) {
@@ -167,11 +166,9 @@ __global__ __launch_bounds__(NTL / res_rows<NTL>() * kWave, NTL >= 6 ? (MC == 1 
     }
 
     for (int q0 = 0; q0 < m; q0 += MC) {
+        if (row < NTL * kT)
 #pragma unroll
-        for (int h = 0; h < RW; ++h)
-            if ((int)threadIdx.x + h * W * kWave < NTL * kT)
-#pragma unroll
-                for (int j = 0; j < MC; ++j) xs[threadIdx.x + h * W * kWave][j] = xn[h][j];
+            for (int j = 0; j < MC; ++j) xs[row][j] = xn[j];
         __syncthreads();
         double cr[NTL];
 #pragma unroll

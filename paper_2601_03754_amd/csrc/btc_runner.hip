@@ -62,7 +62,7 @@ struct Group {
     int stage = 0;
     int op;    // btc_op
     int kind;  // FACTOR: factor kernel family (factor_kind); sweeps: 0 double, 1 float,
-               // 2 / 3 the same over level ranges (subtree launches)
+               // 2 / 3 the same over level ranges (shared launches)
     bool deferred = false;  // FACTOR: some item has deferred updates to apply
     int m_max = 1;   // sweeps / residual: largest number of right-hand sides
     int n_max = 1;   // sweeps / residual: largest block (the launch pads to it)
@@ -570,8 +570,8 @@ void write_call(const Call& c, char* host, char* dev) {
 }
 
 // Enqueue the call (its descriptors already in `dev`): the work items where
-// they are expanded on the device, status resets, then the groups stage by stage, the independent groups of a stage spread over
-// the runner's streams.
+// they are expanded on the device, status resets, then the groups stage by
+// stage, the independent groups of a stage spread over the runner's streams.
 int launch_call(btc_runner r, Call& c, char* dev, hipStream_t st, bool timing) {
     hipError_t e = hipSuccess;
     auto& groups = c.groups;

@@ -15,8 +15,9 @@
 //       strip by strip (one 16-row or 16-column strip per wavefront at a time,
 //       blocked substitution with the inverted diagonal tiles, all products
 //       MFMA, the solved tiles kept in registers as the products' B operand)
-//   K4  S_{i+s} -= R_i R_i^T (lower tiles) and the fill -R_i T_i: from 192
-//       nodes on one workgroup per node, below one per 32 x 32 tile
+//   K4  S_{i+s} -= R_i R_i^T (lower tiles) and the fill -R_i T_i: one workgroup
+//       per 32 x 32 tile; from 192 nodes on, padded size 64 and up and without
+//       BF16 products, one per node
 // In mixed precision the Schur complements and K2 stay FP64 (its solves too;
 // R_i and T_i are rounded to FP32 when stored) and the products of K1 and K4
 // run on FP32 matrix cores (FP32 factor storage); the BF16

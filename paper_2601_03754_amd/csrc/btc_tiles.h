@@ -351,8 +351,6 @@ __device__ __forceinline__ bool potrf_blocked(double* __restrict__ A, double* __
 // ---------------------------------------------------------------------------
 // FP32 tiles
 
-__device__ __forceinline__ int acc32_r(int v, int lane) { return 4 * (lane >> 4) + v; }
-
 // acc += (NEG ? -1 : 1) * sum_{kk<K} opA[ra+i][ka+kk] * opB[kb+kk][cb+j] with the
 // operands rounded to BF16 (round to nearest even) and FP32 accumulation
 // (v_mfma_f32_16x16x32_bf16: lane l holds A[l%16][8(l/16)+e] and
