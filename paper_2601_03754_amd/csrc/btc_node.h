@@ -156,13 +156,16 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
     buf_ld(state, block_rsrc(P.info, 8), 0);
 
     const int lane = threadIdx.x & 63;
-    const int r = lane & 15, c = lane >> 4;
+    int r = lane & 15, c = lane >> 4;
     int po[4], tp[4];  // image positions of the register form and of its transpose
+    auto positions = [&]() {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        po[v] = img_pos(r, 4 * v + c);
-        tp[v] = img_pos(4 * v + c, r);
-    }
+        for (int v = 0; v < 4; ++v) {
+            po[v] = img_pos(r, 4 * v + c);
+            tp[v] = img_pos(4 * v + c, r);
+        }
+    };
+    positions();
     const int w = NTL == 1 ? 0 : wave_id();
     const int64_t N = P.N;
     const int n = P.n;
@@ -507,6 +510,10 @@ __global__ __launch_bounds__(NTL * kWave, node_waves(NTL)) void k_factor_node(La
             for (int t = 0; t < (kRowLds ? 2 : TB); ++t) X[t][q - 1] = X[t][q];
     }
     if (!has_r) return;
+    // the addresses of the stores below are formed anew: kept through the panels
+    // they leave too few registers there (spills at four tile rows)
+    asm volatile("" : "+v"(r), "+v"(c));
+    positions();
     if constexpr (NTL > 1) {
         __syncthreads();
     } else {
