@@ -587,7 +587,7 @@ def step(h: int, op: int, level: int = 0, A_diag=None, A_off=None, B=None, X=Non
 
 
 def btc_sweep_ranges(N: int):
-    """Level ranges the library runs a sweep in (bounds, 0 .. levels)."""
+    """Level ranges a caller may step a sweep in (bounds, 0 .. levels)."""
     b = (i32 * 70)()
     r = lib().btc_sweep_ranges(N, b, 70)
     if r < 0:

@@ -266,8 +266,9 @@ struct Workspace {
 // 127 / 129; N = 2000, n = 96: 237 / 235 / 235 / 243; N = 200, n = 8: 42 / 42 / 42 /
 // 44.  Refined solves launch the rounds after the last as well: N = 1000, n =
 // 32: 235 / 222 / 224 / 236; N = 800, n = 64: 292 / 290 / 293 / 306.  Above n = 96
-// a level of some hundred nodes fills the GPU with block loads either way: N =
-// 1023, n = 128, m = 5: 290 with 1024, 304 with 128.
+// a level of some hundred nodes fills the GPU with block loads either way, 1024 /
+// 256 / 128: N = 1023, n = 128: 224 / 232 / 240 (m = 1), 295 / 307 / 313 (m = 5), 482 /
+// 532 / 571 (mixed); N = 4096: 678 / 687 / 699; n = 100: 568 / 568 / 573.
 inline int64_t flow_limit(int32_t prec, int64_t n) {
     return n > 96 ? 1024 : is_mixed(prec) ? 256 : 128;
 }
@@ -580,8 +581,13 @@ inline int launch_factor(btc_handle h, const double* A_diag, const double* A_off
 // 2 342 us, FP64 1 383 / 1 052 / 1 066; 200 up to 1000, mixed 9 446 / 9 608 / 8 719,
 // FP64 4 407 / 4 090 / 4 063; 512 up to 2048, FP64 15 473 / 14 999 / 14 838.
 constexpr int64_t kFlowNodesBatch = 16384;
-// Served instances, which share launches as they happen to meet.
-constexpr int64_t kFlowNodesServed = 1024;
+// Served instances, which share launches as they happen to meet; a shared launch
+// is one tick, and a long one holds up the instances of its lane.  Measured, served
+// mix of 256 clients with --sweep-ranges, mixed requests/s (p99): 16 nodes 16 350 (51
+// ms), 32 17 400 (56), 64 17 600 (62), 128 15 700 (70), 256 13 100 (82), 1024 7 760
+// (114); FP64: 27 600 (38), 27 400 (38), 26 100 (40), 27 100 (46), 23 700 (50),
+// 17 900 (65).
+constexpr int64_t kFlowNodesServed = 32;
 // Sweep launch shapes (tune key BTC_TUNE_SWEEP_SHAPE): 0 as above, 1 one
 // launch per level, 2 the shared launch starting at twice the limit, one level
 // lower (all levels of a large batch in one launch would make its sweeps four

@@ -252,8 +252,8 @@ int admit_client(btc_server s, Client& c, int64_t nrhs) {
 
 // The steps of a request, in order, grouped into ticks; within a tick a
 // request's steps run in successive stages of one runner call (a step
-// marked par shares its predecessor's stage).  Sweeps run in the library's
-// level ranges (sweep_ranges): one tick per range.
+// marked par shares its predecessor's stage).  Sweeps run level by level, or
+// (option sweep_ranges) with the levels of few nodes in one range: one tick each.
 //   * A refactor+solve request interlaces the factorization with the first
 //     forward sweep (the paper's interlaced factor and forward substitution,
 //     section "Fused and Blocked Kernels"): a forward range ending at level l

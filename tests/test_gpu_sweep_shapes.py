@@ -83,3 +83,33 @@ def test_refinements_that_end_in_different_rounds(large):
     for h in hs:
         btc.btc_destroy(h)
     r.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_served_ranges_share_only_small_levels(precision):
+    """A server in level ranges: one tick of a whole long sweep would hold up
+    every other request of its lane, so only levels of a few nodes (up to 32)
+    share a launch (kind 2 / 3 of the launch profile); the rest run level by level."""
+    from paper_2601_03754_amd import btc
+
+    N, n = 1000, 12
+    pr = inputs.block_tridiag(N, n, seed=3)
+    D, E, B = dev(pr.D), dev(pr.E), dev(pr.B)
+    X = torch.empty_like(B)
+    srv = btc.Server(precision=precision, sweep_ranges=True)
+    c = srv.add_client(N, n)
+    for r in srv.runner_handles():
+        btc.runner_profile(r, FORWARD, -1)
+    srv.submit(c, B, X, A=(D, E))
+    done = []
+    while not done:
+        srv.step()
+        done = srv.poll()
+    torch.cuda.synchronize()
+    stats = [s for r in srv.runner_handles() for s in btc.runner_profile_read(r)]
+    own = [s for s in stats if s["kind"] == precision]
+    shared = [s for s in stats if s["kind"] == 2 + precision]
+    srv.close()
+    assert sum(s["launches"] for s in own) >= 5 and sum(s["launches"] for s in shared) >= 1
+    assert all(s["items"] <= 64 * s["launches"] for s in shared)  # N >> l nodes from level l up
+    assert oracle.relres(pr.D, pr.E, X.cpu().numpy(), pr.B) <= (1e-12 if precision == 0 else 1e-10)
