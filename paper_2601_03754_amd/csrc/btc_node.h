@@ -27,18 +27,18 @@
 // rows of 16 elements instead of sixteen rows of 4.
 //
 // What bounds it: large launches the memory (level 0 of N = 65 536, n = 32,
-// FP64: 453 us for 72 KiB a node, 5.2 TB/s), small ones a node's own latency,
+// FP64: 462 us for 72 KiB a node, 5.1 TB/s), small ones a node's own latency,
 // of which the chains of 4-column steps are about a third, issuing the loads
 // (all of them before the first use; from n = 33 on except T'') a fifth, the
 // products the rest.  Measured against the kernels it replaces (blocks in LDS,
 // the couplings' solves after the Cholesky factorization), one node of an
-// inner level: n = 16 FP64 10.1 -> 6.9 us, n = 32 19.5 -> 12.1 (mixed, tile-
-// parallel there: 16.4 -> 11.3), n = 8 (vector ALUs) 7.9 -> 6.5; at n = 33..64
-// the tile-parallel step takes as long per node in FP64 (24.1 / 26.3 at n =
-// 64) and longer in mixed precision (27.2 / 22.4), and is slower on wide levels
-// (2048 nodes of n = 64: 156 / 137).  n = 33..48 has a kernel of three tile rows
-// (N = 32 768, n = 48: 1 778 us with four, 1 584 with three; mixed 1 460, 1 302;
-// an inner level 21.2 and 18.9).
+// inner level: n = 16 FP64 10.1 -> 7.1 us, n = 32 19.5 -> 11.9 (mixed, tile-
+// parallel there: 16.4 -> 11.2), n = 8 (vector ALUs) 7.9 -> 6.7; at n = 33..64
+// the tile-parallel step takes as long per node in FP64 (24.5 / 25.5 at n =
+// 64) and longer in mixed precision (24.7 / 22.4), and is slower on wide levels
+// (2048 nodes of n = 64: 157 / 139).  n = 33..48 has a kernel of three tile rows
+// (N = 32 768, n = 48: 1 778 us with four, 1 594 with three; mixed 1 460, 1 318;
+// an inner level 21.2 and 18.6).
 //
 // MODE 0: FP64.  MODE 1 (mixed precision): S_j, the Cholesky factorization and
 // the triangular solves in FP64; L_ii, R_i, T_i and the fill rounded to FP32;

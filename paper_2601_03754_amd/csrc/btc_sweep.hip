@@ -33,10 +33,9 @@
 //   * the upper levels run in one launch (k_sweep_flow), whose workgroups have
 //     their blocks in registers when the vectors they wait for arrive.
 // Measured, before and after: N = 4096, n = 96, one right-hand side, FP64:
-// forward 560 -> 223 us, backward 480 -> 217 us (level 0, 377 MB: 94 us, 4.0
-// TB/s; the twelve upper levels in one launch 129 us; a level of its own
-// launch 11 us instead of 40); N = 1023, n = 128, five right-hand sides: whole
-// solve 2 855 -> 291 us.
+// forward 560 -> 228 us, backward 480 -> 226 us (level 0, 377 MB: 94 us, 4.0
+// TB/s; the nine upper levels in one launch 49 us; a level of 256 nodes 14);
+// N = 1023, n = 128, five right-hand sides: whole solve 2 855 -> 291 us.
 #include <type_traits>
 
 #include "btc_device.h"

@@ -275,7 +275,7 @@ constexpr int k2_blocks() { return NP <= 64 ? 4 : NP <= 96 ? 2 : 1; }
 // latency, not by the throughput of nodes sharing a unit: it takes one
 // wavefront per strip, so that all strips are solved in one round (measured
 // when the rule was made, N = 4096, upper levels, padded size 96, twelve
-// wavefronts against eight: 38 / 43 us FP64, 44 / 53 mixed; now 29 and 30 with
+// wavefronts against eight: 38 / 43 us FP64, 44 / 53 mixed; now 30 and 31 with
 // twelve; padded size 64 eight, 128 sixteen).
 constexpr int kK2LatencyWaves = 12;
 constexpr int64_t kK2LatencyItems = 256;

@@ -141,9 +141,8 @@ __device__ __forceinline__ double mma4(double a, double b, double c) {
 // of the diagonal tile.  The chain it replaces held one row per lane and
 // broadcast every multiplier by readlane (16 steps of about 300 cycles a
 // panel), with the diagonal tiles inverted at the end.  Measured, one node of
-// n = 96 alone in its launch: k_tiled_potrf_trsm 35.5 -> 28.4 us in FP64, and
-// with no strips to solve 25.5 -> 17.7; factorization at N = 4096: 1 366 ->
-// 1 239 us (n = 96), 609 -> 551 (n = 64, mixed); N = 1000, n = 32: 216 -> 193.
+// n = 96 alone in its launch: k_tiled_potrf_trsm 35.5 -> 29.6 us in FP64 (28.4
+// before it kept the block's own rows, OWN below); of n = 128 52.7 (49.9).
 // (panel_diag is the chain, panel_rest what hangs on it.)
 struct PanelStep {
     double m;   // lane i + 4b + 16k: M[i][k]
